@@ -381,10 +381,16 @@ int hz_dd_alpha(double k, double H, double h, int32_t sides, hz_c128* alpha);
  * numbering (elems set, order HZ_ORDER_GIVEN, sigma 0) the split values are
  * also stored in stencil form (HZ_SPMV_STENCIL, the solvers' choice there):
  * 27 slots per row at the fixed neighbour offsets of the box, a missing
- * neighbour's slot 0, no column indices.  Environment variables HZ_SPLIT=0
- * and HZ_STENCIL=0 (read when the context is created) disable the split
- * and the stencil forms. */
-enum { HZ_SPMV_SOLVER = 0, HZ_SPMV_COMPLEX = 1, HZ_SPMV_SPLIT = 2, HZ_SPMV_STENCIL = 3 };
+ * neighbour's slot 0, no column indices.  If the box's nodes moreover lie on
+ * a tensor-product grid and no Dirichlet source is set, the solvers, the
+ * adjoint and hz_apply use the tensor form (HZ_SPMV_TENSOR): no stored
+ * entries, the product is formed from the 1-D matrices of the axes, and a
+ * vector is read and written once (with an absorption field also 8 bytes per
+ * element).  HZ_SPMV_SOLVER keeps naming the stored form that stands in where
+ * the tensor form does not apply.  Environment variables HZ_TENSOR=0,
+ * HZ_STENCIL=0 and HZ_SPLIT=0 (read when the context is created) disable the
+ * tensor, the tensor and stencil, and all three forms. */
+enum { HZ_SPMV_SOLVER = 0, HZ_SPMV_COMPLEX = 1, HZ_SPMV_SPLIT = 2, HZ_SPMV_STENCIL = 3, HZ_SPMV_TENSOR = 4 };
 
 /* Measurement of the sparse product (paper Sec. 4: the product dominates
  * the solve time).  Runs y = A x of the current operator `reps` times
@@ -392,9 +398,9 @@ enum { HZ_SPMV_SOLVER = 0, HZ_SPMV_COMPLEX = 1, HZ_SPMV_SPLIT = 2, HZ_SPMV_STENC
  * on that stream, and returns the average duration of one product in
  * milliseconds.  precision HZ_FP64 times the complex128 product of the FP64
  * solvers; HZ_MIXED the complex64 product of the mixed-precision inner
- * solves.  format: HZ_SPMV_SOLVER (the form the solvers use),
- * HZ_SPMV_COMPLEX, HZ_SPMV_SPLIT or HZ_SPMV_STENCIL (HZ_ERR_STATE if that
- * form is not formed).  x and y are internal buffers.  Host result; synchronises the
+ * solves.  format: HZ_SPMV_SOLVER (the stored form the solvers use),
+ * HZ_SPMV_COMPLEX, HZ_SPMV_SPLIT, HZ_SPMV_STENCIL or HZ_SPMV_TENSOR
+ * (HZ_ERR_STATE if that form is not formed).  x and y are internal buffers.  Host result; synchronises the
  * stream. */
 int hz_time_spmv(hz_ctx ctx, int32_t reps, int32_t precision, int32_t format, double* avg_ms);
 

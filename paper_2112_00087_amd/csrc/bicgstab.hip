@@ -1,12 +1,12 @@
 // Stabilised bi-conjugate gradient method (the paper's P-BiCGSTAB, Sec. 4)
 // on the right-Jacobi operator, for every segment of a segmented system.
 //
-// One iteration of van der Vorst's method is five vector kernels (two of
-// them sparse products with fused inner-product epilogues) and three
-// one-block-per-segment finalize kernels that turn block partials into the
-// Krylov scalars (the early-exit test on ||s|| rides on the omega step).
-// The scalars never leave the device; the host only reads the per-segment
-// state every few iterations to decide whether to stop.
+// One iteration of van der Vorst's method is five kernels, two of them
+// products.  The scalar steps (alpha, omega, rho and beta) run at the start
+// of the kernel that needs them (advance), on a state that moves through
+// three slots.  The early-exit test on ||s|| rides on the omega step.  The
+// scalars never leave the device; the host reads the per-segment state every
+// few iterations, one chunk behind.
 // Every kernel first reads its segment's flags and returns if that segment
 // has converged, so extra queued iterations cost only empty launches.
 #include <chrono>
@@ -20,7 +20,7 @@ struct BiSt {
   z_t beta;                       // (rho / rho_old) (alpha / omega) for the next p update
   double rr, ss, thr2, rhat2;
   int iter, done, early, reset;
-  int nan, pad0;
+  int nan, pend;                  // pend: the sums of the rho step are formed
 };
 
 template <typename T>
@@ -38,187 +38,198 @@ struct BiV {
 template <typename T> __device__ __forceinline__ z_t zd(cx<T> a) { return ccast<double>(a); }
 template <typename T> __device__ __forceinline__ cx<T> zt(z_t a) { return ccast<T>(a); }
 
+// ---- the scalar steps, run by one thread once a segment's sums are complete
+__device__ __forceinline__ void bi_resid(BiSt& S, const double* o) {
+  const double rr = o[0];
+  S.rr = rr;
+  S.rho = z_t{rr, 0.0};
+  S.rho_old = S.alpha = S.omega = z_t{1.0, 0.0};
+  S.beta = z_t{rr, 0.0};
+  S.rhat2 = rr;
+  S.early = 0;
+  S.reset = 0;
+  S.pend = 0;
+  S.nan = !isfinite(rr);
+  S.done = (rr <= S.thr2) || S.nan;
+}
+__device__ __forceinline__ void bi_alpha(BiSt& S, const double* o) {
+  S.reset = 0;
+  const z_t rv = {o[0], o[1]};
+  if (norm2(rv) == 0.0 || !isfinite(o[0]) || !isfinite(o[1])) {
+    S.alpha = z_t{0.0, 0.0};   // minimal-residual step this iteration, restart after it
+    S.reset = 1;
+  } else {
+    S.alpha = cdiv(S.rho, rv);
+  }
+}
+// omega = t^H s / t^H t, or the early exit when ||s|| already meets the target
+// (then x += alpha p completes the iteration).
+__device__ __forceinline__ void bi_omega(BiSt& S, const double* o) {
+  const double re = o[0], im = o[1], tt = o[2], ss = o[3];
+  S.ss = ss;
+  S.early = (ss <= S.thr2) ? 1 : 0;
+  S.omega = (tt > 0.0 && !S.early) ? z_t{re / tt, im / tt} : z_t{0.0, 0.0};
+  S.pend = 1;                // k_xr forms the sums of the rho step
+}
+__device__ __forceinline__ void bi_rho(BiSt& S, const double* o) {
+  S.pend = 0;
+  if (S.early) {
+    S.iter += 1;
+    S.rr = S.ss;
+    S.done = 1;
+    S.early = 0;
+    return;
+  }
+  const double re = o[0], im = o[1], rr = o[2];
+  S.iter += 1;
+  S.rho_old = S.rho;
+  S.rho = z_t{re, im};
+  S.rr = rr;
+  if (!isfinite(rr) || !isfinite(re) || !isfinite(im)) {
+    S.nan = 1;
+    S.done = 1;
+  } else if (rr <= S.thr2) {
+    S.done = 1;
+  } else if (sqrt(norm2(S.rho)) < 1e-300 * sqrt(S.rhat2 * rr) || norm2(S.omega) == 0.0) {
+    // breakdown: restart the shadow residual from the current residual
+    S.reset = 1;
+    S.rho = z_t{rr, 0.0};
+    S.rho_old = S.alpha = S.omega = z_t{1.0, 0.0};
+    S.rhat2 = rr;
+  }
+  S.beta = cdiv(S.rho, S.rho_old) * cdiv(S.alpha, S.omega);
+}
+
+__device__ __forceinline__ bool bi_on(const BiSt& S) { return !S.done; }
+__device__ __forceinline__ bool bi_pending(const BiSt& S) { return S.pend; }
+
+// The state after the sums formed last: in place after k_resid (the slot the
+// next iteration starts from), for the host after k_xr.
+__global__ void __launch_bounds__(kBlock) k_bi_resid(Part P, BiSt* st) {
+  advance_alone<1>(P, st, st, [](const BiSt&) { return true; }, bi_resid);
+}
+// Before a restart the slot an iteration starts from takes up the pending sums.
+__global__ void __launch_bounds__(kBlock) k_bi_settle(Part P, BiSt* st) {
+  advance_alone<3>(P, st, st, bi_pending, bi_rho);
+}
+__global__ void __launch_bounds__(kBlock) k_bi_report(Part P, const BiSt* in, BiSt* out) {
+  advance_alone<3>(P, in, out, bi_pending, bi_rho);
+}
+
 // r = f - A u; restart: rhat = r, p = v = 0.  Partial ||r||^2.
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_resid(Seg L, SellOp<T> A, BiV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
-  z_t y = zd(sell_row_form<F>(A, t.row, V.u));
-  z_t r = zd(V.f[t.row]) - y;
-  cx<T> rs = zt<T>(r);
-  V.r[t.row] = rs;
-  V.rhat[t.row] = rs;
-  V.p[t.row] = cx<T>{T(0), T(0)};
-  V.v[t.row] = cx<T>{T(0), T(0)};
-  z_t rr = zd(rs);
-  double q[1] = {norm2(rr)};
+  SumTile t = prod_tile_sums<F>(L);
+  double q[1] = {0.0};
+  for_rows<F>(A, t, V.u, [=](int64_t row) { return V.f[row]; },
+              [&](int64_t row, cx<T> y, cx<T> f) {
+                const cx<T> rs = zt<T>(zd(f) - zd(y));
+                V.r[row] = rs;
+                V.rhat[row] = rs;
+                V.p[row] = cx<T>{T(0), T(0)};
+                V.v[row] = cx<T>{T(0), T(0)};
+                q[0] += norm2(zd(rs));
+              });
   store_partials<1>(q, part, t);
 }
 
-__global__ void k_resid_fin(Seg L, BiSt* st, const double* part) {
-  int s = blockIdx.x;
-  double o[1];
-  seg_sums<1>(L, part, s, o);
-  if (threadIdx.x == 0) {
-    const double rr = o[0];
-    BiSt& S = st[s];
-    S.rr = rr;
-    S.rho = z_t{rr, 0.0};
-    S.rho_old = S.alpha = S.omega = z_t{1.0, 0.0};
-    S.beta = z_t{rr, 0.0};
-    S.rhat2 = rr;
-    S.early = 0;
-    S.reset = 0;
-    S.nan = !isfinite(rr);
-    S.done = (rr <= S.thr2) || S.nan;
-  }
-}
-
-// p = r + beta (p - omega v), beta = (rho / rho_old) (alpha / omega); on reset rhat = p = r.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_p(Seg L, const BiSt* st, BiV<T> V) {
-  Tile t = tile_of(L);
-  const BiSt& S = st[t.seg];
+// rho and beta; p = r + beta (p - omega v), beta = (rho / rho_old) (alpha / omega); on reset
+// rhat = p = r.  In the tensor form p is kept scaled by D^-1.
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_p(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V) {
+  const Tile t = vec_tile(L);
+  const BiSt& S = advance<3>(P, in, out, t, first_block(L, t), bi_pending, bi_rho);
   if (S.done) return;
-  cx<T> r = V.r[t.row];
+  const TzSeg B = form_seg<F>(Z, t);
   if (S.reset) {
-    V.rhat[t.row] = r;
-    V.p[t.row] = r;
+    vec_rows(L, t, [&](int64_t row) {
+      const cx<T> r = V.r[row];
+      V.rhat[row] = r;
+      V.p[row] = zt<T>(tz_pre<F>(Z, B, row, zd(r)));
+    });
     return;
   }
-  z_t p = zd(V.p[t.row]) - S.omega * zd(V.v[t.row]);
-  V.p[t.row] = zt<T>(zd(r) + S.beta * p);
+  const z_t beta = S.beta, omega = S.omega, bo = beta * omega;
+  vec_rows(L, t, [&](int64_t row) {
+    const z_t r = zd(V.r[row]), p = zd(V.p[row]), v = zd(V.v[row]);
+    if (F == kFormComplex) V.p[row] = zt<T>(r + beta * (p - omega * v));
+    else V.p[row] = zt<T>(tz_pre<F>(Z, B, row, r - bo * v) + beta * p);
+  });
 }
 
-// v = A p; partial rhat^H v.  Instantiated per storage form F of A (one
-// form per kernel keeps the register count, hence the occupancy, of that form).
+// v = A p; partial rhat^H v.  Instantiated per storage form F of A (one form
+// per kernel keeps the register count, hence the occupancy, of that form).
 template <typename T, int F>
 __global__ void HZ_PRODUCT_BOUNDS k_v(Seg L, SellOp<T> A, const BiSt* st, BiV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
+  SumTile t = prod_tile_sums<F>(L);
   if (st[t.seg].done) return;
-  cx<T> y = sell_row_form<F>(A, t.row, V.p);
-  V.v[t.row] = y;
-  z_t a = zd(V.rhat[t.row]), b = zd(y);
-  double q[2] = {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
+  double q[2] = {0.0, 0.0};
+  for_rows<F>(A, t, V.p, [=](int64_t row) { return V.rhat[row]; },
+              [&](int64_t row, cx<T> y, cx<T> rh) {
+                V.v[row] = y;
+                const z_t a = zd(rh), b = zd(y);
+                q[0] += a.re * b.re + a.im * b.im;
+                q[1] += a.re * b.im - a.im * b.re;
+              });
   store_partials<2>(q, part, t);
 }
 
-__global__ void k_alpha_fin(Seg L, BiSt* st, const double* part) {
-  int s = blockIdx.x;
-  const int done = st[s].done;
-  double o[2];
-  seg_sums<2>(L, part, s, o);
-  if (done) return;
-  if (threadIdx.x == 0) {
-    const double re = o[0], im = o[1];
-    BiSt& S = st[s];
-    S.reset = 0;
-    z_t rv = {re, im};
-    if (norm2(rv) == 0.0 || !isfinite(re) || !isfinite(im)) {
-      S.alpha = z_t{0.0, 0.0};   // minimal-residual step this iteration, restart after it
-      S.reset = 1;
-    } else {
-      S.alpha = cdiv(S.rho, rv);
-    }
-  }
-}
-
-// s = r - alpha v.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_s(Seg L, const BiSt* st, BiV<T> V) {
-  Tile t = tile_of(L);
-  const BiSt& S = st[t.seg];
+// alpha; s = r - alpha v (scaled by D^-1 in the tensor form).
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_s(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V) {
+  const Tile t = vec_tile(L);
+  const BiSt& S = advance<2>(P, in, out, t, first_block(L, t), bi_on, bi_alpha);
   if (S.done) return;
-  z_t s = zd(V.r[t.row]) - S.alpha * zd(V.v[t.row]);
-  V.s[t.row] = zt<T>(s);
+  const TzSeg B = form_seg<F>(Z, t);
+  const z_t alpha = S.alpha;
+  vec_rows(L, t, [&](int64_t row) {
+    V.s[row] = zt<T>(tz_pre<F>(Z, B, row, zd(V.r[row]) - alpha * zd(V.v[row])));
+  });
 }
 
-// t = A s; partials t^H s, t^H t, s^H s (per storage form F, as k_v).
+// t = A s; partials t^H s, t^H t, s^H s (s unscaled; per storage form F, as k_v).
 template <typename T, int F>
 __global__ void HZ_PRODUCT_BOUNDS k_t(Seg L, SellOp<T> A, const BiSt* st, BiV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
-  const BiSt& S = st[t.seg];
-  if (S.done) return;
-  cx<T> y = sell_row_form<F>(A, t.row, V.s);
-  V.t[t.row] = y;
-  z_t a = zd(y), b = zd(V.s[t.row]);
-  double q[4] = {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re, norm2(a), norm2(b)};
+  SumTile t = prod_tile_sums<F>(L);
+  if (st[t.seg].done) return;
+  const TzSeg B = form_seg<F>(A.tz, t);
+  double q[4] = {0.0, 0.0, 0.0, 0.0};
+  for_rows<F>(A, t, V.s, [&](int64_t row) { return tz_unpre<F>(A.tz, B, row, zd(V.s[row])); },
+              [&](int64_t row, cx<T> y, z_t b) {
+                V.t[row] = y;
+                const z_t a = zd(y);
+                q[0] += a.re * b.re + a.im * b.im;
+                q[1] += a.re * b.im - a.im * b.re;
+                q[2] += norm2(a);
+                q[3] += norm2(b);
+              });
   store_partials<4>(q, part, t);
 }
 
-// omega = t^H s / t^H t, or the early exit when ||s|| already meets the target
-// (then x += alpha p completes the iteration).
-__global__ void k_omega_fin(Seg L, BiSt* st, const double* part) {
-  int s = blockIdx.x;
-  const int done = st[s].done;
-  double o[4];
-  seg_sums<4>(L, part, s, o);
-  if (done) return;
-  if (threadIdx.x == 0) {
-    const double re = o[0], im = o[1], tt = o[2], ss = o[3];
-    BiSt& S = st[s];
-    S.ss = ss;
-    S.early = (ss <= S.thr2) ? 1 : 0;
-    S.omega = (tt > 0.0 && !S.early) ? z_t{re / tt, im / tt} : z_t{0.0, 0.0};
-  }
-}
-
-// u += alpha p + omega s; r = s - omega t; partials rhat^H r, ||r||^2.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_xr(Seg L, const BiSt* st, BiV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
-  const BiSt& S = st[t.seg];
+// omega; u += alpha p + omega s; r = s - omega t (s unscaled); partials rhat^H r, ||r||^2.
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_xr(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V, double* part) {
+  const SumTile t = vec_tile_sums(L);
+  const BiSt& S = advance<4>(P, in, out, t, first_block(L, t), bi_on, bi_omega);
   if (S.done) return;
-  z_t u = zd(V.u[t.row]) + S.alpha * zd(V.p[t.row]);
+  const TzSeg B = form_seg<F>(Z, t);
+  double q[3] = {0.0, 0.0, 0.0};
   if (S.early) {
-    V.u[t.row] = zt<T>(u);
-    return;
+    vec_rows(L, t, [&](int64_t row) { V.u[row] = zt<T>(zd(V.u[row]) + S.alpha * zd(V.p[row])); });
+  } else {
+    vec_rows(L, t, [&](int64_t row) {
+      const z_t u = zd(V.u[row]) + S.alpha * zd(V.p[row]);
+      const z_t s = zd(V.s[row]);
+      V.u[row] = zt<T>(u + S.omega * s);
+      const cx<T> r = zt<T>(tz_unpre<F>(Z, B, row, s) - S.omega * zd(V.t[row]));
+      V.r[row] = r;
+      const z_t a = zd(V.rhat[row]), b = zd(r);
+      q[0] += a.re * b.re + a.im * b.im;
+      q[1] += a.re * b.im - a.im * b.re;
+      q[2] += norm2(b);
+    });
   }
-  z_t s = zd(V.s[t.row]);
-  V.u[t.row] = zt<T>(u + S.omega * s);
-  cx<T> r = zt<T>(s - S.omega * zd(V.t[t.row]));
-  V.r[t.row] = r;
-  z_t a = zd(V.rhat[t.row]), b = zd(r);
-  double q[3] = {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re, norm2(b)};
   store_partials<3>(q, part, t);
-}
-
-__global__ void k_rho_fin(Seg L, BiSt* st, const double* part) {
-  int s = blockIdx.x;
-  BiSt& S = st[s];
-  const int done = S.done, early = S.early;
-  double o[3];
-  // (its barriers also see every thread's flags read before thread 0 rewrites them)
-  seg_sums<3>(L, part, s, o);
-  if (done) return;
-  if (early) {
-    if (threadIdx.x == 0) {
-      S.iter += 1;
-      S.rr = S.ss;
-      S.done = 1;
-      S.early = 0;
-    }
-    return;
-  }
-  if (threadIdx.x == 0) {
-    const double re = o[0], im = o[1], rr = o[2];
-    S.iter += 1;
-    S.rho_old = S.rho;
-    S.rho = z_t{re, im};
-    S.rr = rr;
-    if (!isfinite(rr) || !isfinite(re) || !isfinite(im)) {
-      S.nan = 1;
-      S.done = 1;
-    } else if (rr <= S.thr2) {
-      S.done = 1;
-    } else if (sqrt(norm2(S.rho)) < 1e-300 * sqrt(S.rhat2 * rr) || norm2(S.omega) == 0.0) {
-      // breakdown: restart the shadow residual from the current residual
-      S.reset = 1;
-      S.rho = z_t{rr, 0.0};
-      S.rho_old = S.alpha = S.omega = z_t{1.0, 0.0};
-      S.rhat2 = rr;
-    }
-    S.beta = cdiv(S.rho, S.rho_old) * cdiv(S.alpha, S.omega);
-  }
 }
 
 __global__ void k_set_thr(int nseg, BiSt* st, const double* fn2, double tol, int reset_iter) {
@@ -247,16 +258,15 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
     if (rc) return rc;
     *vecs[i] = b->as<cx<T>>();
   }
-  DevBuf* stb = ctx->buf(p + "st", sizeof(BiSt) * S.nseg, &rc);
-  if (rc) return rc;
-  DevBuf* part = ctx->buf(p + "part", sizeof(double) * 4 * S.nblk, &rc);
+  // state slots: after rho (start of an iteration), alpha, omega
+  DevBuf* stb = ctx->buf(p + "st", sizeof(BiSt) * 3 * S.nseg, &rc);
   if (rc) return rc;
   DevBuf* fnb = ctx->buf(p + "fn2", sizeof(double) * S.nseg, &rc);
   if (rc) return rc;
-  BiSt* st = stb->as<BiSt>();
-  double* pt = part->as<double>();
+  BiSt *st = stb->as<BiSt>(), *st_a = st + S.nseg, *st_b = st_a + S.nseg;   // st: what an iteration starts from
   hipStream_t s = ctx->stream;
   const Seg& L = S.dev;
+  const Seg& P = prod_seg(A, L);   // the products' layout
 
   // ||f||^2 per segment -> thresholds
   std::vector<double> fn2;
@@ -264,75 +274,89 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
   out->fnorm.resize(S.nseg);
   for (int i = 0; i < S.nseg; ++i) out->fnorm[i] = std::sqrt(fn2[i]);
   HZ_HIP(hipMemcpyAsync(fnb->p, fn2.data(), sizeof(double) * S.nseg, hipMemcpyHostToDevice, s));
-  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(BiSt) * S.nseg, s));
+  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(BiSt) * 3 * S.nseg, s));
   k_set_thr<<<ceil_div(S.nseg, kBlock), kBlock, 0, s>>>(S.nseg, st, fnb->as<double>(), ctl.tol, 1);
   HZ_HIP(hipGetLastError());
 
-  void* hp = nullptr;
-  HZ_TRY(ctx_pinned(ctx, sizeof(BiSt) * S.nseg, &hp));
-  BiSt* hst = static_cast<BiSt*>(hp);
-  const int grid = S.nblk;
-  std::vector<int> restarts(S.nseg, 0);
+  StatePoll poll;
+  HZ_TRY(poll.init(ctx, sizeof(BiSt) * S.nseg));
+  const Seg& W = A.tz.on ? S.vec_runs : S.vec;   // vector layout
+  PartBuf pr, pa, po, pn;            // sums of the residual, alpha, omega and rho steps
+  HZ_TRY(pr.init(ctx, S, P, 1, W.nblk, p + "part.r"));
+  HZ_TRY(pa.init(ctx, S, P, 2, W.nblk, p + "part.a"));
+  HZ_TRY(po.init(ctx, S, P, 4, W.nblk, p + "part.o"));
+  HZ_TRY(pn.init(ctx, S, W, 3, W.nblk, p + "part.n"));
   int64_t resid_calls = 0;
-  int chunk = 4;
 
-  auto read_state = [&]() -> int {
-    HZ_HIP(hipMemcpyAsync(hst, st, sizeof(BiSt) * S.nseg, hipMemcpyDeviceToHost, s));
-    HZ_HIP(hipStreamSynchronize(s));
-    return HZ_OK;
+  auto report = [&]() -> int {
+    k_bi_report<<<S.nseg, kBlock, 0, s>>>(pn.part, st, poll.slot<BiSt>());
+    HZ_HIP(hipGetLastError());
+    return poll.posted_one();
   };
   auto enqueue_resid = [&]() -> int {
-    if (A.val) k_resid<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, V, pt);
-    else if (A.st) k_resid<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, V, pt);
-    else k_resid<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, V, pt);
-    k_resid_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
+    k_bi_settle<<<S.nseg, kBlock, 0, s>>>(pn.part, st);
+    HZ_BY_FORM(A, k_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, V, pr.raw));
+    HZ_TRY(pr.close<1>(s));
+    k_bi_resid<<<S.nseg, kBlock, 0, s>>>(pr.part, st);
     HZ_HIP(hipGetLastError());
     ++resid_calls;
-    return HZ_OK;
+    return report();
   };
   auto enqueue_iter = [&]() -> int {
-    k_p<T><<<grid, kBlock, 0, s>>>(L, st, V);
-    if (A.val) k_v<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else if (A.st) k_v<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else k_v<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    k_alpha_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
-    k_s<T><<<grid, kBlock, 0, s>>>(L, st, V);
-    if (A.val) k_t<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else if (A.st) k_t<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else k_t<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    k_omega_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
-    k_xr<T><<<grid, kBlock, 0, s>>>(L, st, V, pt);
-    k_rho_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
+    HZ_BY_SCALING(A, k_p<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pn.part, st, st_a, V));
+    HZ_BY_FORM(A, k_v<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st_a, V, pa.raw));
+    HZ_TRY(pa.close<2>(s));
+    HZ_BY_SCALING(A, k_s<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st_a, st_b, V));
+    HZ_BY_FORM(A, k_t<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st_b, V, po.raw));
+    HZ_TRY(po.close<4>(s));
+    HZ_BY_SCALING(A, k_xr<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, st_b, st, V, pn.raw));
+    HZ_TRY(pn.close<3>(s));
     HZ_HIP(hipGetLastError());
     return HZ_OK;
   };
 
   HZ_TRY(enqueue_resid());
-  HZ_TRY(read_state());
+  HZ_TRY(poll.wait(0));
+  const BiSt* hst = poll.state<BiSt>(0);
+  int chunk = 2;
   for (;;) {
+    // everything queued has run: hst is the state
     bool all_done = true;
     int max_iter = 0;
     for (int i = 0; i < S.nseg; ++i) {
       all_done = all_done && hst[i].done;
       max_iter = std::max(max_iter, hst[i].iter);
     }
-    int64_t mv = 2 * int64_t(max_iter) + resid_calls;
+    const int64_t mv = 2 * int64_t(max_iter) + resid_calls;
     if (all_done) {
       // the recursive residuals say converged: confirm with the true residual
       // (a fresh residual also restarts any segment that drifted)
       HZ_TRY(enqueue_resid());
-      HZ_TRY(read_state());
+      HZ_TRY(poll.wait(poll.posted - 1));
+      hst = poll.state<BiSt>(poll.posted - 1);
       bool ok = true;
       for (int i = 0; i < S.nseg; ++i) ok = ok && hst[i].done;
       if (ok || mv + 1 >= ctl.max_matvec) break;
       continue;
     }
-    if (mv + 2 > ctl.max_matvec) break;
-    int n_it = int(std::min<int64_t>(chunk, (ctl.max_matvec - mv) / 2));
-    if (n_it < 1) break;
-    for (int it = 0; it < n_it; ++it) HZ_TRY(enqueue_iter());
-    HZ_TRY(read_state());
-    chunk = std::min(chunk * 2, 64);
+    int64_t left = (ctl.max_matvec - mv) / 2;   // iterations that may still be queued
+    if (left < 1) break;
+    const int first = poll.posted;
+    for (bool stop = false; !stop && left > 0;) {
+      const int n_it = int(std::min<int64_t>(chunk, left));
+      for (int it = 0; it < n_it; ++it) HZ_TRY(enqueue_iter());
+      left -= n_it;
+      HZ_TRY(report());
+      if (poll.posted - 1 > first) {
+        HZ_TRY(poll.wait(poll.posted - 2));
+        const BiSt* h = poll.state<BiSt>(poll.posted - 2);
+        stop = true;
+        for (int i = 0; i < S.nseg; ++i) stop = stop && h[i].done;
+      }
+      chunk = std::min(chunk * 2, 8);
+    }
+    HZ_TRY(poll.wait(poll.posted - 1));
+    hst = poll.state<BiSt>(poll.posted - 1);
   }
   out->iters.resize(S.nseg);
   out->matvecs.resize(S.nseg);

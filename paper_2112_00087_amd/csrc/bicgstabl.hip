@@ -16,8 +16,15 @@
 // leading well-conditioned directions and the segment restarts from its
 // true residual after the cycle.
 //
-// Per cycle: 6 l + 3 launches, 2 l products.  Krylov scalars stay on the
-// device; the host polls the per-segment state every few cycles.
+// Per cycle: 4 l + 3 launches, 2 l products.  The scalar steps run at the
+// start of the kernel that needs them (advance), on a state that moves
+// through three slots.  Krylov scalars stay on the device; the host polls the
+// per-segment state every few cycles, one chunk behind.
+//
+// In the tensor form the products take D^-1-scaled inputs: the kernels that
+// make u_j and r_j also write the scaled copy that their product reads, and x
+// is the solution: the corrections, which are sums of unscaled vectors,
+// collect in e and enter x as D^-1 e at a restart and at the end.
 #include <chrono>
 
 #include "ops.h"
@@ -31,12 +38,15 @@ struct BlSt {
   z_t gam[kMaxL + 1];   // gamma_1..gamma_l
   double rr, thr2, rhat2;
   int iter, done, brk, nan, restart, trunc;
+  int pend, pad;        // pend: the sums of the cycle's end are formed
 };
 
 template <typename T>
 struct BlV {
   const cx<T>* f;
-  cx<T>* x;                 // iterate of B x = f
+  cx<T>* x;                 // iterate
+  cx<T>* e;                 // where its corrections go: x itself, or e (tensor form)
+  cx<T>* in;                // tensor form: D^-1 times the next product's vector
   cx<T>* rt;                // shadow residual
   cx<T>* r[kMaxL + 1];
   cx<T>* u[kMaxL + 1];
@@ -53,288 +63,110 @@ __device__ __forceinline__ void acc_dot(double* q, z_t a, z_t b) {
   q[1] = fma(a.re, b.im, fma(-a.im, b.re, q[1]));
 }
 
-// Per-segment totals of NQ partials into shared memory (thread q sums
-// quantity q, block order fixed); valid in every thread after the call.
-template <int NQ>
-__device__ __forceinline__ void seg_totals(const Seg& L, const double* part, int seg, double* tot /*[NQ]*/) {
-  __shared__ double lds[NQ][kFinBlock / kWave];
-  const int b0 = L.seg_blk[seg], b1 = L.seg_blk[seg + 1];
-  double acc[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
-  for (int i = b0 + int(threadIdx.x); i < b1; i += int(blockDim.x)) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q] += part[int64_t(i) * NQ + q];
-  }
-  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave, nw = blockDim.x / kWave;
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    double s = wave_sum(acc[q]);
-    if (lane == 0) lds[q][w] = s;
-  }
-  __syncthreads();
-  for (int q = int(threadIdx.x); q < NQ; q += int(blockDim.x)) {
-    double s = 0.0;
-    for (int i = 0; i < nw; ++i) s += lds[q][i];
-    tot[q] = s;
-  }
-  __syncthreads();
+// ---------------------------------------------------------------- scalar steps
+// Run by one thread once a segment's sums are complete.
+__device__ __forceinline__ void bl_resid(BlSt& S, const double* tot) {
+  const double rr = tot[0];
+  S.rr = rr;
+  S.rhat2 = rr;
+  S.rho0 = z_t{rr, 0.0};     // first step: beta = 0, rho0 = rt^H r_0
+  S.alpha = S.beta = z_t{0.0, 0.0};
+  S.omega = z_t{1.0, 0.0};
+  S.nan = !isfinite(rr);
+  S.done = (rr <= S.thr2) || S.nan;
+  S.brk = 0;
+  S.trunc = 0;
+  S.restart = 0;
+  S.pend = 0;
 }
-
-// ---------------------------------------------------------------- restart
-// Segments flagged for a restart: all of them (all = 1: start, or the check
-// of a converged recursion) or those that broke down.
-__global__ void k_bl_mark(int nseg, BlSt* st, int all) {
-  int s = blockIdx.x * kBlock + threadIdx.x;
-  if (s >= nseg) return;
-  st[s].restart = all ? 1 : st[s].brk;
-}
-
-// r_0 = f - B x, rt = r_0, u_0 = 0; partial ||r_0||^2.
-template <typename T, int F>
-__global__ void __launch_bounds__(kBlock) k_bl_resid(Seg L, SellOp<T> A, const BlSt* st, BlV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
-  if (!st[t.seg].restart) return;
-  z_t r = zd(V.f[t.row]) - zd(sell_row_form<F>(A, t.row, V.x));
-  cx<T> rs = zt<T>(r);
-  V.r[0][t.row] = rs;
-  V.rt[t.row] = rs;
-  V.u[0][t.row] = cx<T>{T(0), T(0)};
-  double q[1] = {norm2(zd(rs))};
-  store_partials<1>(q, part, t);
-}
-
-__global__ void k_bl_resid_fin(Seg L, BlSt* st, const double* part) {
-  __shared__ double tot[1];
-  const int s = blockIdx.x;
-  const int go = st[s].restart;
-  __syncthreads();
-  if (!go) return;
-  seg_totals<1>(L, part, s, tot);
-  if (threadIdx.x == 0) {
-    BlSt& S = st[s];
-    const double rr = tot[0];
-    S.rr = rr;
-    S.rhat2 = rr;
-    S.rho0 = z_t{rr, 0.0};     // first step: beta = 0, rho0 = rt^H r_0
-    S.alpha = S.beta = z_t{0.0, 0.0};
-    S.omega = z_t{1.0, 0.0};
-    S.nan = !isfinite(rr);
-    S.done = (rr <= S.thr2) || S.nan;
-    S.brk = 0;
-    S.trunc = 0;
-    S.restart = 0;
-  }
-}
-
-// ---------------------------------------------------------------- bi-conjugate gradient step j
-// u_i = r_i - beta u_i, i = 0..j
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_bl_u(Seg L, const BlSt* st, BlV<T> V, int j) {
-  Tile t = tile_of(L);
-  const BlSt& S = st[t.seg];
-  if (bl_off(S)) return;
-  const z_t b = S.beta;
-  for (int i = 0; i <= j; ++i) V.u[i][t.row] = zt<T>(zd(V.r[i][t.row]) - b * zd(V.u[i][t.row]));
-}
-
-// y_{j+1} = B y_j for the chain y (u or r); partial rt^H y_{j+1}.
-template <typename T, int F>
-__global__ void HZ_PRODUCT_BOUNDS k_bl_prod(Seg L, SellOp<T> A, const BlSt* st, const cx<T>* __restrict__ yj,
-                                                    cx<T>* __restrict__ yj1, const cx<T>* __restrict__ rt,
-                                                    double* part) {
-  SumTile t = tile_of_sums(L);
-  if (bl_off(st[t.seg])) return;
-  cx<T> y = sell_row_form<F>(A, t.row, yj);
-  yj1[t.row] = y;
-  double q[2] = {0.0, 0.0};
-  acc_dot(q, zd(rt[t.row]), zd(y));
-  store_partials<2>(q, part, t);
-}
-
 // alpha = rho0 / rt^H u_{j+1}
-__global__ void k_bl_alpha_fin(Seg L, BlSt* st, const double* part) {
-  __shared__ double tot[2];
-  const int s = blockIdx.x;
-  const int off = bl_off(st[s]);
-  __syncthreads();
-  if (off) return;
-  seg_totals<2>(L, part, s, tot);
-  if (threadIdx.x == 0) {
-    BlSt& S = st[s];
-    const z_t sg = {tot[0], tot[1]};
-    if (norm2(sg) == 0.0 || !isfinite(sg.re) || !isfinite(sg.im)) S.brk = 1;
-    else S.alpha = cdiv(S.rho0, sg);
-  }
+__device__ __forceinline__ void bl_alpha(BlSt& S, const double* tot) {
+  const z_t sg = {tot[0], tot[1]};
+  if (norm2(sg) == 0.0 || !isfinite(sg.re) || !isfinite(sg.im)) S.brk = 1;
+  else S.alpha = cdiv(S.rho0, sg);
 }
-
-// r_i -= alpha u_{i+1}, i = 0..j; x += alpha u_0
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_bl_r(Seg L, const BlSt* st, BlV<T> V, int j) {
-  Tile t = tile_of(L);
-  const BlSt& S = st[t.seg];
-  if (bl_off(S)) return;
-  const z_t a = S.alpha;
-  for (int i = 0; i <= j; ++i) V.r[i][t.row] = zt<T>(zd(V.r[i][t.row]) - a * zd(V.u[i + 1][t.row]));
-  V.x[t.row] = zt<T>(zd(V.x[t.row]) + a * zd(V.u[0][t.row]));
-}
-
 // rho1 = rt^H r_{j+1}; beta = alpha rho1 / rho0; rho0 = rho1
-__global__ void k_bl_beta_fin(Seg L, BlSt* st, const double* part) {
-  __shared__ double tot[2];
-  const int s = blockIdx.x;
-  const int off = bl_off(st[s]);
-  __syncthreads();
-  if (off) return;
-  seg_totals<2>(L, part, s, tot);
-  if (threadIdx.x == 0) {
-    BlSt& S = st[s];
-    const z_t rho1 = {tot[0], tot[1]};
-    if (norm2(S.rho0) == 0.0 || !isfinite(rho1.re) || !isfinite(rho1.im)) {
-      S.brk = 1;
-    } else {
-      S.beta = S.alpha * cdiv(rho1, S.rho0);
-      S.rho0 = rho1;
-    }
-  }
-}
-
-// ---------------------------------------------------------------- minimal-residual step
-// Partials of c_i = r_i^H r_0 (i = 1..LL) and G_ij = r_i^H r_j (1 <= i <= j <= LL).
-template <int LL> constexpr int gram_nq() { return 2 * (LL + LL * (LL + 1) / 2); }
-
-template <typename T, int LL>
-__global__ void __launch_bounds__(kBlock) k_bl_gram(Seg L, const BlSt* st, BlV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
-  if (bl_off(st[t.seg])) return;
-  constexpr int NQ = gram_nq<LL>();
-  z_t r[LL + 1];
-#pragma unroll
-  for (int i = 0; i <= LL; ++i) r[i] = zd(V.r[i][t.row]);
-  double q[NQ];
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) q[i] = 0.0;
-  int k = 0;
-#pragma unroll
-  for (int i = 1; i <= LL; ++i) {
-    acc_dot(q + k, r[i], r[0]);
-    k += 2;
-  }
-#pragma unroll
-  for (int i = 1; i <= LL; ++i) {
-#pragma unroll
-    for (int jj = i; jj <= LL; ++jj) {
-      acc_dot(q + k, r[i], r[jj]);
-      k += 2;
-    }
-  }
-  store_partials<NQ>(q, part, t);
-}
-
-// Cholesky solve of G gamma = c (G Hermitian, LL x LL), truncated at the
-// first pivot below piv times its diagonal entry (G is exact for the stored
-// vectors, so piv guards the FP64 Cholesky only).
-template <int LL>
-__global__ void k_bl_mr_fin(Seg L, BlSt* st, const double* part, double piv) {
-  constexpr int NQ = gram_nq<LL>();
-  __shared__ double tot[NQ];
-  const int s = blockIdx.x;
-  const int off = bl_off(st[s]);
-  __syncthreads();
-  if (off) return;
-  seg_totals<NQ>(L, part, s, tot);
-  if (threadIdx.x != 0) return;
-  BlSt& S = st[s];
-  z_t c[LL], G[LL][LL];
-  int k = 0;
-  for (int i = 0; i < LL; ++i, k += 2) c[i] = z_t{tot[k], tot[k + 1]};
-  for (int i = 0; i < LL; ++i)
-    for (int jj = i; jj < LL; ++jj, k += 2) {
-      G[i][jj] = z_t{tot[k], tot[k + 1]};
-      G[jj][i] = conj(G[i][jj]);
-    }
-  // G = C C^H, C lower triangular (stored in G's lower part, diagonal real)
-  int m = LL;
-  for (int jj = 0; jj < LL && m == LL; ++jj) {
-    double d = G[jj][jj].re;
-    for (int p = 0; p < jj; ++p) d -= norm2(G[jj][p]);
-    if (!(d > piv * G[jj][jj].re) || !isfinite(d)) {
-      m = jj;
-      break;
-    }
-    const double cd = sqrt(d);
-    G[jj][jj] = z_t{cd, 0.0};
-    for (int i = jj + 1; i < LL; ++i) {
-      z_t v = G[i][jj];
-      for (int p = 0; p < jj; ++p) v = v - G[i][p] * conj(G[jj][p]);
-      G[i][jj] = (1.0 / cd) * v;
-    }
-  }
-  z_t g[LL];
-  for (int i = 0; i < LL; ++i) g[i] = z_t{0.0, 0.0};
-  if (m == 0) {
+__device__ __forceinline__ void bl_beta(BlSt& S, const double* tot) {
+  const z_t rho1 = {tot[0], tot[1]};
+  if (norm2(S.rho0) == 0.0 || !isfinite(rho1.re) || !isfinite(rho1.im)) {
     S.brk = 1;
   } else {
-    z_t y[LL];
-    for (int i = 0; i < m; ++i) {        // C y = c
-      z_t v = c[i];
-      for (int p = 0; p < i; ++p) v = v - G[i][p] * y[p];
-      y[i] = (1.0 / G[i][i].re) * v;
-    }
-    for (int i = m - 1; i >= 0; --i) {   // C^H g = y
-      z_t v = y[i];
-      for (int p = i + 1; p < m; ++p) v = v - conj(G[p][i]) * g[p];
-      g[i] = (1.0 / G[i][i].re) * v;
+    S.beta = S.alpha * cdiv(rho1, S.rho0);
+    S.rho0 = rho1;
+  }
+}
+// conj(a) b, each part with one rounding of its second product
+__device__ __forceinline__ z_t conj_mul(z_t a, z_t b) {
+  return {fma(a.re, b.re, a.im * b.im), fma(a.re, b.im, -(a.im * b.re))};
+}
+// Cholesky solve of G gamma = c (G Hermitian, LL x LL), truncated at the
+// first pivot below piv times its diagonal entry (G is exact for the stored
+// vectors, so piv guards the FP64 Cholesky only).  Every loop is unrolled,
+// so the matrix sits in registers (as a scratch array this step took 23 us
+// at LL = 4, five times the kernel around it).
+template <int LL>
+__device__ __forceinline__ void bl_mr(BlSt& S, const double* tot, double piv) {
+  z_t c[LL], G[LL][LL];      // G: lower triangle
+  int k = 0;
+#pragma unroll
+  for (int i = 0; i < LL; ++i, k += 2) c[i] = z_t{tot[k], tot[k + 1]};
+#pragma unroll
+  for (int i = 0; i < LL; ++i)
+#pragma unroll
+    for (int jj = i; jj < LL; ++jj, k += 2) G[jj][i] = z_t{tot[k], -tot[k + 1]};
+  // G = C C^H, C lower triangular (diagonal real)
+  int m = LL;
+#pragma unroll
+  for (int jj = 0; jj < LL; ++jj) {
+    double d = G[jj][jj].re;
+#pragma unroll
+    for (int p = 0; p < jj; ++p) d -= fma(G[jj][p].re, G[jj][p].re, G[jj][p].im * G[jj][p].im);
+    if (m == LL && (!(d > piv * G[jj][jj].re) || !isfinite(d))) m = jj;
+    const double cd = m == LL ? sqrt(d) : 1.0, ci = 1.0 / cd;
+    G[jj][jj] = z_t{cd, 0.0};
+#pragma unroll
+    for (int i = jj + 1; i < LL; ++i) {
+      z_t v = G[i][jj];
+#pragma unroll
+      for (int p = 0; p < jj; ++p) v = v - conj_mul(G[jj][p], G[i][p]);
+      G[i][jj] = ci * v;
     }
   }
-  for (int i = 0; i < LL; ++i)
-    if (!isfinite(g[i].re) || !isfinite(g[i].im)) {
-      S.brk = 1;
-      return;
+  z_t g[LL], y[LL];
+  if (m == 0) S.brk = 1;
+#pragma unroll
+  for (int i = 0; i < LL; ++i) {           // C y = c
+    z_t v = c[i];
+#pragma unroll
+    for (int p = 0; p < i; ++p) {
+      const z_t a = G[i][p];
+      v = v - z_t{fma(a.re, y[p].re, -(a.im * y[p].im)), fma(a.im, y[p].re, a.re * y[p].im)};
     }
+    y[i] = i < m ? (1.0 / G[i][i].re) * v : z_t{0.0, 0.0};
+  }
+#pragma unroll
+  for (int i = LL - 1; i >= 0; --i) {      // C^H g = y
+    z_t v = y[i];
+#pragma unroll
+    for (int p = i + 1; p < LL; ++p)
+      if (p < m) v = v - conj_mul(G[p][i], g[p]);
+    g[i] = i < m ? (1.0 / G[i][i].re) * v : z_t{0.0, 0.0};
+  }
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < LL; ++i) bad = bad || !isfinite(g[i].re) || !isfinite(g[i].im);
+  if (bad) {
+    S.brk = 1;
+    return;
+  }
+#pragma unroll
   for (int i = 0; i < LL; ++i) S.gam[i + 1] = g[i];
   S.omega = g[LL - 1];
   S.trunc = (m < LL) ? 1 : 0;
+  S.pend = !S.brk;           // k_bl_update forms the sums of the cycle's end
 }
-
-// x += sum gamma_j r_{j-1}; r_0 -= sum gamma_j r_j; u_0 -= sum gamma_j u_j;
-// partials rt^H r_0, ||r_0||^2
-template <typename T, int LL>
-__global__ void __launch_bounds__(kBlock) k_bl_update(Seg L, const BlSt* st, BlV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
-  const BlSt& S = st[t.seg];
-  if (bl_off(S)) return;
-  z_t x = zd(V.x[t.row]), r0 = zd(V.r[0][t.row]), u0 = zd(V.u[0][t.row]);
-  z_t rprev = r0;
-#pragma unroll
-  for (int jj = 1; jj <= LL; ++jj) {
-    const z_t g = S.gam[jj];
-    const z_t rj = zd(V.r[jj][t.row]);
-    x = x + g * rprev;
-    r0 = r0 - g * rj;
-    u0 = u0 - g * zd(V.u[jj][t.row]);
-    rprev = rj;
-  }
-  cx<T> rs = zt<T>(r0);
-  V.x[t.row] = zt<T>(x);
-  V.r[0][t.row] = rs;
-  V.u[0][t.row] = zt<T>(u0);
-  double q[3] = {0.0, 0.0, 0.0};
-  const z_t rv = zd(rs);
-  acc_dot(q, zd(V.rt[t.row]), rv);
-  q[2] = norm2(rv);
-  store_partials<3>(q, part, t);
-}
-
-__global__ void k_bl_cycle_fin(Seg L, BlSt* st, const double* part) {
-  __shared__ double tot[3];
-  const int s = blockIdx.x;
-  const int off = bl_off(st[s]);
-  __syncthreads();
-  if (off) return;
-  seg_totals<3>(L, part, s, tot);
-  if (threadIdx.x != 0) return;
-  BlSt& S = st[s];
+__device__ __forceinline__ void bl_cycle(BlSt& S, const double* tot) {
+  S.pend = 0;
   const z_t rho1 = {tot[0], tot[1]};
   const double rr = tot[2];
   S.iter += 1;
@@ -357,6 +189,179 @@ __global__ void k_bl_cycle_fin(Seg L, BlSt* st, const double* part) {
   S.rho0 = rho1;
 }
 
+__device__ __forceinline__ bool bl_on(const BlSt& S) { return !bl_off(S); }
+__device__ __forceinline__ bool bl_pending(const BlSt& S) { return S.pend; }
+
+// The state after the sums formed last: in place after k_bl_resid, for the
+// host at the end of a cycle.
+__global__ void __launch_bounds__(kBlock) k_bl_resid_fin(Part P, BlSt* st) {
+  advance_alone<1>(P, st, st, [](const BlSt& S) { return S.restart != 0; }, bl_resid);
+}
+__global__ void __launch_bounds__(kBlock) k_bl_report(Part P, const BlSt* in, BlSt* out) {
+  advance_alone<3>(P, in, out, bl_pending, bl_cycle);
+}
+// At a restart the slot a cycle starts from takes up the pending sums.
+__global__ void __launch_bounds__(kBlock) k_bl_settle(Part P, BlSt* st, int all) {
+  advance_alone<3>(P, st, st, bl_pending, bl_cycle);
+  if (threadIdx.x == 0) st[blockIdx.x].restart = all ? 1 : st[blockIdx.x].brk;
+}
+
+// ---------------------------------------------------------------- restart
+// x += D^-1 e, e = 0 (tensor form): the segments that restart, or all.
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_bl_fold(Seg L, TzOp Z, const BlSt* st, BlV<T> V, int all) {
+  const Tile t = vec_tile(L);
+  if (!all && !st[t.seg].restart) return;
+  const TzSeg B = tz_seg(Z, t.seg);
+  vec_rows(L, t, [&](int64_t row) {
+    V.x[row] = zt<T>(zd(V.x[row]) + tz_pre<kFormTensor>(Z, B, row, zd(V.e[row])));
+    V.e[row] = cx<T>{T(0), T(0)};
+  });
+}
+
+// r_0 = f - B x, rt = r_0, u_0 = 0; partial ||r_0||^2.
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_bl_resid(Seg L, SellOp<T> A, const BlSt* st, BlV<T> V, double* part) {
+  SumTile t = prod_tile_sums<F>(L);
+  if (!st[t.seg].restart) return;
+  double q[1] = {0.0};
+  for_rows<F, true>(A, t, V.x, [=](int64_t row) { return V.f[row]; },
+              [&](int64_t row, cx<T> y, cx<T> f) {
+                const cx<T> rs = zt<T>(zd(f) - zd(y));
+                V.r[0][row] = rs;
+                V.rt[row] = rs;
+                V.u[0][row] = cx<T>{T(0), T(0)};
+                q[0] += norm2(zd(rs));
+              });
+  store_partials<1>(q, part, t);
+}
+
+// ---------------------------------------------------------------- bi-conjugate gradient step j
+// beta (at j = 0 of the cycle before); u_i = r_i - beta u_i, i = 0..j
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_bl_u(Seg L, TzOp Z, Part P, Part Pc, const BlSt* in, BlSt* out, BlV<T> V,
+                                                 int j) {
+  const Tile t = vec_tile(L);
+  const BlSt& S = j == 0 ? advance<3>(Pc, in, out, t, first_block(L, t), bl_pending, bl_cycle)
+                         : advance<2>(P, in, out, t, first_block(L, t), bl_on, bl_beta);
+  if (bl_off(S)) return;
+  const TzSeg B = form_seg<F>(Z, t);
+  const z_t b = S.beta;
+  vec_rows(L, t, [&](int64_t row) {
+    cx<T> u = {};
+    for (int i = 0; i <= j; ++i) V.u[i][row] = u = zt<T>(zd(V.r[i][row]) - b * zd(V.u[i][row]));
+    if (F == kFormTensor) V.in[row] = zt<T>(tz_pre<F>(Z, B, row, zd(u)));
+  });
+}
+
+// y_{j+1} = B y_j for the chain y (u or r), from yj = y_j (scaled in the
+// tensor form); partial rt^H y_{j+1} (SUMS).
+template <typename T, int F, bool SUMS>
+__global__ void HZ_PRODUCT_BOUNDS k_bl_prod(Seg L, SellOp<T> A, const BlSt* st, const cx<T>* __restrict__ yj,
+                                            cx<T>* __restrict__ yj1, const cx<T>* __restrict__ rt, double* part) {
+  SumTile t = prod_tile_sums<F>(L);
+  if (bl_off(st[t.seg])) return;
+  if constexpr (!SUMS) {
+    for_rows<F>(A, t, yj, [](int64_t) { return 0; }, [=](int64_t row, cx<T> y, int) { yj1[row] = y; });
+  } else {
+    double q[2] = {0.0, 0.0};
+    for_rows<F>(A, t, yj, [=](int64_t row) { return rt[row]; },
+                [&](int64_t row, cx<T> y, cx<T> r) {
+                  yj1[row] = y;
+                  acc_dot(q, zd(r), zd(y));
+                });
+    store_partials<2>(q, part, t);
+  }
+}
+
+// alpha; r_i -= alpha u_{i+1}, i = 0..j; x += alpha u_0
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_bl_r(Seg L, TzOp Z, Part P, const BlSt* in, BlSt* out, BlV<T> V, int j) {
+  const Tile t = vec_tile(L);
+  const BlSt& S = advance<2>(P, in, out, t, first_block(L, t), bl_on, bl_alpha);
+  if (bl_off(S)) return;
+  const TzSeg B = form_seg<F>(Z, t);
+  const z_t a = S.alpha;
+  vec_rows(L, t, [&](int64_t row) {
+    cx<T> r = {};
+    for (int i = 0; i <= j; ++i) V.r[i][row] = r = zt<T>(zd(V.r[i][row]) - a * zd(V.u[i + 1][row]));
+    V.e[row] = zt<T>(zd(V.e[row]) + a * zd(V.u[0][row]));
+    if (F == kFormTensor) V.in[row] = zt<T>(tz_pre<F>(Z, B, row, zd(r)));
+  });
+}
+
+// ---------------------------------------------------------------- minimal-residual step
+// Partials of c_i = r_i^H r_0 (i = 1..LL) and G_ij = r_i^H r_j (1 <= i <= j <= LL).
+template <int LL> constexpr int gram_nq() { return 2 * (LL + LL * (LL + 1) / 2); }
+
+template <typename T, int LL>
+__global__ void __launch_bounds__(kBlock) k_bl_gram(Seg L, const BlSt* st, BlV<T> V, double* part) {
+  const SumTile t = vec_tile_sums(L);
+  if (bl_off(st[t.seg])) return;
+  constexpr int NQ = gram_nq<LL>();
+  double q[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) q[i] = 0.0;
+  vec_rows(L, t, [&](int64_t row) {
+    z_t r[LL + 1];
+#pragma unroll
+    for (int i = 0; i <= LL; ++i) r[i] = zd(V.r[i][row]);
+    int k = 0;
+#pragma unroll
+    for (int i = 1; i <= LL; ++i) {
+      acc_dot(q + k, r[i], r[0]);
+      k += 2;
+    }
+#pragma unroll
+    for (int i = 1; i <= LL; ++i) {
+#pragma unroll
+      for (int jj = i; jj <= LL; ++jj) {
+        acc_dot(q + k, r[i], r[jj]);
+        k += 2;
+      }
+    }
+  });
+  store_partials<NQ>(q, part, t);
+}
+
+// gamma by one block per segment: its 2 LL + LL (LL + 1) sums are too many to
+// add in every block, and its registers would limit k_bl_update.
+template <int LL>
+__global__ void __launch_bounds__(kBlock) k_bl_mr(Part P, const BlSt* in, BlSt* out, double piv) {
+  advance_alone<gram_nq<LL>()>(P, in, out, bl_on, [=](BlSt& S, const double* o) { bl_mr<LL>(S, o, piv); });
+}
+
+// x += sum gamma_j r_{j-1}; r_0 -= sum gamma_j r_j; u_0 -= sum gamma_j u_j;
+// partials rt^H r_0, ||r_0||^2
+template <typename T, int LL>
+__global__ void __launch_bounds__(kBlock) k_bl_update(Seg L, const BlSt* st, BlV<T> V, double* part) {
+  const SumTile t = vec_tile_sums(L);
+  const BlSt& S = st[t.seg];
+  if (bl_off(S)) return;
+  double q[3] = {0.0, 0.0, 0.0};
+  vec_rows(L, t, [&](int64_t row) {
+    z_t x = zd(V.e[row]), r0 = zd(V.r[0][row]), u0 = zd(V.u[0][row]);
+    z_t rprev = r0;
+#pragma unroll
+    for (int jj = 1; jj <= LL; ++jj) {
+      const z_t g = S.gam[jj];
+      const z_t rj = zd(V.r[jj][row]);
+      x = x + g * rprev;
+      r0 = r0 - g * rj;
+      u0 = u0 - g * zd(V.u[jj][row]);
+      rprev = rj;
+    }
+    cx<T> rs = zt<T>(r0);
+    V.e[row] = zt<T>(x);
+    V.r[0][row] = rs;
+    V.u[0][row] = zt<T>(u0);
+    const z_t rv = zd(rs);
+    acc_dot(q, zd(V.rt[row]), rv);
+    q[2] += norm2(rv);
+  });
+  store_partials<3>(q, part, t);
+}
+
 __global__ void k_bl_set_thr(int nseg, BlSt* st, const double* fn2, double tol) {
   int s = blockIdx.x * kBlock + threadIdx.x;
   if (s >= nseg) return;
@@ -365,10 +370,12 @@ __global__ void k_bl_set_thr(int nseg, BlSt* st, const double* fn2, double tol) 
 }
 
 template <typename T, int LL>
-int enqueue_mr(hipStream_t q, const SegHost& S, BlSt* st, const BlV<T>& V, double* pt) {
-  k_bl_gram<T, LL><<<S.nblk, kBlock, 0, q>>>(S.dev, st, V, pt);
-  k_bl_mr_fin<LL><<<S.nseg, kFinBlock, 0, q>>>(S.dev, st, pt, 1e-13);
-  k_bl_update<T, LL><<<S.nblk, kBlock, 0, q>>>(S.dev, st, V, pt);
+int enqueue_mr(hipStream_t q, const Seg& W, const BlSt* in, BlSt* out, const BlV<T>& V, const PartBuf& pg,
+               const PartBuf& pc) {
+  k_bl_gram<T, LL><<<W.nblk, kBlock, 0, q>>>(W, in, V, pg.raw);
+  k_bl_mr<LL><<<W.nseg, kBlock, 0, q>>>(pg.part, in, out, 1e-13);
+  k_bl_update<T, LL><<<W.nblk, kBlock, 0, q>>>(W, out, V, pc.raw);
+  HZ_TRY(pc.close<3>(q));
   HZ_HIP(hipGetLastError());
   return HZ_OK;
 }
@@ -396,80 +403,89 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     V.r[i] = vec("r" + std::to_string(i));
     V.u[i] = vec("u" + std::to_string(i));
   }
+  V.e = A.tz.on ? vec("e") : x;
+  V.in = A.tz.on ? vec("in") : nullptr;
   if (rc) return rc;
-  DevBuf* stb = ctx->buf(p + "st", sizeof(BlSt) * S.nseg, &rc);
-  if (rc) return rc;
-  DevBuf* part = ctx->buf(p + "part", sizeof(double) * 88 * S.nblk, &rc);
+  // state slots: start of a cycle, after beta, after alpha
+  DevBuf* stb = ctx->buf(p + "st", sizeof(BlSt) * 3 * S.nseg, &rc);
   if (rc) return rc;
   DevBuf* fnb = ctx->buf(p + "fn2", sizeof(double) * S.nseg, &rc);
   if (rc) return rc;
-  BlSt* st = stb->as<BlSt>();
-  double* pt = part->as<double>();
+  BlSt *st = stb->as<BlSt>(), *st_b = st + S.nseg, *st_a = st_b + S.nseg;   // st: what a cycle starts from
   hipStream_t s = ctx->stream;
   const Seg& L = S.dev;
+  const Seg& P = prod_seg(A, L);   // the products' layout
 
   std::vector<double> fn2;
   HZ_TRY(seg_norm2_t<T>(ctx, S, f, &fn2));
   out->fnorm.resize(S.nseg);
   for (int i = 0; i < S.nseg; ++i) out->fnorm[i] = std::sqrt(fn2[i]);
   HZ_HIP(hipMemcpyAsync(fnb->p, fn2.data(), sizeof(double) * S.nseg, hipMemcpyHostToDevice, s));
-  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(BlSt) * S.nseg, s));
+  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(BlSt) * 3 * S.nseg, s));
   k_bl_set_thr<<<ceil_div(S.nseg, kBlock), kBlock, 0, s>>>(S.nseg, st, fnb->as<double>(), ctl.tol);
   HZ_HIP(hipGetLastError());
 
-  void* hp = nullptr;
-  HZ_TRY(ctx_pinned(ctx, sizeof(BlSt) * S.nseg, &hp));
-  BlSt* hst = static_cast<BlSt*>(hp);
-  const int grid = S.nblk;
+  StatePoll poll;
+  HZ_TRY(poll.init(ctx, sizeof(BlSt) * S.nseg));
+  const Seg& W = A.tz.on ? S.vec_runs : S.vec;   // vector layout
+  PartBuf pr, pa, pb, pg, pc;        // sums of the residual, alpha, beta, minimal-residual and cycle steps
+  HZ_TRY(pr.init(ctx, S, P, 1, W.nblk, p + "part.r"));
+  HZ_TRY(pa.init(ctx, S, P, 2, W.nblk, p + "part.a"));
+  HZ_TRY(pb.init(ctx, S, P, 2, W.nblk, p + "part.b"));
+  HZ_TRY(pg.init(ctx, S, W, 2 * l + l * (l + 1), 1, p + "part.g"));
+  HZ_TRY(pc.init(ctx, S, W, 3, W.nblk, p + "part.c"));
   int64_t resid_calls = 0;
-  int chunk = 1;
+  if (A.tz.on) HZ_HIP(hipMemsetAsync(V.e, 0, vb, s));
 
-  auto read_state = [&]() -> int {
-    HZ_HIP(hipMemcpyAsync(hst, st, sizeof(BlSt) * S.nseg, hipMemcpyDeviceToHost, s));
-    HZ_HIP(hipStreamSynchronize(s));
-    return HZ_OK;
+  auto report = [&]() -> int {
+    k_bl_report<<<S.nseg, kBlock, 0, s>>>(pc.part, st, poll.slot<BlSt>());
+    HZ_HIP(hipGetLastError());
+    return poll.posted_one();
   };
   auto enqueue_resid = [&](int all) -> int {
-    k_bl_mark<<<ceil_div(S.nseg, kBlock), kBlock, 0, s>>>(S.nseg, st, all);
-    if (A.val) k_bl_resid<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else if (A.st) k_bl_resid<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else k_bl_resid<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    k_bl_resid_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
+    k_bl_settle<<<S.nseg, kBlock, 0, s>>>(pc.part, st, all);
+    if (A.tz.on && resid_calls > 0) k_bl_fold<T><<<W.nblk, kBlock, 0, s>>>(W, A.tz, st, V, 0);
+    HZ_BY_FORM(A, k_bl_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pr.raw));
+    HZ_TRY(pr.close<1>(s));
+    k_bl_resid_fin<<<S.nseg, kBlock, 0, s>>>(pr.part, st);
     HZ_HIP(hipGetLastError());
     ++resid_calls;
-    return HZ_OK;
+    HZ_TRY(report());
+    return poll.wait(poll.posted - 1);
   };
   auto enqueue_cycle = [&]() -> int {
     for (int j = 0; j < l; ++j) {
-      k_bl_u<T><<<grid, kBlock, 0, s>>>(L, st, V, j);
-      if (A.val) k_bl_prod<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V.u[j], V.u[j + 1], V.rt, pt);
-      else if (A.st) k_bl_prod<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V.u[j], V.u[j + 1], V.rt, pt);
-      else k_bl_prod<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V.u[j], V.u[j + 1], V.rt, pt);
-      k_bl_alpha_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
-      k_bl_r<T><<<grid, kBlock, 0, s>>>(L, st, V, j);
-      if (A.val) k_bl_prod<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V.r[j], V.r[j + 1], V.rt, pt);
-      else if (A.st) k_bl_prod<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V.r[j], V.r[j + 1], V.rt, pt);
-      else k_bl_prod<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V.r[j], V.r[j + 1], V.rt, pt);
-      if (j + 1 < l) k_bl_beta_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
+      const BlSt* from = j == 0 ? st : st_a;
+      HZ_BY_SCALING(A, k_bl_u<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pb.part, pc.part, from, st_b, V, j));
+      const cx<T>* uj = A.tz.on ? V.in : V.u[j];
+      HZ_BY_FORM(A, k_bl_prod<T, F, true><<<P.nblk, kBlock, 0, s>>>(P, A, st_b, uj, V.u[j + 1], V.rt, pa.raw));
+      HZ_TRY(pa.close<2>(s));
+      HZ_BY_SCALING(A, k_bl_r<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st_b, st_a, V, j));
+      const cx<T>* rj = A.tz.on ? V.in : V.r[j];
+      if (j + 1 < l) {
+        HZ_BY_FORM(A, k_bl_prod<T, F, true><<<P.nblk, kBlock, 0, s>>>(P, A, st_a, rj, V.r[j + 1], V.rt, pb.raw));
+        HZ_TRY(pb.close<2>(s));
+      } else {
+        HZ_BY_FORM(A, k_bl_prod<T, F, false><<<P.nblk, kBlock, 0, s>>>(P, A, st_a, rj, V.r[j + 1], V.rt, nullptr));
+      }
     }
     switch (l) {
-      case 1: HZ_TRY((enqueue_mr<T, 1>(s, S, st, V, pt))); break;
-      case 2: HZ_TRY((enqueue_mr<T, 2>(s, S, st, V, pt))); break;
-      case 3: HZ_TRY((enqueue_mr<T, 3>(s, S, st, V, pt))); break;
-      case 4: HZ_TRY((enqueue_mr<T, 4>(s, S, st, V, pt))); break;
-      case 5: HZ_TRY((enqueue_mr<T, 5>(s, S, st, V, pt))); break;
-      case 6: HZ_TRY((enqueue_mr<T, 6>(s, S, st, V, pt))); break;
-      case 7: HZ_TRY((enqueue_mr<T, 7>(s, S, st, V, pt))); break;
-      default: HZ_TRY((enqueue_mr<T, 8>(s, S, st, V, pt))); break;
+      case 1: return enqueue_mr<T, 1>(s, W, st_a, st, V, pg, pc);
+      case 2: return enqueue_mr<T, 2>(s, W, st_a, st, V, pg, pc);
+      case 3: return enqueue_mr<T, 3>(s, W, st_a, st, V, pg, pc);
+      case 4: return enqueue_mr<T, 4>(s, W, st_a, st, V, pg, pc);
+      case 5: return enqueue_mr<T, 5>(s, W, st_a, st, V, pg, pc);
+      case 6: return enqueue_mr<T, 6>(s, W, st_a, st, V, pg, pc);
+      case 7: return enqueue_mr<T, 7>(s, W, st_a, st, V, pg, pc);
+      default: return enqueue_mr<T, 8>(s, W, st_a, st, V, pg, pc);
     }
-    k_bl_cycle_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
-    HZ_HIP(hipGetLastError());
-    return HZ_OK;
   };
 
   HZ_TRY(enqueue_resid(1));
-  HZ_TRY(read_state());
+  const BlSt* hst = poll.state<BlSt>(poll.posted - 1);
+  int chunk = 1;
   for (;;) {
+    // everything queued has run: hst is the state
     bool all_done = true, any_brk = false;
     int max_iter = 0;
     for (int i = 0; i < S.nseg; ++i) {
@@ -482,7 +498,7 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
       // the recursive residuals say converged: confirm with the true residual
       // (a segment whose recursion drifted restarts from it)
       HZ_TRY(enqueue_resid(1));
-      HZ_TRY(read_state());
+      hst = poll.state<BlSt>(poll.posted - 1);
       bool ok = true;
       for (int i = 0; i < S.nseg; ++i) ok = ok && hst[i].done;
       if (ok || mv + 1 >= ctl.max_matvec) break;
@@ -491,14 +507,34 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     if (mv + 2 * l > ctl.max_matvec) break;
     if (any_brk) {
       HZ_TRY(enqueue_resid(0));
-      HZ_TRY(read_state());
+      hst = poll.state<BlSt>(poll.posted - 1);
       continue;
     }
-    int n_cyc = int(std::min<int64_t>(chunk, (ctl.max_matvec - mv) / (2 * l)));
-    if (n_cyc < 1) break;
-    for (int c = 0; c < n_cyc; ++c) HZ_TRY(enqueue_cycle());
-    HZ_TRY(read_state());
-    chunk = std::min(chunk * 2, 16);
+    int64_t left = (ctl.max_matvec - mv) / (2 * l);   // cycles that may still be queued
+    const int first = poll.posted;
+    for (bool stop = false; !stop && left > 0;) {
+      const int n_cyc = int(std::min<int64_t>(chunk, left));
+      for (int c = 0; c < n_cyc; ++c) HZ_TRY(enqueue_cycle());
+      left -= n_cyc;
+      HZ_TRY(report());
+      if (poll.posted - 1 > first) {
+        HZ_TRY(poll.wait(poll.posted - 2));
+        const BlSt* h = poll.state<BlSt>(poll.posted - 2);
+        bool off = true, brk = false;
+        for (int i = 0; i < S.nseg; ++i) {
+          off = off && h[i].done;
+          brk = brk || (h[i].brk && !h[i].done);
+        }
+        stop = off || brk;
+      }
+      chunk = std::min(chunk * 2, 2);
+    }
+    HZ_TRY(poll.wait(poll.posted - 1));
+    hst = poll.state<BlSt>(poll.posted - 1);
+  }
+  if (A.tz.on) {
+    k_bl_fold<T><<<W.nblk, kBlock, 0, s>>>(W, A.tz, st, V, 1);
+    HZ_HIP(hipGetLastError());
   }
   out->iters.resize(S.nseg);
   out->matvecs.resize(S.nseg);

@@ -117,7 +117,13 @@ int hz_set_params(hz_ctx ctx, const hz_c128* beta, const double* eta) {
     for (int w = 0; w < 6; ++w) ctx->beta[w] = std::complex<double>(beta[w].re, beta[w].im);
   }
   if (eta) {
-    HZ_TRY(host_assemble_meta(&ctx->h, eta));
+    if (ctx->tz) {   // the matrix itself is assembled when something needs it
+      for (int64_t e = 0; e < ctx->h.ne; ++e)
+        if (!std::isfinite(eta[e])) return hz_fail(HZ_ERR_INVALID, "eta[%lld] is not finite", (long long)e);
+    } else {
+      HZ_TRY(host_assemble_meta(&ctx->h, eta));
+    }
+    ctx->meta_host = !ctx->tz;
     ctx->have_eta = true;
     ctx->eta_field.assign(eta, eta + ctx->h.ne);
   }
@@ -139,7 +145,7 @@ int hz_set_frequency(hz_ctx ctx, double freq_hz) {
   if (!std::isfinite(freq_hz) || freq_hz < 0.0) return hz_fail(HZ_ERR_INVALID, "frequency must be finite and >= 0");
   ctx->freq = freq_hz;
   ctx->k = 2.0 * M_PI * freq_hz / ctx->c;
-  HZ_TRY(op_set_frequency(ctx, op_parts(ctx), ctx->k, 1, false));
+  HZ_TRY(op_set_frequency(ctx, ctx->k, 1, false));
   ctx->scaled = HZ_JACOBI;
   ctx->have_A32 = false;
   ctx->have_freq = true;
@@ -152,11 +158,16 @@ int hz_apply(hz_ctx ctx, const hz_c128* x_dev, hz_c128* y_dev) {
   HZ_TRY(check_ctx(ctx));
   if (!x_dev || !y_dev) return hz_fail(HZ_ERR_INVALID, "null vector");
   if (!ctx->have_freq) return hz_fail(HZ_ERR_STATE, "no frequency set");
-  int rc = 0;
   const int64_t n = ctx->h.n, nr = ctx->sell.n_rows;
+  const z_t* x = reinterpret_cast<const z_t*>(x_dev);
+  if (ctx->tz) {   // the mesh's own numbering, no scaling folded in: x and y as they are
+    SellOp<double> A = op_A(ctx);
+    A.tz.scale = 0;
+    return op_spmv<double>(ctx->stream, nr, n, A, x, reinterpret_cast<z_t*>(y_dev));
+  }
+  int rc = 0;
   DevBuf* t = ctx->buf("apply.x", sizeof(z_t) * nr, &rc);
   if (rc) return rc;
-  const z_t* x = reinterpret_cast<const z_t*>(x_dev);
   // a column-scaled operator A D^-1 is applied to D x
   HZ_TRY(pad_in(ctx, n, nr, x, ctx->scaled == HZ_JACOBI ? ctx->d_d.as<z_t>() : nullptr, t->as<z_t>()));
   if (ctx->perm.empty()) {
@@ -278,15 +289,26 @@ int hz_receiver_energy(hz_ctx ctx, int32_t n_rec, const int32_t* receivers, cons
 }
 
 namespace {
-enum { kKindComplex = 0, kKindSplit = 1, kKindStencil = 2 };
+enum { kKindComplex = 0, kKindSplit = 1, kKindStencil = 2, kKindTensor = 3 };
 // The product of the given form: the solvers' choice, or a forced form.
 int spmv_form(hz_ctx ctx, int32_t precision, int32_t format, int* kind) {
   if (precision != HZ_FP64 && precision != HZ_MIXED) return hz_fail(HZ_ERR_INVALID, "bad precision");
   if (format != HZ_SPMV_SOLVER && format != HZ_SPMV_COMPLEX && format != HZ_SPMV_SPLIT &&
-      format != HZ_SPMV_STENCIL)
+      format != HZ_SPMV_STENCIL && format != HZ_SPMV_TENSOR)
     return hz_fail(HZ_ERR_INVALID, "bad format");
   const bool mixed = precision == HZ_MIXED;
+  if (format == HZ_SPMV_TENSOR) {
+    if (!ctx->tz) return hz_fail(HZ_ERR_STATE, "no tensor form (not a box on a tensor-product grid, or HZ_TENSOR=0)");
+    if (!ctx->have_freq) return hz_fail(HZ_ERR_STATE, "no frequency set (call hz_set_frequency first)");
+    *kind = kKindTensor;
+    return HZ_OK;
+  }
   HZ_TRY(ensure_operator(ctx, ctx->scaled < 0 ? HZ_JACOBI : ctx->scaled, mixed));
+  if (ctx->tz && !ctx->have_stored) {   // the solvers do without the stored forms
+    HZ_TRY(ctx_need_meta(ctx, true));
+    HZ_TRY(op_form_stored(ctx, op_parts(ctx), ctx->k, ctx->scaled == HZ_JACOBI ? 1 : 0, true));
+    ctx->have_stored = true;
+  }
   const bool split = mixed ? ctx->have_split32 : ctx->have_split;
   const bool stencil = mixed ? ctx->have_stencil32 : ctx->have_stencil;
   if (format == HZ_SPMV_SPLIT && !split)
@@ -316,9 +338,11 @@ int hz_time_spmv(hz_ctx ctx, int32_t reps, int32_t precision, int32_t format, do
   DevBuf* yb = ctx->buf("time.y", es * nr, &rc);
   if (rc) return rc;
   HZ_HIP(hipMemsetAsync(xb->p, 0, es * nr, ctx->stream));
-  const SellOp<double> A64 = kind == kKindStencil ? op_stencil<double>(ctx)
+  const SellOp<double> A64 = kind == kKindTensor    ? op_A(ctx)
+                             : kind == kKindStencil ? op_stencil<double>(ctx)
                              : kind == kKindSplit  ? op_split<double>(ctx) : op_A_complex(ctx);
-  const SellOp<float> A32 = kind == kKindStencil ? op_stencil<float>(ctx)
+  const SellOp<float> A32 = kind == kKindTensor    ? op_A32(ctx)
+                            : kind == kKindStencil ? op_stencil<float>(ctx)
                             : kind == kKindSplit  ? op_split<float>(ctx) : op_A32_complex(ctx);
   auto one = [&]() -> int {
     if (mixed) return op_spmv<float>(ctx->stream, nr, nr, A32, xb->as<c_t>(), yb->as<c_t>());
@@ -397,6 +421,8 @@ int hz_spmv_bytes(hz_ctx ctx, int32_t precision, int32_t format, int64_t* bytes)
   const int64_t real = precision == HZ_MIXED ? 4 : 8;   // bytes of one real part
   if (kind == kKindComplex) {
     *bytes = (2 * real + 4) * nnz + 4 * (n + 1) + 4 * real * n;
+  } else if (kind == kKindTensor) {
+    *bytes = 4 * real * n + (ctx->have_eta ? 8 * int64_t(ctx->h.ne) : 0);
   } else if (kind == kKindStencil) {
     *bytes = real * nnz + (real + 4) * ctx->n_imag + 4 * (n + 1) + 4 * real * n;
   } else {

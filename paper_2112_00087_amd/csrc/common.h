@@ -116,9 +116,34 @@ __device__ __forceinline__ int xcd_chunk_tile(int b, int nblocks) {
 }
 
 // ---------------------------------------------------------------- reductions
+// Data-parallel-primitive rotation by N lanes within rows of 16.
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+// Sum over the wave, the same in every lane: the butterfly over lane
+// distances 32, 16, 8, 4, 2, 1, bit for bit, without the LDS pipe that lane
+// shuffles queue on (100 cycles and more per exchange, shared by the CU).
+// Distances 32 and 16 swap halves and rows (v + v of the other half); then
+// the values repeat every 16, 8, 4, 2 lanes, so rotations by 8, 4, 2, 1
+// within a row bring the butterfly's partner.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+  {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
+  {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  }
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
   return v;
 }
 

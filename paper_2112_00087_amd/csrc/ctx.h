@@ -78,6 +78,21 @@ struct DevBuf {
   template <typename T> T* as() const { return static_cast<T*>(p); }
 };
 
+// A box on a tensor-product grid: node coordinates per axis and the boundary
+// tag of each wall (-1: no faces there).
+struct TensorGrid {
+  std::vector<double> c[3];
+  int tag[6] = {-1, -1, -1, -1, -1, -1};
+};
+// Tensor form of one box or of stacked boxes (tensor.h) on the device.
+struct TensorDev {
+  std::vector<TzSeg> segs;
+  std::vector<int64_t> cat;          // coordinates of each box in coord
+  SegHost lay;                       // blocks of the product kernels
+  DevBuf coord, tab, dx, lt, dsegs, eta, ed;
+  bool have_eta = false;
+};
+
 struct hz_ctx_s {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -131,6 +146,15 @@ struct hz_ctx_s {
   DevBuf d_ssrc, d_S, d_S32;
   bool have_stencil = false, have_stencil32 = false;
 
+  // tensor form (a box on a tensor-product grid; HZ_TENSOR=0, HZ_STENCIL=0 or
+  // HZ_SPLIT=0 in the environment turn it off): what the solvers then use,
+  // the stored forms being made only for a call that asks for them
+  std::unique_ptr<TensorDev> tz;
+  TensorGrid tgrid;
+  bool have_stored = false;          // the stored operator holds the current frequency
+  bool meta_host = true;             // h.Meta holds eta_field
+  bool meta_dev = true;              // d_Meta holds it
+
   std::vector<std::complex<double>> beta;   // [6]
   bool have_eta = false;
   int params_version = 0;            // bumped by hz_set_params
@@ -147,6 +171,7 @@ struct hz_ctx_s {
   // scratch for solvers, keyed by name
   std::map<std::string, std::unique_ptr<DevBuf>> ws;
   std::unique_ptr<SegHost> single_seg;
+  hipEvent_t poll_ev[2] = {nullptr, nullptr};   // StatePoll
   void* pinned = nullptr;            // small pinned host buffer for status reads
   size_t pinned_bytes = 0;
 
@@ -157,4 +182,6 @@ struct hz_ctx_s {
 int ctx_upload(hz_ctx ctx);
 inline const int* ctx_perm(hz_ctx ctx) { return ctx->perm.empty() ? nullptr : ctx->d_perm.as<int>(); }
 int ctx_upload_params(hz_ctx ctx);
+// With a tensor form the assembled absorption matrix is made on demand.
+int ctx_need_meta(hz_ctx ctx, bool on_device);
 int ctx_pinned(hz_ctx ctx, size_t bytes, void** out);

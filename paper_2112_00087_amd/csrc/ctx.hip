@@ -59,6 +59,8 @@ DevBuf* hz_ctx_s::buf(const std::string& name, size_t nbytes, int* rc) {
 
 hz_ctx_s::~hz_ctx_s() {
   if (pinned) (void)hipHostFree(pinned);
+  for (hipEvent_t e : poll_ev)
+    if (e) (void)hipEventDestroy(e);
 }
 
 int ctx_pinned(hz_ctx ctx, size_t bytes, void** out) {
@@ -100,11 +102,23 @@ int ctx_upload_params(hz_ctx ctx) {
     Bb[e] = z_t{re, im};
   }
   HZ_TRY(put(ctx, ctx->d_Bb, Bb.data(), Bb.size()));
-  if (ctx->have_eta) {
+  ctx->meta_dev = false;
+  if (ctx->tz) return tensor_eta(ctx, ctx->tz.get(), ctx->have_eta ? ctx->eta_field.data() : nullptr, a.ne);
+  return ctx_need_meta(ctx, true);
+}
+
+int ctx_need_meta(hz_ctx ctx, bool on_device) {
+  if (!ctx->have_eta) return HZ_OK;
+  if (!ctx->meta_host) {
+    HZ_TRY(host_assemble_meta(&ctx->h, ctx->eta_field.data()));
+    ctx->meta_host = true;
+  }
+  if (on_device && !ctx->meta_dev) {
     std::vector<double> v(ctx->sell.n_pad, 0.0);
     for (int64_t p = 0; p < ctx->sell.n_pad; ++p)
-      if (ctx->sell.src[p] >= 0) v[p] = a.Meta[ctx->sell.src[p]];
+      if (ctx->sell.src[p] >= 0) v[p] = ctx->h.Meta[ctx->sell.src[p]];
     HZ_TRY(put(ctx, ctx->d_Meta, v.data(), v.size()));
+    ctx->meta_dev = true;
   }
   return HZ_OK;
 }
@@ -292,8 +306,15 @@ int ctx_upload(hz_ctx ctx) {
   HZ_TRY(put(ctx, ctx->d_bface, to_mesh(a.bface).data(), a.bface.size()));
   HZ_TRY(put(ctx, ctx->d_btag, a.btag.data(), a.btag.size()));
   if (!P.empty()) HZ_TRY(put(ctx, ctx->d_perm, P.data(), P.size()));
+  {
+    const char* env = std::getenv("HZ_TENSOR");
+    if (!(env && env[0] == '0') && ctx->stencil_ok && tensor_detect(a, ctx->elems, &ctx->tgrid)) {
+      ctx->tz.reset(new TensorDev());
+      HZ_TRY(tensor_build(ctx, {ctx->tgrid}, {0}, {nrows}, "tz", ctx->tz.get()));
+    }
+  }
   size_t before = ctx->d_A.bytes + ctx->d_d.bytes + ctx->d_dinv.bytes;
-  HZ_TRY(ctx->d_A.ensure(sizeof(z_t) * s.n_pad));
+  if (!ctx->tz) HZ_TRY(ctx->d_A.ensure(sizeof(z_t) * s.n_pad));
   HZ_TRY(ctx->d_d.ensure(sizeof(z_t) * nrows));
   HZ_TRY(ctx->d_dinv.ensure(sizeof(z_t) * nrows));
   ctx->dev_bytes += int64_t(ctx->d_A.bytes + ctx->d_d.bytes + ctx->d_dinv.bytes) - int64_t(before);

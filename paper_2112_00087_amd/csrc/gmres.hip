@@ -51,11 +51,14 @@ template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_resid(Seg L, SellOp<T> A, const cx<T>* __restrict__ f,
                                                   const cx<T>* __restrict__ u, cx<T>* __restrict__ V0,
                                                   double* part) {
-  SumTile t = tile_of_sums(L);
-  z_t r = zd(f[t.row]) - zd(sell_row_form<F>(A, t.row, u));
-  cx<T> rs = ccast<T>(r);
-  V0[t.row] = rs;
-  double q[1] = {norm2(zd(rs))};
+  SumTile t = prod_tile_sums<F>(L);
+  double q[1] = {0.0};
+  for_rows<F, true>(A, t, u, [=](int64_t row) { return f[row]; },
+              [&](int64_t row, cx<T> y, cx<T> fv) {
+                const cx<T> rs = ccast<T>(zd(fv) - zd(y));
+                V0[row] = rs;
+                q[0] += norm2(zd(rs));
+              });
   store_partials<1>(q, part, t);
 }
 
@@ -177,6 +180,26 @@ __global__ void HZ_PRODUCT_BOUNDS k_gs_prod(Seg L, SellOp<T> A, const GmSt* st, 
   lds_to_partials(lds, nchunk, part, L.nblk, t.tile);
 }
 
+// Pass 1 in the tensor form, whose blocks are not rows of the basis: the
+// product alone; k_mdot takes the dots.
+// Its input is the D^-1-scaled copy that pass 3 leaves beside the vector.
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_gs_only(Seg L, SellOp<T> A, const GmSt* st, GmArr G,
+                                                    const cx<T>* __restrict__ in, int j, cx<T>* __restrict__ w) {
+  Tile t = prod_tile<F>(L);
+  if (st[t.seg].cyc) return;
+  const double s = G.vs[int64_t(t.seg) * (G.m + 1) + j];
+  for_rows<F>(A, t, in, [](int64_t) { return 0; },
+              [=](int64_t row, cx<T> y, int) { w[row] = ccast<T>(s * zd(y)); });
+}
+
+// in = D^-1 V_0 (tensor form)
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_gs_start(Seg L, TzOp Z, const cx<T>* __restrict__ V, cx<T>* __restrict__ in) {
+  const Tile t = tile_of(L);
+  in[t.row] = ccast<T>(tz_pre<kFormTensor>(Z, tz_seg(Z, t.seg), t.row, zd(V[t.row])));
+}
+
 // Pass 2 with R threads per row (R = 4 or 8), for j + 1 <= R Q: a block of
 // 256 threads walks its 256-row tile 256 / R rows at a time; thread (row r,
 // part p) holds basis vectors p Qa .. p Qa + Qa - 1 (Qa = ceil((j + 1) / R))
@@ -258,10 +281,12 @@ __global__ void __launch_bounds__(kBlock) k_gs_second(Seg L, const GmSt* st, GmA
 }
 
 // Pass 3: w2 = w1 - sum_i h2_i v_i with w1 = w - sum_i h1_i v_i, written in
-// place of w (the next stored basis vector); partial ||w2||^2.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_gs_third(Seg L, const GmSt* st, GmArr G, const cx<T>* __restrict__ V,
-                                                     int64_t ld, int j, cx<T>* __restrict__ w, double* part) {
+// place of w (the next stored basis vector), in the tensor form also scaled
+// into in; partial ||w2||^2.
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_gs_third(Seg L, TzOp Z, const GmSt* st, GmArr G,
+                                                     const cx<T>* __restrict__ V, int64_t ld, int j,
+                                                     cx<T>* __restrict__ w, cx<T>* __restrict__ in, double* part) {
   SumTile t = tile_of_sums(L);
   if (st[t.seg].cyc) return;
   const double* vs = G.vs + int64_t(t.seg) * (G.m + 1);
@@ -279,6 +304,7 @@ __global__ void __launch_bounds__(kBlock) k_gs_third(Seg L, const GmSt* st, GmAr
   const z_t w1 = zd(ccast<T>(a1));
   const cx<T> ws = ccast<T>(w1 + a2);
   w[t.row] = ws;
+  if (F == kFormTensor) in[t.row] = ccast<T>(tz_pre<F>(Z, form_seg<F>(Z, t), t.row, zd(ws)));
   double q[1] = {norm2(zd(ws))};
   store_partials<1>(q, part, t);
 }
@@ -350,10 +376,10 @@ __global__ void __launch_bounds__(kFinBlock) k_mdot_fin(Seg L, const GmSt* st, G
 }
 
 // w -= sum_{i<=j} h_i V_i (h = h1 or h2); optionally partial ||w||^2
-template <typename T, bool NORM>
-__global__ void __launch_bounds__(kBlock) k_axpy(Seg L, const GmSt* st, GmArr G, const cx<T>* __restrict__ V,
+template <typename T, bool NORM, int F>
+__global__ void __launch_bounds__(kBlock) k_axpy(Seg L, TzOp Z, const GmSt* st, GmArr G, const cx<T>* __restrict__ V,
                                                  int64_t ld, int j, int pass, cx<T>* __restrict__ w,
-                                                 double* part) {
+                                                 cx<T>* __restrict__ in, double* part) {
   SumTile t = tile_of_sums(L);
   if (st[t.seg].cyc) return;
   const z_t* h = (pass == 1 ? G.h1 : G.h2) + int64_t(t.seg) * (G.m + 1);
@@ -368,6 +394,7 @@ __global__ void __launch_bounds__(kBlock) k_axpy(Seg L, const GmSt* st, GmArr G,
   cx<T> ws = ccast<T>(acc);
   w[t.row] = ws;
   if (NORM) {
+    if (F == kFormTensor) in[t.row] = ccast<T>(tz_pre<F>(Z, form_seg<F>(Z, t), t.row, zd(ws)));
     double q[1] = {norm2(zd(ws))};
     store_partials<1>(q, part, t);
   }
@@ -457,22 +484,24 @@ __global__ void k_solve_fin(const GmSt* st, GmArr G, int nseg) {
   }
 }
 
-// u += sum_{i<k} y_i V_i
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_update(Seg L, const GmSt* st, GmArr G, const cx<T>* __restrict__ V,
+// u += sum_{i<k} y_i V_i (D^-1 times the sum in the tensor form)
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_update(Seg L, TzOp Z, const GmSt* st, GmArr G, const cx<T>* __restrict__ V,
                                                    int64_t ld, cx<T>* __restrict__ u) {
   Tile t = tile_of(L);
   const GmSt& S = st[t.seg];
   if (S.done || S.nan || S.k == 0) return;
   const z_t* y = G.y + int64_t(t.seg) * G.m;
   const double* vs = G.vs + int64_t(t.seg) * (G.m + 1);
-  z_t acc = zd(u[t.row]);
+  const z_t u0 = zd(u[t.row]);
+  z_t acc = F == kFormTensor ? z_t{0.0, 0.0} : u0;
   for (int i = 0; i < S.k; ++i) {
     z_t v = vs[i] * zd(V[int64_t(i) * ld + t.row]);
     z_t yi = y[i];
     acc.re += yi.re * v.re - yi.im * v.im;
     acc.im += yi.re * v.im + yi.im * v.re;
   }
+  if (F == kFormTensor) acc = u0 + tz_pre<F>(Z, form_seg<F>(Z, t), t.row, acc);
   u[t.row] = ccast<T>(acc);
 }
 
@@ -487,10 +516,19 @@ __global__ void k_init_st(int nseg, GmSt* st, const double* fn2, double tol) {
 // pass 1 in the operator's storage form
 template <typename T>
 int gs_pass1(hipStream_t s, const Seg& L, const SellOp<T>& A, const GmSt* st, const GmArr& G, const cx<T>* V,
-             int64_t ld, int j, cx<T>* w, double* pt, int grid) {
-  if (A.val) k_gs_prod<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, G, V, ld, j, w, pt);
-  else if (A.st) k_gs_prod<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, G, V, ld, j, w, pt);
-  else k_gs_prod<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, G, V, ld, j, w, pt);
+             int64_t ld, int j, cx<T>* w, const cx<T>* in, double* pt, int grid) {
+  if (A.tz.on) {
+    const Seg& P = A.tz.lp;
+    if (A.tz.on == 1) k_gs_only<T, kFormTensor><<<P.nblk, kBlock, 0, s>>>(P, A, st, G, in, j, w);
+    else k_gs_only<T, kFormTensorExt><<<P.nblk, kBlock, 0, s>>>(P, A, st, G, in, j, w);
+    k_mdot<T><<<dim3(grid, ceil_div(j + 1, NV)), kBlock, 0, s>>>(L, st, G, V, ld, j, w, pt);
+  } else if (A.val) {
+    k_gs_prod<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, G, V, ld, j, w, pt);
+  } else if (A.st) {
+    k_gs_prod<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, G, V, ld, j, w, pt);
+  } else {
+    k_gs_prod<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, G, V, ld, j, w, pt);
+  }
   HZ_HIP(hipGetLastError());
   return HZ_OK;
 }
@@ -508,7 +546,7 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   DevBuf* Vb = ctx->buf(p + "V", sizeof(cx<T>) * ld * (m + 1), &rc);
   if (rc) return rc;
   const int nchunk = ceil_div(m + 1, NV);
-  DevBuf* part = ctx->buf(p + "part", sizeof(double) * int64_t(nchunk) * S.nblk * 2 * NV, &rc);
+  DevBuf* part = ctx->buf(p + "part", sizeof(double) * std::max(int64_t(nchunk) * S.nblk * 2 * NV, int64_t(prod_seg(A, S.dev).nblk)), &rc);
   if (rc) return rc;
   DevBuf* stb = ctx->buf(p + "st", sizeof(GmSt) * S.nseg, &rc);
   if (rc) return rc;
@@ -530,11 +568,18 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   G.h2 = zp; zp += ns * (m + 1);
   G.cs = reinterpret_cast<double*>(zp);
   G.vs = G.cs + ns * m;
+  cx<T>* in = nullptr;             // tensor form: D^-1 times the next product's vector
+  if (A.tz.on) {
+    DevBuf* ib = ctx->buf(p + "in", sizeof(cx<T>) * ld, &rc);
+    if (rc) return rc;
+    in = ib->as<cx<T>>();
+  }
   GmSt* st = stb->as<GmSt>();
   cx<T>* V = Vb->as<cx<T>>();
   double* pt = part->as<double>();
   hipStream_t s = ctx->stream;
   const Seg& L = S.dev;
+  const Seg& P = prod_seg(A, L);   // the residual product's layout
 
   std::vector<double> fn2;
   HZ_TRY(seg_norm2_t<T>(ctx, S, f, &fn2));
@@ -552,10 +597,9 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   const int grid = S.nblk;
   for (;;) {
     // residual of the current iterate; converged segments stop here
-    if (A.val) k_resid<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, f, u, V, pt);
-    else if (A.st) k_resid<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, f, u, V, pt);
-    else k_resid<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, f, u, V, pt);
-    k_beta_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, G, pt);
+    HZ_BY_FORM(A, k_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, f, u, V, pt));
+    k_beta_fin<<<S.nseg, kFinBlock, 0, s>>>(P, st, G, pt);
+    if (A.tz.on) k_gs_start<T><<<grid, kBlock, 0, s>>>(L, A.tz, V, in);
     HZ_HIP(hipGetLastError());
     int mc = int(std::min<int64_t>(m, ctl.max_matvec - mv_max - 1));
     if (mc >= 1) {
@@ -563,24 +607,27 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
         cx<T>* w = V + int64_t(j + 1) * ld;
         dim3 gd(grid, ceil_div(j + 1, NV));
         dim3 gf(S.nseg, j + 1);
-        HZ_TRY(gs_pass1<T>(s, L, A, st, G, V, ld, j, w, pt, grid));
+        HZ_TRY(gs_pass1<T>(s, L, A, st, G, V, ld, j, w, in, pt, grid));
         k_mdot_fin<<<gf, kFinBlock, 0, s>>>(L, st, G, pt, j, 1);
         if (j + 1 <= 16) k_gs_second<T, 4, 4><<<grid, kBlock, 0, s>>>(L, st, G, V, ld, j, w, pt);
         else if (j + 1 <= 32) k_gs_second<T, 8, 4><<<grid, kBlock, 0, s>>>(L, st, G, V, ld, j, w, pt);
         else if (j + 1 <= 56) k_gs_second<T, 8, 7><<<grid, kBlock, 0, s>>>(L, st, G, V, ld, j, w, pt);
         else {
           // beyond 56 basis vectors: w1 stored, then a multi-dot pass
-          k_axpy<T, false><<<grid, kBlock, 0, s>>>(L, st, G, V, ld, j, 1, w, pt);
+          k_axpy<T, false, kFormComplex><<<grid, kBlock, 0, s>>>(L, A.tz, st, G, V, ld, j, 1, w, in, pt);
           k_mdot<T><<<gd, kBlock, 0, s>>>(L, st, G, V, ld, j, w, pt);
         }
         k_mdot_fin<<<gf, kFinBlock, 0, s>>>(L, st, G, pt, j, 2);
-        if (j + 1 <= 56) k_gs_third<T><<<grid, kBlock, 0, s>>>(L, st, G, V, ld, j, w, pt);
-        else k_axpy<T, true><<<grid, kBlock, 0, s>>>(L, st, G, V, ld, j, 2, w, pt);
+        if (j + 1 <= 56) {
+          HZ_BY_SCALING(A, k_gs_third<T, F><<<grid, kBlock, 0, s>>>(L, A.tz, st, G, V, ld, j, w, in, pt));
+        } else {
+          HZ_BY_SCALING(A, k_axpy<T, true, F><<<grid, kBlock, 0, s>>>(L, A.tz, st, G, V, ld, j, 2, w, in, pt));
+        }
         k_givens_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, G, pt, j);
         HZ_HIP(hipGetLastError());
       }
       k_solve_fin<<<ceil_div(S.nseg, 64), 64, 0, s>>>(st, G, S.nseg);
-      k_update<T><<<grid, kBlock, 0, s>>>(L, st, G, V, ld, u);
+      HZ_BY_SCALING(A, k_update<T, F><<<grid, kBlock, 0, s>>>(L, A.tz, st, G, V, ld, u));
       HZ_HIP(hipGetLastError());
     }
     HZ_HIP(hipMemcpyAsync(hst, st, sizeof(GmSt) * S.nseg, hipMemcpyDeviceToHost, s));

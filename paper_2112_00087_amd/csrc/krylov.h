@@ -21,6 +21,7 @@ struct Seg {
   int64_t nrows = 0;              // nblk * kBlock
   const int* blk_seg = nullptr;   // [nblk]
   const int* seg_blk = nullptr;   // [nseg + 1]
+  const int* blk_row = nullptr;   // [nblk + 1] first rows (vector layout; NULL: 256 rows a block)
 };
 
 // A sliced-ELL operator in one of two storage forms.
@@ -53,6 +54,37 @@ struct ImSlice {
   int base, nl, w, pad;
   unsigned long long mask;
 };
+
+// Tensor form (tensor.h): the operator of a box on a tensor-product grid,
+// applied from the 1-D matrices of its axes; no stored entries.
+struct TzAxis;
+struct TzLine;
+struct TzSeg {                    // one box: a segment's rows
+  int nx, ny, nz;                 // nodes along the axes
+  int njb, nxc, nzc;              // wave grid: line groups, x pieces, plane groups
+  int blk0, nblk;                 // its blocks in the product layout
+  int row0, n, nrows;             // first row, nodes, rows with padding
+  int xt, yt, zt, lt;             // axis tables and line table offsets
+  int e0;                         // first element (absorption field)
+  double inv_nx;                  // 1 / nx
+};
+struct TzOp {
+  int on = 0;                     // 1: plain, 2: with an absorption field
+  int scale = 0;                  // x is scaled by 1 / diag(A) as it is loaded
+  int nseg = 0;
+  TzSeg s0 = {};                  // the only segment (nseg 1)
+  const TzSeg* segs = nullptr;    // [nseg] on the device
+  const TzAxis* tab = nullptr;
+  const TzLine* dx = nullptr;     // diag(A) tables: per x node and per line
+  const TzLine* lt = nullptr;
+  const double* eta = nullptr;    // absorption field per element (NULL: none)
+  const double* ed = nullptr;     // its mass diagonal per row
+  double k2 = 0.0;
+  Seg lp;                         // layout of the product kernels
+};
+struct TzCorner {                 // what each wall adds to its corner of the 1-D stiffness
+  z_t v[6];
+};
 template <typename T>
 struct SellOp {
   const int* ptr = nullptr;       // [nrows / 64 + 1] slice offsets
@@ -66,6 +98,7 @@ struct SellOp {
   const T* st = nullptr;          // stencil form
   int64_t nrows = 0;              // stencil form: rows of the vectors (gathers are clamped to them)
   StencilOffsets soff = {};
+  TzOp tz;                        // tensor form
 };
 
 // Non-temporal loads for the streamed matrix data (read once per product):
@@ -101,7 +134,7 @@ __device__ __forceinline__ void split_real(const I* __restrict__ c, const T* __r
 }
 
 // Storage forms of a SellOp (compile-time selector of sell_row_form).
-enum { kFormComplex = 0, kFormSplit = 1, kFormStencil = 2 };
+enum { kFormComplex = 0, kFormSplit = 1, kFormStencil = 2, kFormTensor = 3, kFormTensorExt = 4 };
 
 // Launch bounds of the solver kernels that carry a sparse product (T: the
 // vector type).  Capping the FP64 kernels at 6 waves per SIMD lets the
@@ -314,6 +347,127 @@ __device__ __forceinline__ void store_partials_qmajor(double (&v)[NQ], double* p
 // Finalize kernels run with kFinBlock threads, one block per segment.
 constexpr int kFinBlock = 1024;
 
+// Partial sums of a segmented reduction, NQ per block: blocks
+// [seg_blk[s], seg_blk[s + 1]) belong to segment s.
+struct Part {
+  double* p = nullptr;
+  const int* seg_blk = nullptr;
+  int nseg = 0, nblk = 0;
+};
+
+// Scalar steps without kernels of their own.  A kernel that forms sums leaves
+// block partials; the kernel that needs the scalars adds all partials of its
+// segment at its start, in block order, in every block alike (a fixed order:
+// every block gets the same bits), and one thread runs the scalar step.  The
+// state it starts from is read from one slot and the state it reaches is
+// written to another by the segment's first block, so no block reads what
+// another one writes in the same kernel.  Against a finalize kernel between
+// the two (4 to 6 us: a launch and one block's chain of loads) this costs
+// about 1 us; against finishing in the producing kernel's last block, which
+// pays a store, two atomic arrivals and a reload one after the other across
+// the XCDs, it saved 3 us per reduction at 20 to 160 thousand rows.
+//
+// All threads of the block call it; the state is in LDS afterwards.
+template <int NQ, class St, class Cond, class Fin>
+__device__ __forceinline__ const St& advance(const Part& P, const St* in, St* out, const Tile& t, bool first, Cond cond,
+                                             Fin fin) {
+  constexpr int kPasses = kFinBlock / kBlock, kWaves = kFinBlock / kWave;
+  __shared__ double lds[NQ][kWaves];
+  __shared__ double tot[NQ];
+  __shared__ St st;
+  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int b0 = P.nseg == 1 ? 0 : P.seg_blk[t.seg], b1 = P.nseg == 1 ? P.nblk : P.seg_blk[t.seg + 1];
+  // the order of a kFinBlock-thread finalize kernel (seg_sums): thread u takes
+  // blocks u, u + kFinBlock, ..., here threads u of pass m stand for u + 256 m
+  const int passes = b1 - b0 > kBlock ? kPasses : 1;
+  double acc[kPasses][NQ];
+#pragma unroll
+  for (int m = 0; m < kPasses; ++m) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[m][q] = 0.0;
+    if (m < passes)
+      for (int b = b0 + m * kBlock + int(threadIdx.x); b < b1; b += kFinBlock) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[m][q] += P.p[int64_t(b) * NQ + q];
+      }
+  }
+  // the state through LDS word by word: a private copy of the struct would
+  // live in scratch memory, which alone costs a kernel 10 us
+  static_assert(sizeof(St) % sizeof(int) == 0, "state is copied by words");
+  constexpr int kWords = sizeof(St) / sizeof(int);
+  int* sw = reinterpret_cast<int*>(&st);
+  for (int u = threadIdx.x; u < kWords; u += kBlock) sw[u] = reinterpret_cast<const int*>(in + t.seg)[u];
+#pragma unroll
+  for (int m = 0; m < kPasses; ++m) {
+    if (m < passes) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const double s = wave_sum(acc[m][q]);
+        if (lane == 0) lds[q][m * (kBlock / kWave) + w] = s;
+      }
+    }
+  }
+  __syncthreads();
+  const int waves = passes * (kBlock / kWave);
+  auto total = [&](int q) {
+    double s = 0.0;
+    for (int i = 0; i < waves; ++i) s += lds[q][i];
+    return s;
+  };
+  if (NQ > 4) {
+    for (int q = threadIdx.x; q < NQ; q += kBlock) tot[q] = total(q);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0 && cond(st)) {
+    if (NQ <= 4) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) tot[q] = total(q);
+    }
+    fin(st, static_cast<const double*>(tot));
+  }
+  __syncthreads();
+  if (first)
+    for (int u = threadIdx.x; u < kWords; u += kBlock) reinterpret_cast<int*>(out + t.seg)[u] = sw[u];
+  return st;
+}
+// First block of its segment in layout L.
+__device__ __forceinline__ bool first_block(const Seg& L, const Tile& t) {
+  return t.tile == (L.nseg == 1 ? 0 : L.seg_blk[t.seg]);
+}
+
+// The same step by one block per segment, in place (restarts) or into a
+// copy for the host (out).
+template <int NQ, class St, class Cond, class Fin>
+__device__ __forceinline__ void advance_alone(const Part& P, const St* in, St* out, Cond cond, Fin fin) {
+  Tile t;
+  t.tile = t.seg = blockIdx.x;
+  t.row = 0;
+  advance<NQ>(P, in, out, t, true, cond, fin);
+}
+
+// Vector layout: block b works on rows [blk_row[b], blk_row[b + 1]) of one
+// segment, a whole number of 256-row tiles.
+__device__ __forceinline__ Tile vec_tile(const Seg& L) {
+  Tile t;
+  t.tile = blockIdx.x;
+  t.seg = L.nseg == 1 ? 0 : L.blk_seg[t.tile];
+  t.row = L.blk_row[t.tile] + int(threadIdx.x);
+  return t;
+}
+__device__ __forceinline__ SumTile vec_tile_sums(const Seg& L) {
+  SumTile t;
+  static_cast<Tile&>(t) = vec_tile(L);
+  if (threadIdx.x == 0) *block_wave_count() = 0;
+  __syncthreads();
+  return t;
+}
+template <class Body>
+__device__ __forceinline__ void vec_rows(const Seg& L, const Tile& t, Body body) {
+  const int64_t end = L.blk_row[t.tile + 1];
+#pragma unroll 2
+  for (int64_t row = t.row; row < end; row += kBlock) body(row);
+}
+
 // Sum every quantity of this segment's partials in one pass (thread t takes
 // tiles t, t + blockDim, ...; then wave sums and the waves in order); the
 // totals are valid in thread 0.  Finalize kernels call it before they branch
@@ -367,4 +521,9 @@ struct SegHost {
   std::vector<int> seg_blk;       // host copy [nseg + 1]
   std::vector<int64_t> seg_n;     // true (unpadded) rows per segment
   Seg dev;                        // device view
+  // vector layouts of the same segments: one 256-row tile per block (stored
+  // forms), and runs of tiles, about 1,000 blocks (four per CU) at most, so
+  // that advance has few partials to add (tensor form)
+  Seg vec, vec_runs;
+  const int* iota = nullptr;      // [nseg + 1] 0, 1, ... (device)
 };

@@ -3,6 +3,7 @@
 
 #include "ctx.h"
 #include "krylov.h"
+#include "tensor.h"
 
 // Device pointers of the real operator parts (SELL layout).
 struct OpParts {
@@ -78,16 +79,44 @@ inline SellOp<T> op_stencil(hz_ctx ctx) {
   A.soff = ctx->soff;
   return A;
 }
-// The operator the solvers use: the stencil form, else the split form, when formed.
+// ---------------------------------------------------------------- tensor form
+bool tensor_detect(const HostAsm& a, const int32_t elems[3], TensorGrid* g);
+// Layout, tables and buffers of stacked boxes; rows of box s: [row0[s], row0[s] + nrows[s]).
+int tensor_build(hz_ctx ctx, const std::vector<TensorGrid>& grids, const std::vector<int64_t>& row0,
+                 const std::vector<int64_t>& nrows, const std::string& name, TensorDev* D);
+// The tables for mass coefficient m and the walls' corner terms (stream-ordered).
+int tensor_tables(hz_ctx ctx, TensorDev* D, const std::vector<TzCorner>& corners, double m);
+int tensor_diag(hz_ctx ctx, const TensorDev& D, double k2, z_t* d, z_t* dinv);
+int tensor_eta(hz_ctx ctx, TensorDev* D, const double* eta_host, int64_t count);
+TzOp tensor_op(const TensorDev& D, double k2, bool scale);
+
+// The operator the solvers use: the tensor form, else the stencil form, else
+// the split form, when formed.
+inline TzOp op_tensor(hz_ctx ctx) {
+  return tensor_op(*ctx->tz, ctx->k * ctx->k, ctx->scaled == HZ_JACOBI);
+}
 inline SellOp<double> op_A(hz_ctx ctx) {
+  if (ctx->tz) {
+    SellOp<double> A;
+    A.tz = op_tensor(ctx);
+    return A;
+  }
   return ctx->have_stencil ? op_stencil<double>(ctx) : ctx->have_split ? op_split<double>(ctx) : op_A_complex(ctx);
 }
 inline SellOp<float> op_A32(hz_ctx ctx) {
+  if (ctx->tz) {
+    SellOp<float> A;
+    A.tz = op_tensor(ctx);
+    return A;
+  }
   return ctx->have_stencil32 ? op_stencil<float>(ctx)
                              : ctx->have_split32 ? op_split<float>(ctx) : op_A32_complex(ctx);
 }
 
-int op_set_frequency(hz_ctx ctx, const OpParts& P, double k, int scale, bool want32);
+// The solvers' operator at wavenumber k: the tensor form's tables, or the stored forms.
+int op_set_frequency(hz_ctx ctx, double k, int scale, bool want32);
+// The stored forms (complex, split, stencil) whatever form the solvers use.
+int op_form_stored(hz_ctx ctx, const OpParts& P, double k, int scale, bool want32);
 // Forms A(k) (optionally column-scaled by 1/diag) on an explicit sliced-ELL
 // system; rows i >= n or with diag[i] < 0 are padding (d = 1).
 int op_form(hipStream_t s, int64_t n, int64_t nrows, int64_t npad, const int* col, const OpParts& P, double k,
@@ -127,8 +156,46 @@ struct KrylovOut {
   std::vector<double> relres_est, fnorm;
 };
 
+// The solvers' view of their device state.  Chunks of iterations are queued
+// one ahead: while a chunk runs, the state that the chunk before it left is
+// already in one of two pinned slots, so the device never waits for the
+// host's decision.  Kernels of a chunk queued after a segment has
+// stopped return at once.
+struct StatePoll {
+  hz_ctx ctx;
+  size_t bytes = 0;
+  char* host = nullptr;
+  int posted = 0;                    // copies queued so far
+  int init(hz_ctx c, size_t nbytes);
+  // Where the kernel that reports the state next writes it (pinned host
+  // memory that the device can write); posted_one() after its launch.
+  template <typename S> S* slot() const { return reinterpret_cast<S*>(host + (posted & 1) * bytes); }
+  int posted_one();
+  int wait(int k);                   // report k (0-based, one of the last two) has arrived
+  template <typename S> const S* state(int k) const { return reinterpret_cast<const S*>(host + (k & 1) * bytes); }
+};
+
+// Block partials of one reduction.  The kernels that need the sums add the
+// partials themselves (advance) as long as their blocks together read no more
+// than kMaxConsumed of them: 1,024 blocks of a tensor-form vector kernel each
+// adding 2,560 partials of 4 sums move 84 MB from L2, about the 5 us of a
+// kernel of its own.  Beyond (stored forms of large meshes, 4,942 blocks that
+// would each add 4,942 partials at 160x96x80) every block would read more
+// partials than rows, and close() adds them once with a kernel of its own;
+// it is called after every kernel that forms the sums.
+constexpr int64_t kMaxConsumed = int64_t(2560) * 1024;
+struct PartBuf {
+  double* raw = nullptr;             // where the producing kernel stores
+  Part part;                         // what the consuming kernels add
+  Seg lay;
+  bool many = false;
+  int init(hz_ctx ctx, const SegHost& S, const Seg& L, int nq, int consumers, const std::string& name);
+  template <int NQ> int close(hipStream_t s) const;
+};
+
 // Solve A u = f on every segment (u: in x0 / out), vectors of the storage
-// type T, reductions and Krylov scalars in FP64.
+// type T, reductions and Krylov scalars in FP64.  In the stored forms A is
+// A D^-1 and u = D x; in the tensor form A is unscaled and u is x.
 template <typename T>
 int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, cx<T>* u,
                  const KrylovCtl& ctl, KrylovOut* out, const std::string& tag);

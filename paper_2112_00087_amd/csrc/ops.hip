@@ -108,9 +108,25 @@ int grow(hz_ctx ctx, DevBuf& b, size_t bytes) {
 }
 }  // namespace
 
-int op_set_frequency(hz_ctx ctx, const OpParts& P, double k, int scale, bool want32) {
+int op_set_frequency(hz_ctx ctx, double k, int scale, bool want32) {
+  if (!ctx->tz) return op_form_stored(ctx, op_parts(ctx), k, scale, want32);
+  // i k beta_w adds to the corner of wall w's axis
+  std::vector<TzCorner> corner(1, TzCorner{});
+  for (int w = 0; w < 6; ++w)
+    if (ctx->tgrid.tag[w] >= 0) {
+      const std::complex<double> b = ctx->beta[ctx->tgrid.tag[w]];
+      corner[0].v[w] = z_t{-k * b.imag(), k * b.real()};
+    }
+  ctx->have_stored = false;
+  HZ_TRY(tensor_tables(ctx, ctx->tz.get(), corner, mass_coefficient(k, ctx->h.gls_h)));
+  return tensor_diag(ctx, *ctx->tz, k * k, ctx->d_d.as<z_t>(), ctx->d_dinv.as<z_t>());
+}
+
+int op_form_stored(hz_ctx ctx, const OpParts& P, double k, int scale, bool want32) {
   const bool split = ctx->split_on && !ctx->have_eta;
   const int64_t npad = ctx->sell.n_pad, ni = ctx->n_islots;
+  HZ_TRY(grow(ctx, ctx->d_A, sizeof(z_t) * npad));
+  if (want32) HZ_TRY(grow(ctx, ctx->d_A32, sizeof(c_t) * npad));
   if (split) {
     HZ_TRY(grow(ctx, ctx->d_R, sizeof(double) * npad));
     HZ_TRY(grow(ctx, ctx->d_I, sizeof(double) * std::max<int64_t>(ni, 1)));
@@ -154,16 +170,24 @@ int op_set_frequency(hz_ctx ctx, const OpParts& P, double k, int scale, bool wan
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_spmv(int64_t nout, SellOp<T> A, const cx<T>* __restrict__ x,
                                                  cx<T>* __restrict__ y) {
-  int64_t row = int64_t(xcd_chunk_tile(blockIdx.x, gridDim.x)) * kBlock + threadIdx.x;
-  cx<T> v = sell_row_form<F>(A, row, x);
-  if (row < nout) y[row] = v;
+  Tile t;
+  if constexpr (F == kFormTensor || F == kFormTensorExt) {
+    t = prod_tile<F>(A.tz.lp);
+  } else {
+    t.tile = xcd_chunk_tile(blockIdx.x, gridDim.x);
+    t.seg = 0;
+    t.row = int64_t(t.tile) * kBlock + threadIdx.x;
+  }
+  for_rows<F>(A, t, x, [](int64_t) { return 0; },
+              [=](int64_t row, cx<T> v, int) {
+                if (row < nout) y[row] = v;
+              });
 }
 
 template <typename T>
 int op_spmv(hipStream_t s, int64_t nrows, int64_t nout, const SellOp<T>& A, const cx<T>* x, cx<T>* y) {
-  if (A.val) k_spmv<T, kFormComplex><<<int(nrows / kBlock), kBlock, 0, s>>>(nout, A, x, y);
-  else if (A.st) k_spmv<T, kFormStencil><<<int(nrows / kBlock), kBlock, 0, s>>>(nout, A, x, y);
-  else k_spmv<T, kFormSplit><<<int(nrows / kBlock), kBlock, 0, s>>>(nout, A, x, y);
+  const int grid = A.tz.on ? A.tz.lp.nblk : int(nrows / kBlock);
+  HZ_BY_FORM(A, k_spmv<T, F><<<grid, kBlock, 0, s>>>(nout, A, x, y));
   HZ_HIP(hipGetLastError());
   return HZ_OK;
 }

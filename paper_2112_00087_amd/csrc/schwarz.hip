@@ -166,7 +166,7 @@ int build_dd(hz_ctx ctx, DDData* D) {
             }
         std::vector<int32_t> hex(lx * ly * lz * 8);
         std::vector<double> eta;   // the subdomain's share of the loss field
-        if (!g.Meta.empty() && !ctx->eta_field.empty()) eta.resize(lx * ly * lz);
+        if (ctx->have_eta) eta.resize(lx * ly * lz);
         for (int64_t k = 0; k < lz; ++k)
           for (int64_t j = 0; j < ly; ++j)
             for (int64_t i = 0; i < lx; ++i) {
@@ -226,7 +226,7 @@ int build_dd(hz_ctx ctx, DDData* D) {
         row_off += U.nrows;
       }
   D->nrows = row_off;
-  D->eta = !g.Meta.empty();
+  D->eta = ctx->have_eta;
   // stacked sliced-ELL system
   std::vector<int32_t> sptr(1, 0), scol, bidx, dpos(row_off, -1), l2g(row_off, 0);
   std::vector<uint8_t> real_slot;   // 1 for a stored entry (0: slice padding)
@@ -857,7 +857,7 @@ int schwarz_solve(hz_ctx ctx, const hz_solve_opts& o, const z_t* f, z_t* p, hz_s
     HZ_TRY(R.local_solve(fst, nl > 0 ? lam : nullptr));
     k_dd_glue<<<ceil_div(n, kBlock), kBlock, 0, s>>>(n, D->g2r_ptr.as<int>(), D->g2r_row.as<int>(), u, p);
     HZ_HIP(hipGetLastError());
-    HZ_TRY(pad_in(ctx, n, ctx->sell.n_rows, p, ctx->d_d.as<z_t>(), uz));
+    HZ_TRY(pad_in(ctx, n, ctx->sell.n_rows, p, ctx->tz ? nullptr : ctx->d_d.as<z_t>(), uz));
     std::vector<double> rr;
     HZ_TRY(true_residual(ctx, *G1, op_A(ctx), fz, uz, nullptr, &rr));
     inf.matvecs += 1;

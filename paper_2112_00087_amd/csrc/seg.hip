@@ -22,10 +22,14 @@ template <int F>
 __global__ void __launch_bounds__(kBlock) k_true_resid(Seg L, SellOp<double> A, const z_t* __restrict__ f,
                                                        const z_t* __restrict__ u, z_t* __restrict__ r,
                                                        double* part) {
-  SumTile t = tile_of_sums(L);
-  z_t v = f[t.row] - sell_row_form<F>(A, t.row, u);
-  if (r) r[t.row] = v;
-  double q[1] = {norm2(v)};
+  SumTile t = prod_tile_sums<F>(L);
+  double q[1] = {0.0};
+  for_rows<F, true>(A, t, u, [=](int64_t row) { return f[row]; },
+              [&](int64_t row, z_t y, z_t fv) {
+                const z_t v = fv - y;
+                if (r) r[row] = v;
+                q[0] += norm2(v);
+              });
   store_partials<1>(q, part, t);
 }
 
@@ -58,17 +62,74 @@ template int seg_norm2_t<float>(hz_ctx, const SegHost&, const c_t*, std::vector<
 int true_residual(hz_ctx ctx, const SegHost& S, const SellOp<double>& A, const z_t* f, const z_t* u,
                   z_t* r, std::vector<double>* rr) {
   int rc = 0;
-  DevBuf* part = ctx->buf("tres.part", sizeof(double) * S.nblk, &rc);
+  const Seg& P = prod_seg(A, S.dev);
+  DevBuf* part = ctx->buf("tres.part", sizeof(double) * P.nblk, &rc);
   if (rc) return rc;
   DevBuf* res = ctx->buf("tres.out", sizeof(double) * S.nseg, &rc);
   if (rc) return rc;
-  if (A.val) k_true_resid<kFormComplex><<<S.nblk, kBlock, 0, ctx->stream>>>(S.dev, A, f, u, r, part->as<double>());
-  else if (A.st) k_true_resid<kFormStencil><<<S.nblk, kBlock, 0, ctx->stream>>>(S.dev, A, f, u, r, part->as<double>());
-  else k_true_resid<kFormSplit><<<S.nblk, kBlock, 0, ctx->stream>>>(S.dev, A, f, u, r, part->as<double>());
-  k_seg_fin1<<<S.nseg, kFinBlock, 0, ctx->stream>>>(S.dev, part->as<double>(), res->as<double>());
+  HZ_BY_FORM(A, k_true_resid<F><<<P.nblk, kBlock, 0, ctx->stream>>>(P, A, f, u, r, part->as<double>()));
+  k_seg_fin1<<<S.nseg, kFinBlock, 0, ctx->stream>>>(P, part->as<double>(), res->as<double>());
   HZ_HIP(hipGetLastError());
   return fetch_seg(ctx, S, res->as<double>(), rr);
 }
+
+int StatePoll::init(hz_ctx c, size_t nbytes) {
+  ctx = c;
+  bytes = nbytes;
+  posted = 0;
+  void* hp = nullptr;
+  HZ_TRY(ctx_pinned(c, 2 * nbytes, &hp));
+  host = static_cast<char*>(hp);
+  for (hipEvent_t& e : c->poll_ev)
+    if (!e) HZ_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  return HZ_OK;
+}
+int StatePoll::posted_one() {
+  HZ_HIP(hipEventRecord(ctx->poll_ev[posted & 1], ctx->stream));
+  ++posted;
+  return HZ_OK;
+}
+int StatePoll::wait(int k) {
+  HZ_HIP(hipEventSynchronize(ctx->poll_ev[k & 1]));
+  return HZ_OK;
+}
+
+// One total per segment and quantity (layouts of many blocks).
+namespace {
+template <int NQ>
+__global__ void k_totals(Seg L, const double* part, double* out) {
+  double o[NQ];
+  seg_sums<NQ>(L, part, blockIdx.x, o);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) out[int64_t(blockIdx.x) * NQ + q] = o[q];
+  }
+}
+}  // namespace
+int PartBuf::init(hz_ctx ctx, const SegHost& S, const Seg& L, int nq, int consumers, const std::string& name) {
+  int rc = 0;
+  many = int64_t(L.nblk) * consumers > kMaxConsumed * S.nseg;
+  DevBuf* b = ctx->buf(name, sizeof(double) * nq * (size_t(L.nblk) + S.nseg), &rc);
+  if (rc) return rc;
+  raw = b->as<double>();
+  lay = L;
+  part.nseg = S.nseg;
+  part.p = many ? raw + size_t(L.nblk) * nq : raw;
+  part.seg_blk = many ? S.iota : L.seg_blk;
+  part.nblk = many ? S.nseg : L.nblk;
+  return HZ_OK;
+}
+template <int NQ>
+int PartBuf::close(hipStream_t s) const {
+  if (!many) return HZ_OK;
+  k_totals<NQ><<<lay.nseg, kFinBlock, 0, s>>>(lay, raw, part.p);
+  HZ_HIP(hipGetLastError());
+  return HZ_OK;
+}
+template int PartBuf::close<1>(hipStream_t) const;
+template int PartBuf::close<2>(hipStream_t) const;
+template int PartBuf::close<3>(hipStream_t) const;
+template int PartBuf::close<4>(hipStream_t) const;
 
 int seg_upload(hz_ctx ctx, SegHost* S, const std::string& tag) {
   int rc = 0;
@@ -84,6 +145,43 @@ int seg_upload(hz_ctx ctx, SegHost* S, const std::string& tag) {
   if (rc) return rc;
   HZ_HIP(hipMemcpy(a->p, blk_seg.data(), sizeof(int) * S->nblk, hipMemcpyHostToDevice));
   HZ_HIP(hipMemcpy(b->p, S->seg_blk.data(), sizeof(int) * (S->nseg + 1), hipMemcpyHostToDevice));
+  // vector layouts: one tile per block, and runs of tiles of one segment
+  auto layout = [&](int per, const std::string& name, Seg* V) -> int {
+    std::vector<int> vseg, vrow, vblk(1, 0);
+    for (int s = 0; s < S->nseg; ++s) {
+      for (int b = S->seg_blk[s]; b < S->seg_blk[s + 1]; b += per) {
+        vseg.push_back(s);
+        vrow.push_back(b * kBlock);
+      }
+      vblk.push_back(int(vseg.size()));
+    }
+    vrow.push_back(S->nblk * kBlock);
+    const size_t nv = vseg.size();
+    DevBuf* vb = ctx->buf(tag + name, sizeof(int) * (nv + (nv + 1) + (S->nseg + 1)), &rc);
+    if (rc) return rc;
+    int* vp = vb->as<int>();
+    HZ_HIP(hipMemcpy(vp, vseg.data(), sizeof(int) * nv, hipMemcpyHostToDevice));
+    HZ_HIP(hipMemcpy(vp + nv, vrow.data(), sizeof(int) * (nv + 1), hipMemcpyHostToDevice));
+    HZ_HIP(hipMemcpy(vp + 2 * nv + 1, vblk.data(), sizeof(int) * (S->nseg + 1), hipMemcpyHostToDevice));
+    V->nseg = S->nseg;
+    V->nblk = int(nv);
+    V->nrows = S->nrows;
+    V->blk_seg = vp;
+    V->blk_row = vp + nv;
+    V->seg_blk = vp + 2 * nv + 1;
+    return HZ_OK;
+  };
+  const int per = std::max(1, ceil_div(S->nblk, 1024));
+  HZ_TRY(layout(1, ".vec", &S->vec));
+  if (per > 1) HZ_TRY(layout(per, ".vecr", &S->vec_runs));
+  else S->vec_runs = S->vec;
+  // one total per segment
+  std::vector<int> iota(S->nseg + 1);
+  for (int i = 0; i <= S->nseg; ++i) iota[i] = i;
+  DevBuf* ib = ctx->buf(tag + ".iota", sizeof(int) * (S->nseg + 1), &rc);
+  if (rc) return rc;
+  HZ_HIP(hipMemcpy(ib->p, iota.data(), sizeof(int) * (S->nseg + 1), hipMemcpyHostToDevice));
+  S->iota = ib->as<int>();
   S->dev.nseg = S->nseg;
   S->dev.nblk = S->nblk;
   S->dev.nrows = S->nrows;

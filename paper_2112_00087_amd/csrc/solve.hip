@@ -64,13 +64,13 @@ int unpad_out(hz_ctx ctx, int64_t n, const z_t* u, const z_t* scale, z_t* p) {
 
 int ensure_operator(hz_ctx ctx, int precond, bool want32) {
   if (!ctx->have_freq) return hz_fail(HZ_ERR_STATE, "no frequency set (call hz_set_frequency first)");
-  if (want32 && !ctx->d_A32.p) {
-    size_t before = ctx->d_A32.bytes;
-    HZ_TRY(ctx->d_A32.ensure(sizeof(c_t) * ctx->sell.n_pad));
-    ctx->dev_bytes += int64_t(ctx->d_A32.bytes) - int64_t(before);
+  if (ctx->tz) {
+    // the tables serve both scalings and both precisions
+    ctx->scaled = precond;
+    return HZ_OK;
   }
   if (ctx->scaled != precond || (want32 && !ctx->have_A32)) {
-    HZ_TRY(op_set_frequency(ctx, op_parts(ctx), ctx->k, precond == HZ_JACOBI ? 1 : 0, want32));
+    HZ_TRY(op_set_frequency(ctx, ctx->k, precond == HZ_JACOBI ? 1 : 0, want32));
     ctx->scaled = precond;
     ctx->have_A32 = want32;
   }
@@ -159,7 +159,7 @@ int solve_single(hz_ctx ctx, const hz_solve_opts& o, const z_t* f, z_t* p, hz_so
   if (rc) return rc;
   z_t* fz = fb->as<z_t>();
   z_t* uz = ub->as<z_t>();
-  const bool jac = o.precond == HZ_JACOBI;
+  const bool jac = o.precond == HZ_JACOBI && !ctx->tz;   // the stored forms' unknown is D x
   HZ_TRY(pad_in(ctx, n, nr, f, nullptr, fz));
   HZ_TRY(pad_in(ctx, n, nr, p, jac ? ctx->d_d.as<z_t>() : nullptr, uz));
   std::vector<double> fn2;

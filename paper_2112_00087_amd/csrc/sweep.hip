@@ -1473,6 +1473,7 @@ int build_sweep_data(hz_ctx ctx, SweepData* D) {
   const int64_t nnz = int64_t(a.col.size());
   std::vector<int> rowptr(nrows + 1, 0), col(nnz), dpos(n), bptr(nrows + 1, 0), bcol;
   std::vector<double> K(nnz), M(nnz), E(D->eta ? nnz : 0);
+  HZ_TRY(ctx_need_meta(ctx, false));
   D->eta = ctx->have_eta && !a.Meta.empty();
   if (D->eta) E.resize(nnz);
   std::vector<z_t> B64, Bd(n, z_t{0.0, 0.0});

@@ -9,12 +9,15 @@
 //   odd:   w -= alpha uhat;  d = u' + (theta^2/alpha) eta d;  theta, c, tau, eta as above
 //          x += eta d;  rho' = r*^H w, beta = rho'/rho;  u = w + beta u'
 //          v = beta uhat + beta^2 v + B u;  uhat = B u;  alpha = rho' / r*^H v
-// Kernels: 3 vector, 2 product (with fused dot), 3 one-block-per-segment
-// finalize per pair.  u' lives in its own buffer for the odd half-step (it
+// Kernels: 3 vector and 2 product (with fused dot) per pair.  The scalar
+// steps run at the start of the kernel that needs them (advance), on a state
+// that moves through three slots.  In the tensor form u, u', d and x are kept scaled by D^-1 (x
+// is the solution itself), so only w and v are scaled where they enter u and
+// u' and the product's inputs need no pass of their own.  u' lives in its own buffer for the odd half-step (it
 // is never copied back into u), and the odd product reads B u' from uhat
 // and writes B u over it row by row, so v needs no staging buffer: 29
 // vector passes per pair.  A segment whose quasi-residual bound tau sqrt(m+1)
-// meets the target applies its last x update and stops; the host confirms
+// meets the target makes its last x update in the kernel that finds it and stops; the host confirms
 // with the true residual (restarting a segment that has not converged), and
 // restarts segments that broke down (r*^H v or rho zero).
 #include <chrono>
@@ -27,7 +30,8 @@ struct TqSt {
   z_t alpha, rho, beta, eta;
   double theta, tau, thr, thr2, rr;
   double chk;           // quasi-residual bound at the last stall checkpoint
-  int m, iter, done, last, brk, nan, restart, pad;
+  int m, iter, done, brk, nan, restart;
+  int pend, pad;        // pend: the sums of the alpha step are formed
   int mchk, stall_win;  // half-step of that checkpoint; its spacing (0: off)
   int stalled, pad2;    // the bound stalled: the solve ends unconfirmed
 };
@@ -47,6 +51,11 @@ struct TqV {
 
 template <typename T> __device__ __forceinline__ z_t zd(cx<T> a) { return ccast<double>(a); }
 template <typename T> __device__ __forceinline__ cx<T> zt(z_t a) { return ccast<T>(a); }
+
+template <typename T>
+struct TqPair {
+  cx<T> a, b;
+};
 
 __device__ __forceinline__ bool tq_off(const TqSt& S) { return S.done || S.brk || S.nan; }
 
@@ -69,11 +78,9 @@ __device__ __forceinline__ void tq_qmr(TqSt& S, double ww) {
   const double bound = S.tau * sqrt(double(S.m + 1));
   if (bound <= S.thr) {
     S.done = 1;       // quasi-residual bound met: the last x update follows
-    S.last = 1;
   } else if (S.stall_win > 0 && S.m - S.mchk >= S.stall_win) {
     if (bound > 0.5 * S.chk) {
       S.done = 1;     // stalled: stop with the iterate reached (last x update follows)
-      S.last = 1;
       S.stalled = 1;
     }
     S.chk = bound;
@@ -82,180 +89,184 @@ __device__ __forceinline__ void tq_qmr(TqSt& S, double ww) {
   S.m += 1;
 }
 
-// ---------------------------------------------------------------- restart
-__global__ void k_tq_mark(int nseg, TqSt* st, int all) {
-  int s = blockIdx.x * kBlock + threadIdx.x;
-  if (s >= nseg) return;
-  st[s].restart = all ? 1 : st[s].brk;
+// The scalar steps, run by one thread once a segment's sums are complete.
+__device__ __forceinline__ void tq_resid(TqSt& S, const double* o) {
+  const double rr = o[0];
+  S.rr = rr;
+  S.nan = !isfinite(rr);
+  S.done = (rr <= S.thr2) || S.nan;
+  S.brk = 0;
+  S.restart = S.done ? 0 : 2;   // 2: the first product, v = uhat = B u, is due
+  S.pend = !S.done;
+  S.tau = sqrt(rr);
+  S.theta = 0.0;
+  S.eta = z_t{0.0, 0.0};
+  S.rho = z_t{rr, 0.0};
+  S.m = 0;
+  S.chk = S.tau;
+  S.mchk = 0;
+}
+// alpha = rho / r*^H v
+__device__ __forceinline__ void tq_alpha(TqSt& S, const double* o) {
+  S.pend = 0;
+  S.restart = 0;
+  const z_t sg = {o[0], o[1]};
+  if (norm2(sg) == 0.0 || !isfinite(o[0]) || !isfinite(o[1])) S.brk = 1;
+  else S.alpha = cdiv(S.rho, sg);
+}
+__device__ __forceinline__ void tq_odd(TqSt& S, const double* o) {
+  tq_qmr(S, o[0]);
+  const z_t rho1 = {o[1], o[2]};
+  if (norm2(S.rho) == 0.0 || !isfinite(o[1]) || !isfinite(o[2])) {
+    if (!S.done) S.brk = 1;
+  } else {
+    S.beta = cdiv(rho1, S.rho);
+    S.rho = rho1;
+  }
+  S.pend = !tq_off(S);   // k_tq_odd3 forms the sums of the alpha step
+}
+__device__ __forceinline__ void tq_even(TqSt& S, const double* o) { tq_qmr(S, o[0]); }
+__device__ __forceinline__ bool tq_on(const TqSt& S) { return !tq_off(S); }
+__device__ __forceinline__ bool tq_pending(const TqSt& S) { return S.pend; }
+
+// The state after the sums formed last: in place after k_tq_resid, for the
+// host after k_tq_odd3.
+__global__ void __launch_bounds__(kBlock) k_tq_resid_fin(Part P, TqSt* st) {
+  advance_alone<1>(P, st, st, [](const TqSt& S) { return S.restart == 1; }, tq_resid);
+}
+// At a restart the slot a pair starts from takes up the pending sums; the
+// segments that restart are all of them, or those that broke down.
+__global__ void __launch_bounds__(kBlock) k_tq_settle(Part P, TqSt* st, int all) {
+  advance_alone<2>(P, st, st, tq_pending, tq_alpha);
+  if (threadIdx.x == 0) st[blockIdx.x].restart = all ? 1 : st[blockIdx.x].brk;
+}
+__global__ void __launch_bounds__(kBlock) k_tq_report(Part P, const TqSt* in, TqSt* out) {
+  advance_alone<2>(P, in, out, tq_pending, tq_alpha);
 }
 
+// ---------------------------------------------------------------- restart
 // r0 = f - B x; r* = w = u = r0; d = 0; partial ||r0||^2
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_tq_resid(Seg L, SellOp<T> A, const TqSt* st, TqV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
-  if (!st[t.seg].restart) return;
-  const cx<T> r = zt<T>(zd(V.f[t.row]) - zd(sell_row_form<F>(A, t.row, V.x)));
-  V.rs[t.row] = r;
-  V.w[t.row] = r;
-  V.u[t.row] = r;
-  V.d[t.row] = cx<T>{T(0), T(0)};
-  double q[1] = {norm2(zd(r))};
+  SumTile t = prod_tile_sums<F>(L);
+  if (st[t.seg].restart != 1) return;
+  double q[1] = {0.0};
+  for_rows<F, true>(A, t, V.x, [=](int64_t row) { return V.f[row]; },
+              [&](int64_t row, cx<T> y, cx<T> f) {
+                const cx<T> r = zt<T>(zd(f) - zd(y));
+                V.rs[row] = r;
+                V.w[row] = r;
+                V.u[row] = r;
+                V.d[row] = cx<T>{T(0), T(0)};
+                q[0] += norm2(zd(r));
+              });
   store_partials<1>(q, part, t);
 }
 
-__global__ void k_tq_resid_fin(Seg L, TqSt* st, const double* part) {
-  const int s = blockIdx.x;
-  const int go = st[s].restart;
-  __syncthreads();
-  if (!go) return;
-  double o[1];
-  seg_sums<1>(L, part, s, o);
-  if (threadIdx.x == 0) {
-    TqSt& S = st[s];
-    const double rr = o[0];
-    S.rr = rr;
-    S.nan = !isfinite(rr);
-    S.done = (rr <= S.thr2) || S.nan;
-    S.last = 0;
-    S.brk = 0;
-    S.tau = sqrt(rr);
-    S.theta = 0.0;
-    S.eta = z_t{0.0, 0.0};
-    S.rho = z_t{rr, 0.0};
-    S.m = 0;
-    S.chk = S.tau;
-    S.mchk = 0;
-    // restart stays set until the first product (v = uhat = B u) is formed
-  }
+// Tensor form: u is kept scaled by D^-1
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_tq_start(Seg L, TzOp Z, const TqSt* st, TqV<T> V) {
+  const Tile t = vec_tile(L);
+  if (st[t.seg].restart != 2) return;
+  const TzSeg B = form_seg<F>(Z, t);
+  vec_rows(L, t, [&](int64_t row) { V.u[row] = zt<T>(tz_pre<F>(Z, B, row, zd(V.u[row]))); });
 }
 
 // v = uhat = B u for restarting segments; partial r*^H v
 template <typename T, int F>
-__global__ void HZ_PRODUCT_BOUNDS k_tq_resid_prod(Seg L, SellOp<T> A, const TqSt* st, TqV<T> V,
-                                                          double* part) {
-  SumTile t = tile_of_sums(L);
-  const TqSt& S = st[t.seg];
-  if (!S.restart || S.done) return;
-  const cx<T> y = sell_row_form<F>(A, t.row, V.u);
-  V.v[t.row] = y;
-  V.uh[t.row] = y;
+__global__ void HZ_PRODUCT_BOUNDS k_tq_resid_prod(Seg L, SellOp<T> A, const TqSt* st, TqV<T> V, double* part) {
+  SumTile t = prod_tile_sums<F>(L);
+  if (st[t.seg].restart != 2) return;
   double q[2] = {0.0, 0.0};
-  acc_dot(q, zd(V.rs[t.row]), zd(y));
+  for_rows<F>(A, t, V.u, [=](int64_t row) { return V.rs[row]; },
+              [&](int64_t row, cx<T> y, cx<T> rs) {
+                V.v[row] = y;
+                V.uh[row] = y;
+                acc_dot(q, zd(rs), zd(y));
+              });
   store_partials<2>(q, part, t);
 }
 
-// alpha = rho / r*^H v (after a restart, or after the odd half-step's product)
-__global__ void k_tq_alpha_fin(Seg L, TqSt* st, const double* part, int after_restart) {
-  const int s = blockIdx.x;
-  const TqSt& S0 = st[s];
-  const int go = after_restart ? (S0.restart && !S0.done) : !tq_off(S0);
-  const int clear = after_restart && S0.restart;
-  const int done = S0.done;
-  double o[2];
-  seg_sums<2>(L, part, s, o);   // its barriers: every thread has read the flags
-  if (threadIdx.x == 0 && clear) st[s].restart = 0;
-  if (threadIdx.x == 0 && done) st[s].last = 0;
-  if (!go) return;
-  if (threadIdx.x == 0) {
-    TqSt& S = st[s];
-    const z_t sg = {o[0], o[1]};
-    if (norm2(sg) == 0.0 || !isfinite(o[0]) || !isfinite(o[1])) S.brk = 1;
-    else S.alpha = cdiv(S.rho, sg);
-  }
-}
-
 // ---------------------------------------------------------------- even half-step
-// u' = u - alpha v; w -= alpha uhat; d = u + (theta^2/alpha) eta d; partial ||w||^2
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_tq_even1(Seg L, const TqSt* st, TqV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
-  const TqSt& S = st[t.seg];
+// alpha; u' = u - alpha v; w -= alpha uhat; d = u + (theta^2/alpha) eta d; partial ||w||^2
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_tq_even1(Seg L, TzOp Z, Part P, const TqSt* in, TqSt* out, TqV<T> V, double* part) {
+  const SumTile t = vec_tile_sums(L);
+  const TqSt& S = advance<2>(P, in, out, t, first_block(L, t), tq_pending, tq_alpha);
   if (tq_off(S)) return;
+  const TzSeg B = form_seg<F>(Z, t);
   const z_t a = S.alpha;
-  const z_t u = zd(V.u[t.row]);
-  V.un[t.row] = zt<T>(u - a * zd(V.v[t.row]));
-  const cx<T> w = zt<T>(zd(V.w[t.row]) - a * zd(V.uh[t.row]));
-  V.w[t.row] = w;
   const z_t g = (S.theta * S.theta) * cdiv(S.eta, a);
-  V.d[t.row] = zt<T>(u + g * zd(V.d[t.row]));
-  double q[1] = {norm2(zd(w))};
+  double q[1] = {0.0};
+  vec_rows(L, t, [&](int64_t row) {
+    const z_t u = zd(V.u[row]);
+    const z_t av = a * zd(V.v[row]);
+    const cx<T> w = zt<T>(zd(V.w[row]) - a * zd(V.uh[row]));
+    const z_t d = zd(V.d[row]);
+    V.un[row] = zt<T>(u - tz_pre<F>(Z, B, row, av));
+    V.w[row] = w;
+    V.d[row] = zt<T>(u + g * d);
+    q[0] += norm2(zd(w));
+  });
   store_partials<1>(q, part, t);
 }
 
-__global__ void k_tq_qmr_fin(Seg L, TqSt* st, const double* part) {
-  const int s = blockIdx.x;
-  const TqSt& S0 = st[s];
-  const int off = tq_off(S0), done = S0.done;
-  double o[1];
-  seg_sums<1>(L, part, s, o);   // its barriers: every thread has read the flags
-  if (off) {
-    if (threadIdx.x == 0 && done) st[s].last = 0;
-    return;
-  }
-  if (threadIdx.x == 0) tq_qmr(st[s], o[0]);
-}
-
-// x += eta d; then (unless stopping) uhat = B u'
+// theta, tau, eta; x += eta d; then (unless stopping) uhat = B u'
 template <typename T, int F>
-__global__ void HZ_PRODUCT_BOUNDS k_tq_even2(Seg L, SellOp<T> A, const TqSt* st, TqV<T> V) {
-  Tile t = tile_of(L);
-  const TqSt& S = st[t.seg];
-  if (S.brk || S.nan || (S.done && !S.last)) return;
-  V.x[t.row] = zt<T>(zd(V.x[t.row]) + S.eta * zd(V.d[t.row]));
-  if (S.done) return;
-  V.uh[t.row] = sell_row_form<F>(A, t.row, V.un);
+__global__ void HZ_PRODUCT_BOUNDS k_tq_even2(Seg L, SellOp<T> A, Part P, const TqSt* in, TqSt* out, TqV<T> V) {
+  Tile t = prod_tile<F>(L);
+  const bool was_done = in[t.seg].done;
+  const TqSt& S = advance<1>(P, in, out, t, first_block(L, t), tq_on, tq_even);
+  if (S.brk || S.nan || was_done) return;
+  const z_t eta = S.eta;
+  const bool done = S.done;
+  for_rows<F>(A, t, V.un, [=](int64_t row) { return TqPair<T>{V.x[row], V.d[row]}; },
+              [=](int64_t row, cx<T> y, TqPair<T> a) {
+                V.x[row] = zt<T>(zd(a.a) + eta * zd(a.b));
+                if (!done) V.uh[row] = y;
+              });
 }
 
 // ---------------------------------------------------------------- odd half-step
 // w -= alpha uhat; d = u' + (theta^2/alpha) eta d; partials ||w||^2, r*^H w
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_tq_odd1(Seg L, const TqSt* st, TqV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
+  const SumTile t = vec_tile_sums(L);
   const TqSt& S = st[t.seg];
   if (tq_off(S)) return;
   const z_t a = S.alpha;
-  const cx<T> w = zt<T>(zd(V.w[t.row]) - a * zd(V.uh[t.row]));
-  V.w[t.row] = w;
   const z_t g = (S.theta * S.theta) * cdiv(S.eta, a);
-  V.d[t.row] = zt<T>(zd(V.un[t.row]) + g * zd(V.d[t.row]));
-  const z_t wv = zd(w);
-  double q[3] = {norm2(wv), 0.0, 0.0};
-  acc_dot(q + 1, zd(V.rs[t.row]), wv);
+  double q[3] = {0.0, 0.0, 0.0};
+  vec_rows(L, t, [&](int64_t row) {
+    const cx<T> w = zt<T>(zd(V.w[row]) - a * zd(V.uh[row]));
+    const z_t d = zd(V.un[row]) + g * zd(V.d[row]), rs = zd(V.rs[row]);
+    V.w[row] = w;
+    V.d[row] = zt<T>(d);
+    const z_t wv = zd(w);
+    q[0] += norm2(wv);
+    acc_dot(q + 1, rs, wv);
+  });
   store_partials<3>(q, part, t);
 }
 
-__global__ void k_tq_odd_fin(Seg L, TqSt* st, const double* part) {
-  const int s = blockIdx.x;
-  const TqSt& S0 = st[s];
-  const int off = tq_off(S0), done = S0.done;
-  double o[3];
-  seg_sums<3>(L, part, s, o);   // its barriers: every thread has read the flags
-  if (off) {
-    if (threadIdx.x == 0 && done) st[s].last = 0;
+// theta, tau, eta, beta; x += eta d; then (unless stopping) u = w + beta u'
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_tq_odd2(Seg L, TzOp Z, Part P, const TqSt* in, TqSt* out, TqV<T> V) {
+  const Tile t = vec_tile(L);
+  const bool was_done = in[t.seg].done;
+  const TqSt& S = advance<3>(P, in, out, t, first_block(L, t), tq_on, tq_odd);
+  if (S.nan || (S.brk && !S.done) || was_done) return;
+  const TzSeg B = form_seg<F>(Z, t);
+  if (S.done) {
+    vec_rows(L, t, [&](int64_t row) { V.x[row] = zt<T>(zd(V.x[row]) + S.eta * zd(V.d[row])); });
     return;
   }
-  if (threadIdx.x == 0) {
-    TqSt& S = st[s];
-    tq_qmr(S, o[0]);
-    const z_t rho1 = {o[1], o[2]};
-    if (norm2(S.rho) == 0.0 || !isfinite(o[1]) || !isfinite(o[2])) {
-      if (!S.done) S.brk = 1;
-    } else {
-      S.beta = cdiv(rho1, S.rho);
-      S.rho = rho1;
-    }
-  }
-}
-
-// x += eta d; then (unless stopping) u = w + beta u'
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_tq_odd2(Seg L, const TqSt* st, TqV<T> V) {
-  Tile t = tile_of(L);
-  const TqSt& S = st[t.seg];
-  if (S.brk || S.nan || (S.done && !S.last)) return;
-  V.x[t.row] = zt<T>(zd(V.x[t.row]) + S.eta * zd(V.d[t.row]));
-  if (S.done) return;
-  V.u[t.row] = zt<T>(zd(V.w[t.row]) + S.beta * zd(V.un[t.row]));
+  const z_t eta = S.eta, beta = S.beta;
+  vec_rows(L, t, [&](int64_t row) {
+    const z_t x = zd(V.x[row]), d = zd(V.d[row]), w = zd(V.w[row]), un = zd(V.un[row]);
+    V.x[row] = zt<T>(x + eta * d);
+    V.u[row] = zt<T>(tz_pre<F>(Z, B, row, w) + beta * un);
+  });
 }
 
 // uhat = B u over B u' (each row reads its old value first); v = beta B u'
@@ -263,17 +274,29 @@ __global__ void __launch_bounds__(kBlock) k_tq_odd2(Seg L, const TqSt* st, TqV<T
 // the product is added; partial r*^H v
 template <typename T, int F>
 __global__ void HZ_PRODUCT_BOUNDS k_tq_odd3(Seg L, SellOp<T> A, const TqSt* st, TqV<T> V, double* part) {
-  SumTile t = tile_of_sums(L);
+  SumTile t = prod_tile_sums<F>(L);
   const TqSt& S = st[t.seg];
   if (tq_off(S)) return;
   const z_t b = S.beta;
-  const cx<T> vt = zt<T>(b * zd(V.uh[t.row]) + (b * b) * zd(V.v[t.row]));
-  const cx<T> y = sell_row_form<F>(A, t.row, V.u);
-  V.uh[t.row] = y;
-  const cx<T> v = zt<T>(zd(vt) + zd(y));
-  V.v[t.row] = v;
+  const z_t b2 = b * b;
   double q[2] = {0.0, 0.0};
-  acc_dot(q, zd(V.rs[t.row]), zd(v));
+  if constexpr (F == kFormTensor || F == kFormTensorExt) {
+    for_rows<F>(A, t, V.u,
+                [=](int64_t row) { return TqPair<T>{zt<T>(b * zd(V.uh[row]) + b2 * zd(V.v[row])), V.rs[row]}; },
+                [&](int64_t row, cx<T> y, TqPair<T> a) {
+                  V.uh[row] = y;
+                  const cx<T> v = zt<T>(zd(a.a) + zd(y));
+                  V.v[row] = v;
+                  acc_dot(q, zd(a.b), zd(v));
+                });
+  } else {
+    const cx<T> vt = zt<T>(b * zd(V.uh[t.row]) + b2 * zd(V.v[t.row]));
+    const cx<T> y = sell_row_form<F>(A, t.row, V.u);
+    V.uh[t.row] = y;
+    const cx<T> v = zt<T>(zd(vt) + zd(y));
+    V.v[t.row] = v;
+    acc_dot(q, zd(V.rs[t.row]), zd(v));
+  }
   store_partials<2>(q, part, t);
 }
 
@@ -306,74 +329,74 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     if (rc) return rc;
     *vecs[i] = b->as<cx<T>>();
   }
-  DevBuf* stb = ctx->buf(p + "st", sizeof(TqSt) * S.nseg, &rc);
-  if (rc) return rc;
-  DevBuf* part = ctx->buf(p + "part", sizeof(double) * 3 * S.nblk, &rc);
+  // state slots: start of a pair, after alpha, after the even half-step
+  DevBuf* stb = ctx->buf(p + "st", sizeof(TqSt) * 3 * S.nseg, &rc);
   if (rc) return rc;
   DevBuf* fnb = ctx->buf(p + "fn2", sizeof(double) * S.nseg, &rc);
   if (rc) return rc;
-  TqSt* st = stb->as<TqSt>();
-  double* pt = part->as<double>();
+  TqSt *st = stb->as<TqSt>(), *st_a = st + S.nseg, *st_e = st_a + S.nseg;   // st: what a pair starts from
   hipStream_t s = ctx->stream;
   const Seg& L = S.dev;
+  const Seg& P = prod_seg(A, L);   // the products' layout
 
   std::vector<double> fn2;
   HZ_TRY(seg_norm2_t<T>(ctx, S, f, &fn2));
   out->fnorm.resize(S.nseg);
   for (int i = 0; i < S.nseg; ++i) out->fnorm[i] = std::sqrt(fn2[i]);
   HZ_HIP(hipMemcpyAsync(fnb->p, fn2.data(), sizeof(double) * S.nseg, hipMemcpyHostToDevice, s));
-  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(TqSt) * S.nseg, s));
+  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(TqSt) * 3 * S.nseg, s));
   k_tq_set_thr<<<ceil_div(S.nseg, kBlock), kBlock, 0, s>>>(S.nseg, st, fnb->as<double>(), ctl.tol,
                                                             ctl.stall_halfsteps);
   HZ_HIP(hipGetLastError());
 
-  void* hp = nullptr;
-  HZ_TRY(ctx_pinned(ctx, sizeof(TqSt) * S.nseg, &hp));
-  TqSt* hst = static_cast<TqSt*>(hp);
-  const int grid = S.nblk;
+  StatePoll poll;
+  HZ_TRY(poll.init(ctx, sizeof(TqSt) * S.nseg));
+  const Seg& W = A.tz.on ? S.vec_runs : S.vec;   // vector layout
+  PartBuf pr, pa, pe, po;            // sums of the residual, alpha, even and odd steps
+  HZ_TRY(pr.init(ctx, S, P, 1, W.nblk, p + "part.r"));
+  HZ_TRY(pa.init(ctx, S, P, 2, W.nblk, p + "part.a"));
+  HZ_TRY(pe.init(ctx, S, W, 1, W.nblk, p + "part.e"));
+  HZ_TRY(po.init(ctx, S, W, 3, W.nblk, p + "part.o"));
   int64_t restarts = 0, pairs = 0;
-  int chunk = 4;
 
-  auto read_state = [&]() -> int {
-    HZ_HIP(hipMemcpyAsync(hst, st, sizeof(TqSt) * S.nseg, hipMemcpyDeviceToHost, s));
-    HZ_HIP(hipStreamSynchronize(s));
-    return HZ_OK;
+  auto report = [&]() -> int {
+    k_tq_report<<<S.nseg, kBlock, 0, s>>>(pa.part, st, poll.slot<TqSt>());
+    HZ_HIP(hipGetLastError());
+    return poll.posted_one();
   };
   auto enqueue_restart = [&](int all) -> int {
-    k_tq_mark<<<ceil_div(S.nseg, kBlock), kBlock, 0, s>>>(S.nseg, st, all);
-    if (A.val) k_tq_resid<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else if (A.st) k_tq_resid<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else k_tq_resid<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    k_tq_resid_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
-    if (A.val) k_tq_resid_prod<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else if (A.st) k_tq_resid_prod<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else k_tq_resid_prod<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    k_tq_alpha_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt, 1);
+    k_tq_settle<<<S.nseg, kBlock, 0, s>>>(pa.part, st, all);
+    HZ_BY_FORM(A, k_tq_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pr.raw));
+    HZ_TRY(pr.close<1>(s));
+    k_tq_resid_fin<<<S.nseg, kBlock, 0, s>>>(pr.part, st);
+    // u = r_0 is the first product's input
+    if (A.tz.on) HZ_BY_SCALING(A, k_tq_start<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, st, V));
+    HZ_BY_FORM(A, k_tq_resid_prod<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pa.raw));
+    HZ_TRY(pa.close<2>(s));
     HZ_HIP(hipGetLastError());
     ++restarts;
-    return HZ_OK;
+    HZ_TRY(report());
+    return poll.wait(poll.posted - 1);
   };
   auto enqueue_pair = [&]() -> int {
-    k_tq_even1<T><<<grid, kBlock, 0, s>>>(L, st, V, pt);
-    k_tq_qmr_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
-    if (A.val) k_tq_even2<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V);
-    else if (A.st) k_tq_even2<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V);
-    else k_tq_even2<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V);
-    k_tq_odd1<T><<<grid, kBlock, 0, s>>>(L, st, V, pt);
-    k_tq_odd_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt);
-    k_tq_odd2<T><<<grid, kBlock, 0, s>>>(L, st, V);
-    if (A.val) k_tq_odd3<T, kFormComplex><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else if (A.st) k_tq_odd3<T, kFormStencil><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    else k_tq_odd3<T, kFormSplit><<<grid, kBlock, 0, s>>>(L, A, st, V, pt);
-    k_tq_alpha_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, pt, 0);
+    HZ_BY_SCALING(A, k_tq_even1<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st, st_a, V, pe.raw));
+    HZ_TRY(pe.close<1>(s));
+    HZ_BY_FORM(A, k_tq_even2<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, st_e, V));
+    k_tq_odd1<T><<<W.nblk, kBlock, 0, s>>>(W, st_e, V, po.raw);
+    HZ_TRY(po.close<3>(s));
+    HZ_BY_SCALING(A, k_tq_odd2<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, st_e, st, V));
+    HZ_BY_FORM(A, k_tq_odd3<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pa.raw));
+    HZ_TRY(pa.close<2>(s));
     HZ_HIP(hipGetLastError());
     ++pairs;
     return HZ_OK;
   };
 
   HZ_TRY(enqueue_restart(1));
-  HZ_TRY(read_state());
+  const TqSt* hst = poll.state<TqSt>(poll.posted - 1);
+  int chunk = 2;
   for (;;) {
+    // everything queued has run: hst is the state
     bool all_done = true, any_brk = false, any_stalled = false;
     for (int i = 0; i < S.nseg; ++i) {
       all_done = all_done && hst[i].done;
@@ -385,7 +408,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     if (all_done && any_stalled) break;   // hand the iterate reached back to the refinement
     if (all_done) {
       HZ_TRY(enqueue_restart(1));   // confirm with the true residual
-      HZ_TRY(read_state());
+      hst = poll.state<TqSt>(poll.posted - 1);
       bool ok = true;
       for (int i = 0; i < S.nseg; ++i) ok = ok && hst[i].done;
       if (ok || mv + 2 >= ctl.max_matvec) break;
@@ -394,14 +417,30 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     if (mv + 2 > ctl.max_matvec) break;
     if (any_brk) {
       HZ_TRY(enqueue_restart(0));
-      HZ_TRY(read_state());
+      hst = poll.state<TqSt>(poll.posted - 1);
       continue;
     }
-    const int n_pair = int(std::min<int64_t>(chunk, (ctl.max_matvec - mv) / 2));
-    if (n_pair < 1) break;
-    for (int c = 0; c < n_pair; ++c) HZ_TRY(enqueue_pair());
-    HZ_TRY(read_state());
-    chunk = std::min(chunk * 2, 32);
+    int64_t left = (ctl.max_matvec - mv) / 2;   // pairs that may still be queued
+    const int first = poll.posted;
+    for (bool stop = false; !stop && left > 0;) {
+      const int n_pair = int(std::min<int64_t>(chunk, left));
+      for (int c = 0; c < n_pair; ++c) HZ_TRY(enqueue_pair());
+      left -= n_pair;
+      HZ_TRY(report());
+      if (poll.posted - 1 > first) {
+        HZ_TRY(poll.wait(poll.posted - 2));
+        const TqSt* h = poll.state<TqSt>(poll.posted - 2);
+        bool off = true, brk = false;
+        for (int i = 0; i < S.nseg; ++i) {
+          off = off && h[i].done;
+          brk = brk || (h[i].brk && !h[i].done);
+        }
+        stop = off || brk;
+      }
+      chunk = std::min(chunk * 2, 8);
+    }
+    HZ_TRY(poll.wait(poll.posted - 1));
+    hst = poll.state<TqSt>(poll.posted - 1);
   }
   out->iters.resize(S.nseg);
   out->matvecs.resize(S.nseg);

@@ -26,7 +26,7 @@ HZ_JACOBI, HZ_NONE = 0, 1
 
 METHODS = {"gmres": HZ_GMRES, "bicgstab": HZ_BICGSTAB, "schwarz": HZ_SCHWARZ, "bicgstabl": HZ_BICGSTABL, "tfqmr": HZ_TFQMR}
 PRECISIONS = {"fp64": HZ_FP64, "mixed": HZ_MIXED}
-SPMV_FORMS = {"solver": 0, "complex": 1, "split": 2, "stencil": 3}
+SPMV_FORMS = {"solver": 0, "complex": 1, "split": 2, "stencil": 3, "tensor": 4}
 ORDERS = {"given": 0, "rcm": 1}
 HZ_HEX8, HZ_TET4 = 0, 1
 
