@@ -86,6 +86,7 @@ int tensor_build(hz_ctx ctx, const std::vector<TensorGrid>& grids, const std::ve
                  const std::vector<int64_t>& nrows, const std::string& name, TensorDev* D);
 // The tables for mass coefficient m and the walls' corner terms (stream-ordered).
 int tensor_tables(hz_ctx ctx, TensorDev* D, const std::vector<TzCorner>& corners, double m);
+int tensor_axes(hz_ctx ctx, const TensorDev& D, DevBuf* tab);   // without frequency and walls
 int tensor_diag(hz_ctx ctx, const TensorDev& D, double k2, z_t* d, z_t* dinv);
 int tensor_eta(hz_ctx ctx, TensorDev* D, const double* eta_host, int64_t count);
 TzOp tensor_op(const TensorDev& D, double k2, bool scale);

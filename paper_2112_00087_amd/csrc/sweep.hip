@@ -23,6 +23,7 @@
 
 #include "ops.h"
 #include "solve.h"
+#include "sweep_tensor.h"
 
 namespace {
 
@@ -60,6 +61,7 @@ struct RowOp {
   const int* BSI = nullptr;
   const cx<R>* BSV = nullptr;
   int bx = 0, by = 0, bz = 0;      // box nodes per direction (0: no stencil form)
+  TwOp tw;                         // tensor form
 };
 
 struct SwCol {
@@ -1204,6 +1206,7 @@ struct Variant {
   // zl > 0: stencil-form product, blocks of pw x ph lines, nzc z chunks,
   // pairs broadcast by readlane (bc 0) or through LDS (bc 1)
   int zl = 0, pw = 0, ph = 0, nzc = 0, bc = 0;
+  int tz = 0;           // > 0: tensor-form product in tz z chunks
 };
 
 // LDS bytes the staged product needs for a column group of cg columns.
@@ -1305,9 +1308,45 @@ int launch_zl(hipStream_t stream, const Variant& v, int64_t nrows, int s, const 
   return HZ_OK;
 }
 
+// Tensor form: blocks of kTwWaves waves along x, one line group along y and
+// nzc runs of planes.
+template <typename T, int LS>
+int launch_tz(hipStream_t stream, int chunks, int64_t nrows, const RowOp<T>& A, const double* kc, const cx<T>* Z,
+              cx<T>* Y) {
+  const TwOp& W = A.tw;
+  const int64_t n = int64_t(W.nx) * W.ny * W.nz;
+  if (nrows > n) {
+    const int64_t tail = (nrows - n) << LS;
+    k_zero_tail<T><<<ceil_div(tail, kBlock), kBlock, 0, stream>>>(tail, Y + (n << LS));
+    HZ_HIP(hipGetLastError());
+  }
+  const int npx = ceil_div(W.nx, kTwI * (kWave >> LS) * kTwWaves), npy = ceil_div(W.ny, kTwJ);
+  const int zc = ceil_div(W.nz, std::min(chunks, W.nz));
+  const int64_t nblk = int64_t(npx) * npy * ceil_div(W.nz, zc);
+  if (nblk > INT32_MAX) return hz_fail(HZ_ERR_INVALID, "tensor product grid too large");
+  const dim3 grid = dim3(unsigned(nblk)), block = dim3(kTwWaves * kWave);
+  if (W.eta) k_spmm_tz<T, LS, true><<<grid, block, 0, stream>>>(W, npx, npy, zc, kc, Z, Y);
+  else k_spmm_tz<T, LS, false><<<grid, block, 0, stream>>>(W, npx, npy, zc, kc, Z, Y);
+  HZ_HIP(hipGetLastError());
+  return HZ_OK;
+}
+
 template <typename T, bool RESID>
 int launch_spmm(hipStream_t stream, const Variant& v, int64_t nrows, int s, const RowOp<T>& A, const double* st,
                 const cx<T>* Z, const cx<T>* F, cx<T>* Y, double* part, int* nblk_out) {
+  if (!RESID && v.tz > 0) {
+    if (!A.tw.tab) return hz_fail(HZ_ERR_INVALID, "no tensor form");
+    switch (s) {
+      case 1: return launch_tz<T, 0>(stream, v.tz, nrows, A, st, Z, Y);
+      case 2: return launch_tz<T, 1>(stream, v.tz, nrows, A, st, Z, Y);
+      case 4: return launch_tz<T, 2>(stream, v.tz, nrows, A, st, Z, Y);
+      case 8: return launch_tz<T, 3>(stream, v.tz, nrows, A, st, Z, Y);
+      case 16: return launch_tz<T, 4>(stream, v.tz, nrows, A, st, Z, Y);
+      case 32: return launch_tz<T, 5>(stream, v.tz, nrows, A, st, Z, Y);
+      case 64: return launch_tz<T, 6>(stream, v.tz, nrows, A, st, Z, Y);
+      default: return hz_fail(HZ_ERR_INVALID, "no tensor product for %d columns", s);
+    }
+  }
   if (!RESID && v.zl > 0) {
     if (!zl_fits<T>(v, s, A)) return hz_fail(HZ_ERR_INVALID, "bad stencil product variant");
     auto go = [&](auto Rc) -> int {
@@ -1365,15 +1404,19 @@ struct SweepData {
   // stencil form (boxes in their own numbering): (K, M) pairs and M_eta, 27 slots per row
   DevBuf KM64, KM32, SE64, SE32, BSI, BSV64, BSV32;
   int box[3] = {0, 0, 0};
+  DevBuf tztab;                     // tensor form: axis tables
+  TwOp tw;
+  int64_t ne = 0;
   int64_t n = 0, nnz = 0, nb = 0;   // mesh nodes, stored entries, boundary entries
 };
 
 // Algorithmic bytes of one multi-vector product over s columns in variant
-// v: the operator's values (K, M, with M_eta when present; column indices
+// v: the operator's values (none in the tensor form but the absorption field; else K, M, with M_eta when present; column indices
 // and row pointers for the row-wise forms, none for the stencil form, whose
 // zero slots are not counted), the boundary lists, one read of the input
 // and one write of the output.
 int64_t spmm_bytes(const Variant& v, const SweepData& D, int s, int tsize) {
+  if (v.tz > 0) return 2 * 2 * int64_t(tsize) * D.n * s + (D.eta ? 8 * D.ne : 0);
   const int64_t n = D.n, vals = (D.eta ? 3 : 2) * int64_t(tsize) * D.nnz;
   // row-wise: row pointers, columns and values of the boundary lists;
   // stencil form: the per-row slot index and the listed values
@@ -1468,6 +1511,21 @@ int build_sweep_data(hz_ctx ctx, SweepData* D) {
       }
       bnd[row].push_back({a.col[pos], z_t{re, im}});
     }
+  }
+  if (ctx->tz) {
+    HZ_TRY(tensor_axes(ctx, *ctx->tz, &D->tztab));
+    TwOp& W = D->tw;
+    W.tab = D->tztab.as<TzAxis>();
+    W.eta = ctx->tz->have_eta ? ctx->tz->eta.as<double>() : nullptr;
+    W.nx = ctx->tz->segs[0].nx;
+    W.ny = ctx->tz->segs[0].ny;
+    W.nz = ctx->tz->segs[0].nz;
+    for (int w = 0; w < 6; ++w)
+      if (ctx->tgrid.tag[w] >= 0) {
+        const std::complex<double> b = ctx->beta[ctx->tgrid.tag[w]];
+        W.beta[w] = z_t{b.real(), b.imag()};
+      }
+    D->ne = a.ne;
   }
   // the operator in the internal order
   const int64_t nnz = int64_t(a.col.size());
@@ -1653,6 +1711,7 @@ template <> RowOp<double> row_op<double>(const SweepData& D) {
                      D.eta ? D.E64.as<double>() : nullptr, D.bptr.as<int>(), D.bcol.as<int>(), D.B64.as<z_t>()};
   add_halo(D, &A);
   add_stencil(D, D.KM64, D.SE64, &A);
+  A.tw = D.tw;
   return A;
 }
 template <> RowOp<float> row_op<float>(const SweepData& D) {
@@ -1660,6 +1719,7 @@ template <> RowOp<float> row_op<float>(const SweepData& D) {
                     D.eta ? D.E32.as<float>() : nullptr, D.bptr.as<int>(), D.bcol.as<int>(), D.B32.as<c_t>()};
   add_halo(D, &A);
   add_stencil(D, D.KM32, D.SE32, &A);
+  A.tw = D.tw;
   return A;
 }
 
@@ -1677,13 +1737,19 @@ inline int log2p1(int v) {
 }
 // A stencil-form variant has eight digits: 1, the broadcast (0 readlane,
 // 1 LDS), pw, ph, then four of nzc.
+// A tensor-form variant: 20000000 + its z chunks.
 inline int variant_code(const Variant& v) {
+  if (v.tz > 0) return 20000000 + v.tz;
   if (v.zl > 0) return 10000000 + v.bc * 1000000 + v.pw * 100000 + v.ph * 10000 + v.nzc;
   return ((log2p1(v.lds) * 10 + v.xcd) * 10 + v.cpl) * 1000 + v.bs;
 }
 inline Variant variant_decode(int code) {
   auto un = [](int d) { return d == 0 ? 0 : 1 << (d - 1); };
   Variant v;
+  if (code >= 20000000) {
+    v.tz = code - 20000000;
+    return v;
+  }
   if (code >= 10000000) {
     v.zl = 1;
     v.bc = code / 1000000 % 10;
@@ -1701,9 +1767,10 @@ inline Variant variant_decode(int code) {
   v.lds = un(code % 10);
   return v;
 }
-std::string tune_key(int64_t n, int64_t nnz, int s, int bytes) {
+// (contexts with a tensor form have their own entries)
+std::string tune_key(int64_t n, int64_t nnz, int s, int bytes, bool tensor) {
   std::ostringstream o;
-  o << "spmm5 n=" << n << " nnz=" << nnz << " s=" << s << " t=" << bytes;
+  o << (tensor ? "spmm6 n=" : "spmm5 n=") << n << " nnz=" << nnz << " s=" << s << " t=" << bytes;
   return o.str();
 }
 
@@ -1729,11 +1796,13 @@ void save_tune_entry(const std::string& key, int code) {
 template <typename T>
 int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T>& A, const double* st,
              const cx<T>* Z, cx<T>* Y, Variant* best) {
-  const std::string key = tune_key(ctx->h.n, int64_t(ctx->h.col.size()), s, int(sizeof(T)));
+  const std::string key = tune_key(ctx->h.n, int64_t(ctx->h.col.size()), s, int(sizeof(T)),
+                                   A.tw.tab != nullptr);
   if (const char* fv = std::getenv("HZ_SPMM_VARIANT")) {
     // one given variant (tests and measurements), if it fits this width
     const Variant v = variant_decode(std::atoi(fv));
-    const bool fits = v.zl > 0    ? zl_fits<T>(v, s, A)
+    const bool fits = v.tz > 0    ? A.tw.tab != nullptr
+                      : v.zl > 0  ? zl_fits<T>(v, s, A)
                       : v.lds > 0 ? (A.hblocks > 0 && s % v.lds == 0 && lds_bytes(A, v.lds) <= lds_limit())
                                   : (v.cpl <= s && v.bs >= s / v.cpl);
     if (fits) {
@@ -1748,8 +1817,20 @@ int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T
     *best = variant_decode(it->second);
     return HZ_OK;
   }
+  // The tensor form is the only candidate kind where there is one: against the
+  // best of the others it took 92 : 163 us (80x48x40, 64 columns, complex128),
+  // 24 : 46 (57x43x31, 32), 13 : 126 (80x48x40, 4), 8.4 : 10.3 (20x12x10, 1) and
+  // in complex64 69 : 85 (80x48x40, 64); few planes per wave where the box is
+  // small, whole runs where it fills the chip.
   std::vector<Variant> cands;
-  if (!(force && force[0] == '1'))
+  const bool tensor = A.tw.tab && !force;
+  if (tensor)
+    for (int nzc : {1, 2, 4, 8, 16, 32, 64}) {
+      Variant v;
+      v.tz = nzc;
+      if (nzc < 2 * A.tw.nz) cands.push_back(v);
+    }
+  if (!tensor && !(force && force[0] == '1'))
     for (int xcd : {0, 1})
       for (int cpl : {1, 2})
         for (int bs : {128, 256, 512}) {
@@ -1761,7 +1842,7 @@ int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T
           v.xcd = xcd;
           cands.push_back(v);
         }
-  if (!(force && force[0] == '0'))
+  if (!tensor && !(force && force[0] == '0'))
     for (int cg : {1, 2, 4, 8, 16})
       if (A.hblocks > 0 && cg <= s && lds_bytes(A, cg) <= lds_limit()) {
         Variant v;
@@ -1769,7 +1850,7 @@ int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T
         v.lds = cg;
         cands.push_back(v);
       }
-  if (!(force && force[0] == '1'))
+  if (!tensor && !(force && force[0] == '1'))
     for (int bc : {0, 1})
       for (const ZlShape& h : kZlShapes)
         for (int nzc : {2, 4, 8, 16}) {

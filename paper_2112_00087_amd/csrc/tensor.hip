@@ -61,6 +61,15 @@ __global__ void k_tz_tables(TzSeg S, const double* __restrict__ c, TzCorner w, d
   }
 }
 
+// Axis rows without frequency and walls (the sweep adds them per column).
+__global__ void k_tz_axes(TzSeg S, const double* __restrict__ c, TzAxis* __restrict__ tab) {
+  const int t = blockIdx.x * kBlock + threadIdx.x;
+  const z_t z = {0.0, 0.0};
+  if (t < S.nx) tab[t] = axis_row(c, S.nx, t, z, z);
+  else if (t < S.nx + S.ny) tab[t] = axis_row(c + S.nx, S.ny, t - S.nx, z, z);
+  else if (t < S.nx + S.ny + S.nz) tab[t] = axis_row(c + S.nx + S.ny, S.nz, t - S.nx - S.ny, z, z);
+}
+
 // diag(A) and its reciprocal of one box's rows (1 on padding rows)
 __global__ void k_tz_diag(TzSeg S, const TzAxis* __restrict__ tab, const TzLine* __restrict__ lt,
                           const double* __restrict__ ed, double k2, z_t* __restrict__ d, z_t* __restrict__ dinv) {
@@ -247,6 +256,15 @@ int tensor_tables(hz_ctx ctx, TensorDev* D, const std::vector<TzCorner>& corners
     k_tz_tables<<<ceil_div(count, kBlock), kBlock, 0, ctx->stream>>>(S, D->coord.as<double>() + D->cat[s], corners[s], m,
                                                                     D->tab.as<TzAxis>(), D->dx.as<TzLine>(), D->lt.as<TzLine>());
   }
+  HZ_HIP(hipGetLastError());
+  return HZ_OK;
+}
+
+int tensor_axes(hz_ctx ctx, const TensorDev& D, DevBuf* tab) {
+  const TzSeg& S = D.segs[0];
+  const int count = S.nx + S.ny + S.nz;
+  HZ_TRY(tab->ensure(sizeof(TzAxis) * count));
+  k_tz_axes<<<ceil_div(count, kBlock), kBlock, 0, ctx->stream>>>(S, D.coord.as<double>(), tab->as<TzAxis>());
   HZ_HIP(hipGetLastError());
   return HZ_OK;
 }

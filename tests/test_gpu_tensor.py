@@ -269,3 +269,42 @@ def test_more_blocks_than_a_kernel_adds(P, monkeypatch, method, kw):
         assert info["matvecs"] >= 32 and np.isfinite(info["relres_true"])
         m.close()
     assert float((x["1"] - x["0"]).norm() / x["0"].norm()) <= 1e-10
+
+
+# columns around the lane groups (64 / s groups of 2 nodes along x, 4 waves a block: 8 nodes a
+# block at 64 columns, 512 at one), odd sizes against the 2 x 2 patch, single cells
+@pytest.mark.parametrize("eta", [False, True])
+@pytest.mark.parametrize("size,nf", [((1, 1, 1), 64), ((8, 3, 4), 64), ((7, 4, 3), 33), ((16, 2, 5), 32),
+                                     ((15, 6, 2), 13), ((33, 2, 2), 8), ((31, 3, 3), 3), ((20, 5, 4), 2),
+                                     ((65, 2, 2), 1)])
+def test_sweep_product(P, monkeypatch, size, nf, eta):
+    """The multi-vector product in the tensor form, in one run of planes, in
+    runs of two and as tuned.  complex64 vectors hold float32 inputs exactly,
+    so their outputs carry one rounding (2^-24) beyond the FP64 bound."""
+    say("tensor sweep product", size, nf, "eta" if eta else "")
+    rng = np.random.default_rng(sum(size) + nf)
+    mesh = graded_box(*size, seed=sum(size))
+    beta = _beta(rng)
+    e = rng.uniform(0, 0.02, mesh["n_elems"]) if eta else None
+    S = H.System(mesh, beta, e, gls=not eta)
+    m = P.Helmholtz(mesh, beta, eta=e, gls=not eta)
+    freqs = np.linspace(60.0, 240.0, nf)
+    x = (rng.standard_normal((S.n, nf)) + 1j * rng.standard_normal((S.n, nf))).astype(np.complex64)
+    X = torch.as_tensor(x.astype(np.complex128), device="cuda")
+    for chunks in (1, max(1, (size[2] + 1) // 2), None):
+        if chunks:
+            monkeypatch.setenv("HZ_SPMM_VARIANT", str(20000000 + chunks))
+        else:
+            monkeypatch.delenv("HZ_SPMM_VARIANT")
+        for precision in ("fp64", "mixed"):
+            Y, code = m.apply_sweep(freqs, X, precision=precision)
+            assert code == 20000000 + chunks if chunks else code > 20000000
+            for c in sorted({0, nf // 2, nf - 1}):
+                k = W.wavenumber(freqs[c])
+                A, B = _reference(mesh, beta, e, k, S.mass_coefficient(k))
+                want = A @ x[:, c].astype(np.complex128)
+                bound = 7e-15 * (B @ np.abs(x[:, c]))
+                if precision == "mixed":
+                    bound = bound + 2.0**-23 * np.abs(want).astype(np.float64)
+                assert _within(Y[:, c].cpu().numpy(), want, bound) <= 1.0
+    m.close()
