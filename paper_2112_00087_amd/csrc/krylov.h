@@ -514,6 +514,67 @@ __device__ __forceinline__ double seg_sum(const Seg& L, const double* partial, i
   return block_sum_strided(partial + int64_t(b0) * NQ + q, b1 - b0, NQ, lds);
 }
 
+// conj(a) b, each part with one rounding of its second product
+__device__ __forceinline__ z_t conj_mul(z_t a, z_t b) {
+  return {fma(a.re, b.re, a.im * b.im), fma(a.re, b.im, -(a.im * b.re))};
+}
+// Minimal-residual step of BiCGStab(l): Cholesky solve of G gamma = c (G
+// Hermitian, LL x LL) from the sums tot (c, then the rows of G's upper
+// triangle), truncated at the first pivot below piv times its diagonal entry
+// (G is exact for the stored vectors, so piv guards the FP64 Cholesky only).
+// Returns the number of pivots used; gamma beyond it is 0.  Every loop is unrolled,
+// so the matrix sits in registers (as a scratch array this step took 23 us
+// at LL = 4, five times the kernel around it).
+template <int LL>
+__device__ __forceinline__ int gram_solve(const double* tot, double piv, z_t (&g)[LL]) {
+  z_t c[LL], G[LL][LL];      // G: lower triangle
+  int k = 0;
+#pragma unroll
+  for (int i = 0; i < LL; ++i, k += 2) c[i] = z_t{tot[k], tot[k + 1]};
+#pragma unroll
+  for (int i = 0; i < LL; ++i)
+#pragma unroll
+    for (int jj = i; jj < LL; ++jj, k += 2) G[jj][i] = z_t{tot[k], -tot[k + 1]};
+  // G = C C^H, C lower triangular (diagonal real)
+  int m = LL;
+#pragma unroll
+  for (int jj = 0; jj < LL; ++jj) {
+    double d = G[jj][jj].re;
+#pragma unroll
+    for (int p = 0; p < jj; ++p) d -= fma(G[jj][p].re, G[jj][p].re, G[jj][p].im * G[jj][p].im);
+    if (m == LL && (!(d > piv * G[jj][jj].re) || !isfinite(d))) m = jj;
+    const double cd = m == LL ? sqrt(d) : 1.0, ci = 1.0 / cd;
+    G[jj][jj] = z_t{cd, 0.0};
+#pragma unroll
+    for (int i = jj + 1; i < LL; ++i) {
+      z_t v = G[i][jj];
+#pragma unroll
+      for (int p = 0; p < jj; ++p) v = v - conj_mul(G[jj][p], G[i][p]);
+      G[i][jj] = ci * v;
+    }
+  }
+  z_t y[LL];
+#pragma unroll
+  for (int i = 0; i < LL; ++i) {           // C y = c
+    z_t v = c[i];
+#pragma unroll
+    for (int p = 0; p < i; ++p) {
+      const z_t a = G[i][p];
+      v = v - z_t{fma(a.re, y[p].re, -(a.im * y[p].im)), fma(a.im, y[p].re, a.re * y[p].im)};
+    }
+    y[i] = i < m ? (1.0 / G[i][i].re) * v : z_t{0.0, 0.0};
+  }
+#pragma unroll
+  for (int i = LL - 1; i >= 0; --i) {      // C^H g = y
+    z_t v = y[i];
+#pragma unroll
+    for (int p = i + 1; p < LL; ++p)
+      if (p < m) v = v - conj_mul(G[p][i], g[p]);
+    g[i] = i < m ? (1.0 / G[i][i].re) * v : z_t{0.0, 0.0};
+  }
+  return m;
+}
+
 // Host-side description of a segmented system on the device.
 struct SegHost {
   int nseg = 0, nblk = 0;

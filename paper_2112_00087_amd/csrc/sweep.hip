@@ -2519,8 +2519,32 @@ __global__ void __launch_bounds__(kBlock) k_sl_dots(int64_t total, int s, const 
   }
 }
 
-__device__ __forceinline__ double sl_sum(int G_, int s, int nq, const double* part, int c, int i, double* lds) {
-  return block_sum_strided(part + int64_t(i) * s + c, G_, nq * s, lds);
+// All NQ sums of column c over the G_ blocks' partials, by one block in one
+// pass (the order of block_sum_strided for each), valid in every thread.  One
+// sum after the other cost a reload latency and two barriers each: 44 us for
+// the 28 sums and the solve of k_sl_mr<4>, 15 us now.
+template <int NQ>
+__device__ __forceinline__ void sl_totals(int G_, int s, const double* __restrict__ part, int c, double (&o)[NQ]) {
+  __shared__ double lds[NQ][kBlock / kWave];
+  double acc[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) acc[i] = 0.0;
+  for (int b = threadIdx.x; b < G_; b += kBlock) {
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) acc[i] += part[(int64_t(b) * NQ + i) * s + c];
+  }
+  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    const double t = wave_sum(acc[i]);
+    if (lane == 0) lds[i][w] = t;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    o[i] = 0.0;
+    for (int k = 0; k < kBlock / kWave; ++k) o[i] += lds[i][k];
+  }
 }
 
 // u_i = r_i - beta u_i (i <= j); Z = D^-1 u_j
@@ -2541,13 +2565,13 @@ __global__ void k_sl_u(int64_t total, int s, const SlCol* __restrict__ st, SlVec
 
 // alpha = rho0 / rt^H u_{j+1}
 __global__ void k_sl_alpha(int G_, int s, SlCol* st, const double* __restrict__ part) {
-  __shared__ double lds[kBlock / kWave];
   const int c = blockIdx.x;
   const int off = sl_off(st[c]);
   __syncthreads();
   if (off) return;
-  const double re = sl_sum(G_, s, 2, part, c, 0, lds);
-  const double im = sl_sum(G_, s, 2, part, c, 1, lds);
+  double o[2];
+  sl_totals<2>(G_, s, part, c, o);
+  const double re = o[0], im = o[1];
   if (threadIdx.x != 0) return;
   SlCol& S = st[c];
   const z_t sg = {re, im};
@@ -2574,13 +2598,13 @@ __global__ void k_sl_r(int64_t total, int s, const SlCol* __restrict__ st, SlVec
 
 // rho1 = rt^H r_{j+1}; beta = alpha rho1 / rho0; rho0 = rho1
 __global__ void k_sl_beta(int G_, int s, SlCol* st, const double* __restrict__ part) {
-  __shared__ double lds[kBlock / kWave];
   const int c = blockIdx.x;
   const int off = sl_off(st[c]);
   __syncthreads();
   if (off) return;
-  const double re = sl_sum(G_, s, 2, part, c, 0, lds);
-  const double im = sl_sum(G_, s, 2, part, c, 1, lds);
+  double o[2];
+  sl_totals<2>(G_, s, part, c, o);
+  const double re = o[0], im = o[1];
   if (threadIdx.x != 0) return;
   SlCol& S = st[c];
   const z_t rho1 = {re, im};
@@ -2634,66 +2658,24 @@ __global__ void __launch_bounds__(kBlock) k_sl_gram(int64_t total, int s, const 
 // Cholesky solve of G gamma = c per column (truncated at the first pivot
 // below piv times its diagonal entry)
 template <int LL>
-__global__ void k_sl_mr(int G_, int s, SlCol* st, const double* __restrict__ part, double piv) {
+__global__ void __launch_bounds__(kBlock) k_sl_mr(int G_, int s, SlCol* st, const double* __restrict__ part, double piv) {
   constexpr int NQ = sl_nq<LL>();
-  __shared__ double lds[kBlock / kWave];
-  __shared__ double tot[NQ];
   const int c = blockIdx.x;
-  const int off = sl_off(st[c]);
-  __syncthreads();
-  if (off) return;
-  for (int i = 0; i < NQ; ++i) {
-    const double t = sl_sum(G_, s, NQ, part, c, i, lds);
-    if (threadIdx.x == 0) tot[i] = t;
-  }
+  if (sl_off(st[c])) return;
+  double tot[NQ];
+  sl_totals<NQ>(G_, s, part, c, tot);
   if (threadIdx.x != 0) return;
   SlCol& S = st[c];
-  z_t cv[LL], G[LL][LL];
-  int k = 0;
-  for (int i = 0; i < LL; ++i, k += 2) cv[i] = z_t{tot[k], tot[k + 1]};
-  for (int i = 0; i < LL; ++i)
-    for (int jj = i; jj < LL; ++jj, k += 2) {
-      G[i][jj] = z_t{tot[k], tot[k + 1]};
-      G[jj][i] = conj(G[i][jj]);
-    }
-  int m = LL;
-  for (int jj = 0; jj < LL; ++jj) {
-    double d = G[jj][jj].re;
-    for (int p = 0; p < jj; ++p) d -= norm2(G[jj][p]);
-    if (!(d > piv * G[jj][jj].re) || !isfinite(d)) {
-      m = jj;
-      break;
-    }
-    const double cd = sqrt(d);
-    G[jj][jj] = z_t{cd, 0.0};
-    for (int i = jj + 1; i < LL; ++i) {
-      z_t v = G[i][jj];
-      for (int p = 0; p < jj; ++p) v = v - G[i][p] * conj(G[jj][p]);
-      G[i][jj] = (1.0 / cd) * v;
-    }
-  }
   z_t g[LL];
-  for (int i = 0; i < LL; ++i) g[i] = z_t{0.0, 0.0};
-  if (m == 0) {
+  const int m = gram_solve<LL>(tot, piv, g);
+  bool bad = m == 0;
+#pragma unroll
+  for (int i = 0; i < LL; ++i) bad = bad || !isfinite(g[i].re) || !isfinite(g[i].im);
+  if (bad) {
     S.idone = 1;
     return;
   }
-  z_t yv[LL];
-  for (int i = 0; i < m; ++i) {
-    z_t v = cv[i];
-    for (int p = 0; p < i; ++p) v = v - G[i][p] * yv[p];
-    yv[i] = (1.0 / G[i][i].re) * v;
-  }
-  for (int i = m - 1; i >= 0; --i) {
-    z_t v = yv[i];
-    for (int p = i + 1; p < m; ++p) v = v - conj(G[p][i]) * g[p];
-    g[i] = (1.0 / G[i][i].re) * v;
-  }
-  for (int i = 0; i < LL; ++i)
-    if (!isfinite(g[i].re) || !isfinite(g[i].im)) {
-      S.idone = 1;
-      return;
-    }
+#pragma unroll
   for (int i = 0; i < LL; ++i) S.gam[i + 1] = g[i];
   S.omega = g[LL - 1];
   S.trunc = m < LL;
@@ -2724,14 +2706,13 @@ __global__ void k_sl_update(int64_t total, int s, const SlCol* __restrict__ st, 
 
 // after the update: rho1 = rt^H r_0, ||r_0||^2; next cycle's beta, or done
 __global__ void k_sl_cycle(int G_, int s, SlCol* st, const double* __restrict__ part) {
-  __shared__ double lds[kBlock / kWave];
   const int c = blockIdx.x;
   const int off = sl_off(st[c]);
   __syncthreads();
   if (off) return;
-  const double re = sl_sum(G_, s, 3, part, c, 0, lds);
-  const double im = sl_sum(G_, s, 3, part, c, 1, lds);
-  const double rr = sl_sum(G_, s, 3, part, c, 2, lds);
+  double o[3];
+  sl_totals<3>(G_, s, part, c, o);
+  const double re = o[0], im = o[1], rr = o[2];
   if (threadIdx.x != 0) return;
   SlCol& S = st[c];
   S.iters += 1;
@@ -3232,13 +3213,13 @@ __global__ void __launch_bounds__(kBlock) k_ts_v0(int64_t total, int s, const Ts
 }
 
 __global__ void k_ts_start_fin(int G_, int s, TsCol* st, const double* __restrict__ part) {
-  __shared__ double lds[kBlock / kWave];
   const int c = blockIdx.x;
   const int go = st[c].restart_now;
   __syncthreads();
   if (!go) return;
-  const double re = sl_sum(G_, s, 2, part, c, 0, lds);
-  const double im = sl_sum(G_, s, 2, part, c, 1, lds);
+  double o[2];
+  sl_totals<2>(G_, s, part, c, o);
+  const double re = o[0], im = o[1];
   if (threadIdx.x != 0) return;
   TsCol& S = st[c];
   S.restart_now = 0;
@@ -3319,7 +3300,6 @@ __global__ void __launch_bounds__(kBlock) k_ts_even1(int64_t total, int s, const
 }
 
 __global__ void k_ts_qmr_fin(int G_, int s, TsCol* st, const double* __restrict__ part) {
-  __shared__ double lds[kBlock / kWave];
   const int c = blockIdx.x;
   const int off = ts_off(st[c]), idn = st[c].idone;
   __syncthreads();
@@ -3327,7 +3307,9 @@ __global__ void k_ts_qmr_fin(int G_, int s, TsCol* st, const double* __restrict_
     if (threadIdx.x == 0 && idn) st[c].last = 0;
     return;
   }
-  const double ww = sl_sum(G_, s, 1, part, c, 0, lds);
+  double o[1];
+  sl_totals<1>(G_, s, part, c, o);
+  const double ww = o[0];
   if (threadIdx.x != 0) return;
   TsCol& S = st[c];
   S.ge = (S.theta * S.theta) * cdiv(S.eta, S.alpha);   // the even half-step's d = u + ge d
@@ -3376,7 +3358,6 @@ __global__ void __launch_bounds__(kBlock) k_ts_odd1(int64_t total, int s, const 
 }
 
 __global__ void k_ts_odd_fin(int G_, int s, TsCol* st, const double* __restrict__ part) {
-  __shared__ double lds[kBlock / kWave];
   const int c = blockIdx.x;
   const int off = ts_off(st[c]), idn = st[c].idone;
   __syncthreads();
@@ -3387,9 +3368,9 @@ __global__ void k_ts_odd_fin(int G_, int s, TsCol* st, const double* __restrict_
     }
     return;
   }
-  const double ww = sl_sum(G_, s, 3, part, c, 0, lds);
-  const double re = sl_sum(G_, s, 3, part, c, 1, lds);
-  const double im = sl_sum(G_, s, 3, part, c, 2, lds);
+  double o[3];
+  sl_totals<3>(G_, s, part, c, o);
+  const double ww = o[0], re = o[1], im = o[2];
   if (threadIdx.x != 0) return;
   TsCol& S = st[c];
   ts_qmr(S, ww);
@@ -3454,7 +3435,6 @@ __global__ void __launch_bounds__(kBlock) k_ts_odd3(int64_t total, int s, const 
 }
 
 __global__ void k_ts_alpha_fin(int G_, int s, TsCol* st, const double* __restrict__ part) {
-  __shared__ double lds[kBlock / kWave];
   const int c = blockIdx.x;
   const int off = ts_off(st[c]), idn = st[c].idone;
   __syncthreads();
@@ -3462,8 +3442,9 @@ __global__ void k_ts_alpha_fin(int G_, int s, TsCol* st, const double* __restric
     if (threadIdx.x == 0 && idn) st[c].last = 0;
     return;
   }
-  const double re = sl_sum(G_, s, 2, part, c, 0, lds);
-  const double im = sl_sum(G_, s, 2, part, c, 1, lds);
+  double o[2];
+  sl_totals<2>(G_, s, part, c, o);
+  const double re = o[0], im = o[1];
   if (threadIdx.x != 0) return;
   TsCol& S = st[c];
   const z_t sg = {re, im};
