@@ -29,7 +29,7 @@ constexpr int NV = 8;    // basis vectors per multi-dot chunk
 struct GmSt {
   double beta, thr2, est, inv_next;
   int k, done, cyc, nan;
-  int iters, pad0;
+  int iters, off;      // off: cyc as of the step before (k_few_prod)
 };
 
 struct GmArr {         // per-segment small arrays (FP64)
@@ -75,7 +75,7 @@ __global__ void k_beta_fin(Seg L, GmSt* st, GmArr G, const double* part) {
     S.k = 0;
     S.nan = !isfinite(rr);
     S.done = (rr <= S.thr2) || S.nan;
-    S.cyc = S.done;
+    S.cyc = S.off = S.done;
     S.inv_next = b > 0.0 ? 1.0 / b : 0.0;
     G.vs[int64_t(s) * (G.m + 1)] = S.inv_next;
     z_t* g = G.g + int64_t(s) * (G.m + 1);
@@ -404,38 +404,34 @@ __global__ void __launch_bounds__(kBlock) k_axpy(Seg L, TzOp Z, const GmSt* st, 
 // residual estimate |g_{j+1}|.
 // The column and the previous rotations are staged in LDS by the whole
 // block, so the sequential rotation loop of thread 0 reads no global memory.
-__global__ void __launch_bounds__(kFinBlock) k_givens_fin(Seg L, GmSt* st, GmArr G, const double* part, int j) {
-  int s = blockIdx.x;
-  const int cyc = st[s].cyc;
+struct GivensLds {
+  z_t h[kGmMaxM + 1], sn[kGmMaxM];
+  double cs[kGmMaxM];
+};
+__device__ __forceinline__ void givens_stage(const GmArr& G, int s, int j, GivensLds& W) {
+  const z_t* H = G.H + int64_t(s) * (G.m + 1) * G.m + int64_t(j) * (G.m + 1);
+  for (int i = threadIdx.x; i <= j; i += int(blockDim.x)) {
+    W.h[i] = H[i];
+    if (i < j) {
+      W.cs[i] = G.cs[int64_t(s) * G.m + i];
+      W.sn[i] = G.sn[int64_t(s) * G.m + i];
+    }
+  }
+}
+// by one thread, after a barrier; ww = ||w||^2 of the new vector
+__device__ __forceinline__ void givens_step(GmSt& S, const GmArr& G, int s, int j, double ww, GivensLds& W) {
   const int m = G.m;
   z_t* H = G.H + int64_t(s) * (m + 1) * m + int64_t(j) * (m + 1);
-  double* cs = G.cs + int64_t(s) * m;
-  z_t* sn = G.sn + int64_t(s) * m;
   z_t* g = G.g + int64_t(s) * (m + 1);
-  __shared__ z_t hS[kGmMaxM + 1], snS[kGmMaxM];
-  __shared__ double csS[kGmMaxM];
-  if (!cyc)
-    for (int i = threadIdx.x; i <= j; i += kFinBlock) {
-      hS[i] = H[i];
-      if (i < j) {
-        csS[i] = cs[i];
-        snS[i] = sn[i];
-      }
-    }
-  double o[1];
-  seg_sums<1>(L, part, s, o);   // its barriers also order the staging above
-  if (cyc || threadIdx.x != 0) return;
-  const double ww = o[0];
-  GmSt& S = st[s];
   double hn = sqrt(ww);
-  hS[j + 1] = z_t{hn, 0.0};
+  W.h[j + 1] = z_t{hn, 0.0};
   for (int i = 0; i < j; ++i) {
-    z_t a = hS[i], b = hS[i + 1];
-    hS[i] = csS[i] * a + snS[i] * b;
-    hS[i + 1] = (-1.0 * (conj(snS[i]) * a)) + csS[i] * b;
+    z_t a = W.h[i], b = W.h[i + 1];
+    W.h[i] = W.cs[i] * a + W.sn[i] * b;
+    W.h[i + 1] = (-1.0 * (conj(W.sn[i]) * a)) + W.cs[i] * b;
   }
-  for (int i = 0; i < j; ++i) H[i] = hS[i];
-  z_t a = hS[j], b = hS[j + 1];
+  for (int i = 0; i < j; ++i) H[i] = W.h[i];
+  z_t a = W.h[j], b = W.h[j + 1];
   double rho = sqrt(norm2(a) + norm2(b));
   double c;
   z_t sv;
@@ -450,8 +446,8 @@ __global__ void __launch_bounds__(kFinBlock) k_givens_fin(Seg L, GmSt* st, GmArr
     c = aa / rho;
     sv = (1.0 / (aa * rho)) * (a * conj(b));
   }
-  cs[j] = c;
-  sn[j] = sv;
+  G.cs[int64_t(s) * m + j] = c;
+  G.sn[int64_t(s) * m + j] = sv;
   H[j] = c * a + sv * b;
   H[j + 1] = z_t{0.0, 0.0};
   z_t gj = g[j];
@@ -466,22 +462,57 @@ __global__ void __launch_bounds__(kFinBlock) k_givens_fin(Seg L, GmSt* st, GmArr
   S.inv_next = hn > 0.0 ? 1.0 / hn : 0.0;
   G.vs[int64_t(s) * (m + 1) + j + 1] = S.inv_next;
 }
+__global__ void __launch_bounds__(kFinBlock) k_givens_fin(Seg L, GmSt* st, GmArr G, const double* part, int j) {
+  __shared__ GivensLds W;
+  const int s = blockIdx.x;
+  const int cyc = st[s].cyc;
+  if (!cyc) givens_stage(G, s, j, W);
+  double o[1];
+  seg_sums<1>(L, part, s, o);   // its barriers also order the staging above
+  if (cyc || threadIdx.x != 0) return;
+  givens_step(st[s], G, s, j, o[0], W);
+}
 
-// y = H(0:k,0:k)^-1 g(0:k)
-__global__ void k_solve_fin(const GmSt* st, GmArr G, int nseg) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nseg) return;
-  const GmSt& S = st[s];
-  if (S.done || S.nan) return;
-  const int m = G.m, k = S.k;
+// y = H(0:k,0:k)^-1 g(0:k), one wave per segment: H's triangle staged in LDS
+// (up to 56 columns; beyond, read as it is used), the terms H_il y_l of a row
+// in parallel over l, then added in order by lane 0.  One thread forming and
+// adding them took 47 us at k = 30, a chain of dependent global loads.
+constexpr int kSolveStaged = 56;
+struct SolveLds {
+  z_t h[kSolveStaged * (kSolveStaged + 1) / 2], t[kGmMaxM], y[kGmMaxM], g[kGmMaxM];
+};
+__device__ __forceinline__ void solve_y(const GmSt& S, const GmArr& G, int s, SolveLds& W) {
+  const int m = G.m, k = S.k, lane = threadIdx.x;
   const z_t* H = G.H + int64_t(s) * (m + 1) * m;
-  const z_t* g = G.g + int64_t(s) * (m + 1);
-  z_t* y = G.y + int64_t(s) * m;
-  for (int i = k - 1; i >= 0; --i) {
-    z_t acc = g[i];
-    for (int l = i + 1; l < k; ++l) acc = acc - H[int64_t(l) * (m + 1) + i] * y[l];
-    y[i] = cdiv(acc, H[int64_t(i) * (m + 1) + i]);
+  const bool staged = k <= kSolveStaged;
+  for (int i = lane; i < k; i += kWave) W.g[i] = G.g[int64_t(s) * (m + 1) + i];
+  if (staged) {
+    for (int l = 0; l < k; ++l)      // column l: rows 0..l
+      if (lane <= l) W.h[l * (l + 1) / 2 + lane] = H[int64_t(l) * (m + 1) + lane];
   }
+  auto at = [&](int i, int l) { return staged ? W.h[l * (l + 1) / 2 + i] : H[int64_t(l) * (m + 1) + i]; };
+  __syncthreads();
+  for (int i = k - 1; i >= 0; --i) {
+    for (int l = i + 1 + lane; l < k; l += kWave) {
+      const z_t h = at(i, l), v = W.y[l];
+      W.t[l] = z_t{fma(h.re, v.re, -(h.im * v.im)), fma(h.im, v.re, h.re * v.im)};
+    }
+    __syncthreads();
+    if (lane == 0) {
+      z_t acc = W.g[i];
+#pragma unroll 4
+      for (int l = i + 1; l < k; ++l) acc = acc - W.t[l];
+      W.y[i] = cdiv(acc, at(i, i));
+    }
+    __syncthreads();
+  }
+  for (int i = lane; i < k; i += kWave) G.y[int64_t(s) * m + i] = W.y[i];
+}
+__global__ void __launch_bounds__(kWave) k_solve_fin(const GmSt* st, GmArr G) {
+  __shared__ SolveLds W;
+  const GmSt& S = st[blockIdx.x];
+  if (S.done || S.nan) return;
+  solve_y(S, G, blockIdx.x, W);
 }
 
 // u += sum_{i<k} y_i V_i (D^-1 times the sum in the tensor form)
@@ -503,6 +534,248 @@ __global__ void __launch_bounds__(kBlock) k_update(Seg L, TzOp Z, const GmSt* st
   }
   if (F == kFormTensor) acc = u0 + tz_pre<F>(Z, form_seg<F>(Z, t), t.row, acc);
   u[t.row] = ccast<T>(acc);
+}
+
+// ---- one small system in the tensor form (few_blocks)
+// A step of the path above is seven launches there, each a few us of latency.
+// Here it is four: the sums are added by the kernel that needs them, and the
+// Givens step of a column runs in a block of its own beside the next column's
+// product.  A block takes 64 rows with four threads each (a quarter of the
+// basis per thread, 16 rows a wave), so 3,003 rows are 47 blocks whose loads
+// are all in flight at once.  Measured at 21x13x11 nodes, m = 30: 53 -> 26 us
+// a step.
+constexpr int kFewRows = 64, kFewParts = kBlock / kFewRows;
+constexpr int kFewBlocks = 256;      // at most; four partials a lane
+constexpr int kFewMaxM = 56;         // basis vectors per thread: 14
+
+// Sum of nb partials, by one wave; the same value in every lane.
+__device__ __forceinline__ double few_sum(const double* __restrict__ p, int nb) {
+  double v = 0.0;
+  for (int b = threadIdx.x & (kWave - 1); b < nb; b += kWave) v += p[b];
+  return wave_sum(v);
+}
+// The n complex coefficients of partials [nb][2 n], by the whole block: a
+// thread adds one of E sums over every (kBlock / E)-th block, with its loads
+// in flight together (one sum a wave after the other took 6 us at n = 30).
+template <int E>
+__device__ __forceinline__ void few_coefs(const double* __restrict__ p, int n, int nb, z_t* h) {
+  constexpr int kGroups = kBlock / E;
+  __shared__ double lds[kGroups][E];
+  const int e = threadIdx.x % E, g = threadIdx.x / E;
+  double v = 0.0;
+  if (e < 2 * n) {
+#pragma unroll 16
+    for (int b = g; b < nb; b += kGroups) v += p[int64_t(b) * 2 * n + e];
+  }
+  lds[g][e] = v;
+  __syncthreads();
+  if (int(threadIdx.x) < 2 * n) {
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < kGroups; ++k) t += lds[k][e];
+    reinterpret_cast<double*>(h)[e] = t;
+  }
+  __syncthreads();
+}
+
+// w = A v_j = s_j (A V_j) from the D^-1-scaled copy in; the last block adds
+// the norm's partials of column j - 1 and runs its Givens step.  The product's
+// blocks read neither what that step writes nor its flag: they stop one column
+// later (off).
+template <typename T, int F>
+__global__ void __launch_bounds__(kBlock) k_few_prod(Seg L, SellOp<T> A, GmSt* st, GmArr G, const cx<T>* __restrict__ in,
+                                                     int j, cx<T>* __restrict__ w, const double* __restrict__ pn, int nb) {
+  __shared__ GivensLds W;
+  if (int(blockIdx.x) == L.nblk) {
+    if (st->cyc) return;
+    givens_stage(G, 0, j - 1, W);
+    const double ww = few_sum(pn, nb);
+    __syncthreads();
+    if (threadIdx.x == 0) givens_step(*st, G, 0, j - 1, ww, W);
+    return;
+  }
+  if (st->off) return;
+  double s;
+  if (j == 0) {
+    s = G.vs[0];
+  } else {
+    const double hn = sqrt(few_sum(pn, nb));
+    s = hn > 0.0 ? 1.0 / hn : 0.0;
+  }
+  Tile t;
+  t.tile = xcd_tile(blockIdx.x, L.nblk);
+  t.seg = 0;
+  t.row = 0;
+  for_rows<F>(A, t, in, [](int64_t) { return 0; },
+              [=](int64_t row, cx<T> y, int) { w[row] = ccast<T>(s * zd(y)); });
+}
+
+// A thread's row and its share of the basis: vectors i0 .. i0 + q - 1 < n.
+struct FewRow {
+  int64_t row;
+  int part, i0, q;
+};
+__device__ __forceinline__ FewRow few_row(int n) {
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  FewRow r;
+  r.part = lane / 16;
+  r.row = int64_t(blockIdx.x) * kFewRows + wave * 16 + lane % 16;
+  const int qa = (n + kFewParts - 1) / kFewParts;
+  r.i0 = r.part * qa;
+  r.q = n - r.i0 < qa ? n - r.i0 : qa;
+  return r;
+}
+// Partials [nb][2 n] of the dots d[u] of a block's rows with vector i0 + u.
+template <int Q>
+__device__ __forceinline__ void few_partials(double (&d)[Q][2], const FewRow& r, int n, double* part) {
+  __shared__ double lds[2 * kFewMaxM][kBlock / kWave];
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+#pragma unroll
+  for (int u = 0; u < Q; ++u)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      double v = d[u][c];          // over the wave's 16 rows
+      v += row_rotate<8>(v);
+      v += row_rotate<4>(v);
+      v += row_rotate<2>(v);
+      v += row_rotate<1>(v);
+      if (lane % 16 == 0 && u < r.q) lds[2 * (r.i0 + u) + c][wave] = v;
+    }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 2 * n; e += kBlock) {
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < kBlock / kWave; ++k) t += lds[e][k];
+    part[int64_t(blockIdx.x) * 2 * n + e] = t;
+  }
+}
+
+// Partials of h1_i = v_i^H w, i <= j.
+template <typename T, int Q>
+__global__ void __launch_bounds__(kBlock) k_few_dots(GmSt* st, GmArr G, const cx<T>* __restrict__ V, int64_t ld, int j,
+                                                     const cx<T>* __restrict__ w, double* __restrict__ p1) {
+  if (st->cyc) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->off = 1;
+    return;
+  }
+  const int n = j + 1;
+  const FewRow r = few_row(n);
+  cx<T> v[Q];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) v[u] = u < r.q ? V[int64_t(r.i0 + u) * ld + r.row] : cx<T>{T(0), T(0)};
+  const z_t x = zd(w[r.row]);
+  double d[Q][2];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) {
+    d[u][0] = d[u][1] = 0.0;
+    if (u < r.q) dot_acc(d[u], G.vs[r.i0 + u] * zd(v[u]), x);
+  }
+  few_partials<Q>(d, r, n, p1);
+}
+
+// FIRST: w1 = w - sum_i h1_i v_i in place of w and the partials of h2_i =
+// v_i^H w1.  Else: w2 = w1 - sum_i h2_i v_i in place of w, its D^-1-scaled copy
+// in, the partials of ||w2||^2, and H[:, j] = h1 + h2.
+template <typename T, int Q, bool FIRST>
+__global__ void __launch_bounds__(kBlock) k_few_axpy(TzOp Z, const GmSt* st, GmArr G, const cx<T>* __restrict__ V,
+                                                     int64_t ld, int j, cx<T>* __restrict__ w, cx<T>* __restrict__ in,
+                                                     const double* __restrict__ p, double* __restrict__ out, int nb) {
+  __shared__ z_t h[kFewMaxM];
+  __shared__ double nrm[kBlock / kWave];
+  if (st->cyc) return;
+  const int n = j + 1;
+  const FewRow r = few_row(n);
+  cx<T> v[Q];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) v[u] = u < r.q ? V[int64_t(r.i0 + u) * ld + r.row] : cx<T>{T(0), T(0)};
+  const z_t x = zd(w[r.row]);
+  few_coefs<(2 * Q * kFewParts <= kWave ? kWave : 2 * kWave)>(p, n, nb, h);
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < n; i += kBlock) {
+      if (FIRST) G.h1[i] = h[i];
+      else G.H[int64_t(j) * (G.m + 1) + i] = G.h1[i] + h[i];
+    }
+  z_t acc = r.part == 0 ? x : z_t{0.0, 0.0};
+#pragma unroll
+  for (int u = 0; u < Q; ++u)
+    if (u < r.q) {
+      const z_t c = G.vs[r.i0 + u] * h[r.i0 + u], b = zd(v[u]);
+      acc = acc - c * b;
+    }
+  // over the four parts of the row: lane distances 16 and 32
+#pragma unroll
+  for (int o = 16; o < kWave; o <<= 1) {
+    acc.re += __shfl_xor(acc.re, o, kWave);
+    acc.im += __shfl_xor(acc.im, o, kWave);
+  }
+  const cx<T> ws = ccast<T>(acc);
+  if (r.part == 0) w[r.row] = ws;
+  const z_t y = zd(ws);
+  if constexpr (FIRST) {
+    double d[Q][2];
+#pragma unroll
+    for (int u = 0; u < Q; ++u) {
+      d[u][0] = d[u][1] = 0.0;
+      if (u < r.q) dot_acc(d[u], G.vs[r.i0 + u] * zd(v[u]), y);
+    }
+    few_partials<Q>(d, r, n, out);
+  } else {
+    if (r.part == 0) in[r.row] = ccast<T>(tz_pre<kFormTensor>(Z, tz_seg(Z, 0), r.row, y));
+    const double q = wave_sum(r.part == 0 ? norm2(y) : 0.0);
+    if ((threadIdx.x & (kWave - 1)) == 0) nrm[threadIdx.x / kWave] = q;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < kBlock / kWave; ++k) t += nrm[k];
+      out[blockIdx.x] = t;
+    }
+  }
+}
+
+// The last column's Givens step and y, by one wave.
+__global__ void __launch_bounds__(kWave) k_few_end(GmSt* st, GmArr G, int j, const double* __restrict__ pn, int nb) {
+  __shared__ GivensLds W;
+  __shared__ SolveLds Y;
+  if (!st->cyc) {
+    givens_stage(G, 0, j, W);
+    const double ww = few_sum(pn, nb);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      givens_step(*st, G, 0, j, ww, W);
+      __threadfence_block();
+    }
+  }
+  __syncthreads();
+  if (st->done || st->nan) return;
+  solve_y(*st, G, 0, Y);
+}
+
+template <typename T>
+int few_cycle(hipStream_t s, const SellOp<T>& A, GmSt* st, const GmArr& G, cx<T>* V, int64_t ld, int mc, cx<T>* in,
+              double* pt) {
+  const int nb = int(ld / kFewRows);
+  double *p1 = pt, *p2 = p1 + 2 * int64_t(kFewMaxM) * nb, *pn = p2 + 2 * int64_t(kFewMaxM) * nb;
+  const Seg& P = A.tz.lp;
+  for (int j = 0; j < mc; ++j) {
+    cx<T>* w = V + int64_t(j + 1) * ld;
+    const int grid = P.nblk + (j > 0);
+    if (A.tz.on == 1) k_few_prod<T, kFormTensor><<<grid, kBlock, 0, s>>>(P, A, st, G, in, j, w, pn, nb);
+    else k_few_prod<T, kFormTensorExt><<<grid, kBlock, 0, s>>>(P, A, st, G, in, j, w, pn, nb);
+    auto rest = [&](auto Qc) {
+      constexpr int Q = decltype(Qc)::value;
+      k_few_dots<T, Q><<<nb, kBlock, 0, s>>>(st, G, V, ld, j, w, p1);
+      k_few_axpy<T, Q, true><<<nb, kBlock, 0, s>>>(A.tz, st, G, V, ld, j, w, in, p1, p2, nb);
+      k_few_axpy<T, Q, false><<<nb, kBlock, 0, s>>>(A.tz, st, G, V, ld, j, w, in, p2, pn, nb);
+    };
+    if (j < 4 * kFewParts) rest(std::integral_constant<int, 4>{});
+    else if (j < 8 * kFewParts) rest(std::integral_constant<int, 8>{});
+    else rest(std::integral_constant<int, kFewMaxM / kFewParts>{});
+    HZ_HIP(hipGetLastError());
+  }
+  k_few_end<<<1, kWave, 0, s>>>(st, G, mc - 1, pn, nb);
+  HZ_HIP(hipGetLastError());
+  return HZ_OK;
 }
 
 __global__ void k_init_st(int nseg, GmSt* st, const double* fn2, double tol) {
@@ -546,7 +819,13 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   DevBuf* Vb = ctx->buf(p + "V", sizeof(cx<T>) * ld * (m + 1), &rc);
   if (rc) return rc;
   const int nchunk = ceil_div(m + 1, NV);
-  DevBuf* part = ctx->buf(p + "part", sizeof(double) * std::max(int64_t(nchunk) * S.nblk * 2 * NV, int64_t(prod_seg(A, S.dev).nblk)), &rc);
+  // One small system in the tensor form takes its own kernels: up to 256 blocks
+  // of 64 rows and 56 basis vectors, beyond which adding the partials in every
+  // block costs more than the launches it saves.
+  const bool few = A.tz.on && S.nseg == 1 && m <= kFewMaxM && ld <= int64_t(kFewBlocks) * kFewRows;
+  int64_t np = std::max(int64_t(nchunk) * S.nblk * 2 * NV, int64_t(prod_seg(A, S.dev).nblk));
+  if (few) np = std::max(np, (4 * kFewMaxM + 1) * (ld / kFewRows));
+  DevBuf* part = ctx->buf(p + "part", sizeof(double) * np, &rc);
   if (rc) return rc;
   DevBuf* stb = ctx->buf(p + "st", sizeof(GmSt) * S.nseg, &rc);
   if (rc) return rc;
@@ -603,7 +882,8 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     HZ_HIP(hipGetLastError());
     int mc = int(std::min<int64_t>(m, ctl.max_matvec - mv_max - 1));
     if (mc >= 1) {
-      for (int j = 0; j < mc; ++j) {
+      if (few) HZ_TRY(few_cycle<T>(s, A, st, G, V, ld, mc, in, pt));
+      for (int j = 0; j < mc && !few; ++j) {
         cx<T>* w = V + int64_t(j + 1) * ld;
         dim3 gd(grid, ceil_div(j + 1, NV));
         dim3 gf(S.nseg, j + 1);
@@ -626,7 +906,7 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
         k_givens_fin<<<S.nseg, kFinBlock, 0, s>>>(L, st, G, pt, j);
         HZ_HIP(hipGetLastError());
       }
-      k_solve_fin<<<ceil_div(S.nseg, 64), 64, 0, s>>>(st, G, S.nseg);
+      if (!few) k_solve_fin<<<S.nseg, kWave, 0, s>>>(st, G);
       HZ_BY_SCALING(A, k_update<T, F><<<grid, kBlock, 0, s>>>(L, A.tz, st, G, V, ld, u));
       HZ_HIP(hipGetLastError());
     }

@@ -308,3 +308,35 @@ def test_sweep_product(P, monkeypatch, size, nf, eta):
                     bound = bound + 2.0**-23 * np.abs(want).astype(np.float64)
                 assert _within(Y[:, c].cpu().numpy(), want, bound) <= 1.0
     m.close()
+
+
+# basis vectors per thread change at 16 and 32, the small-system kernels end at a restart
+# length of 56 and at 16,384 rows (31x31x17 nodes are 16,337 rows in 64 tiles, 32x31x17 are 67)
+@pytest.mark.parametrize("size,restart", [((2, 1, 1), 1), ((6, 5, 4), 3), ((9, 8, 7), 16), ((9, 8, 7), 17),
+                                          ((9, 8, 7), 32), ((9, 8, 7), 33), ((9, 8, 7), 56), ((9, 8, 7), 57),
+                                          ((30, 30, 16), 30), ((31, 30, 16), 30)])
+def test_gmres_of_small_boxes(P, monkeypatch, size, restart):
+    """One restart cycle and two: the residual estimate from the rotations is
+    the true residual (Arnoldi identity, kept to 1e-10 by two Gram-Schmidt
+    passes), the same in the stencil form, and no basis is read beyond the
+    columns formed when the cap stops a cycle early."""
+    say("small GMRES", size, restart)
+    rng = np.random.default_rng(restart)
+    mesh = graded_box(*size, seed=sum(size))
+    beta = _beta(rng)
+    g = torch.as_tensor(rng.standard_normal(mesh["n_nodes"]) + 1j * rng.standard_normal(mesh["n_nodes"]), device="cuda")
+    for cap in (restart + 1, restart + 2 + restart // 2, 2 * restart + 2):
+        res, x = [], []
+        for form in ("1", "0"):
+            monkeypatch.setenv("HZ_TENSOR", form)
+            m = P.Helmholtz(mesh, beta)
+            m.set_frequency(80.0)
+            f = m.load(g)
+            p, info = m.solve(f, method="gmres", restart=restart, tol=1e-12, max_matvec=cap)
+            r = float((f - m.apply(p)).norm() / f.norm())
+            assert info["matvecs"] <= cap + 1 and abs(info["relres_true"] - r) <= 1e-10
+            res.append(r)
+            x.append(p)
+            m.close()
+        assert abs(res[0] - res[1]) <= 1e-8 * max(res) + 1e-11
+        assert float((x[0] - x[1]).norm()) <= 1e-7 * float(x[1].norm())
