@@ -315,6 +315,17 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
     return HZ_OK;
   };
 
+  constexpr int kChunk = 8;          // iterations between reports
+  ReplayKey key;
+  key.op(A).add(V).add(P).add(W).add(st).add(S.nseg);
+  for (const PartBuf* b : {&pa, &po, &pn}) b->key(&key);
+  auto run_chunk = [&](hipStream_t on) -> int {
+    s = on;
+    int crc = HZ_OK;
+    for (int it = 0; it < kChunk && crc == HZ_OK; ++it) crc = enqueue_iter();
+    s = ctx->stream;
+    return crc;
+  };
   HZ_TRY(enqueue_resid());
   HZ_TRY(poll.wait(0));
   const BiSt* hst = poll.state<BiSt>(0);
@@ -344,7 +355,9 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
     const int first = poll.posted;
     for (bool stop = false; !stop && left > 0;) {
       const int n_it = int(std::min<int64_t>(chunk, left));
-      for (int it = 0; it < n_it; ++it) HZ_TRY(enqueue_iter());
+      bool ran = false;
+      if (n_it == kChunk) HZ_TRY(replay(ctx, p, key, run_chunk, &ran));
+      for (int it = 0; it < n_it && !ran; ++it) HZ_TRY(enqueue_iter());
       left -= n_it;
       HZ_TRY(report());
       if (poll.posted - 1 > first) {
@@ -353,7 +366,7 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
         stop = true;
         for (int i = 0; i < S.nseg; ++i) stop = stop && h[i].done;
       }
-      chunk = std::min(chunk * 2, 8);
+      chunk = std::min(chunk * 2, kChunk);
     }
     HZ_TRY(poll.wait(poll.posted - 1));
     hst = poll.state<BiSt>(poll.posted - 1);

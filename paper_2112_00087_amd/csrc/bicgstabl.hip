@@ -430,6 +430,17 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     }
   };
 
+  constexpr int kChunk = 2;          // cycles between reports
+  ReplayKey key;
+  key.op(A).add(V).add(P).add(W).add(st).add(S.nseg).add(l);
+  for (const PartBuf* b : {&pa, &pb, &pg, &pc}) b->key(&key);
+  auto run_chunk = [&](hipStream_t on) -> int {
+    s = on;
+    int crc = HZ_OK;
+    for (int c = 0; c < kChunk && crc == HZ_OK; ++c) crc = enqueue_cycle();
+    s = ctx->stream;
+    return crc;
+  };
   HZ_TRY(enqueue_resid(1));
   const BlSt* hst = poll.state<BlSt>(poll.posted - 1);
   int chunk = 1;
@@ -463,7 +474,9 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     const int first = poll.posted;
     for (bool stop = false; !stop && left > 0;) {
       const int n_cyc = int(std::min<int64_t>(chunk, left));
-      for (int c = 0; c < n_cyc; ++c) HZ_TRY(enqueue_cycle());
+      bool ran = false;
+      if (n_cyc == kChunk) HZ_TRY(replay(ctx, p, key, run_chunk, &ran));
+      for (int c = 0; c < n_cyc && !ran; ++c) HZ_TRY(enqueue_cycle());
       left -= n_cyc;
       HZ_TRY(report());
       if (poll.posted - 1 > first) {
@@ -476,7 +489,7 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
         }
         stop = off || brk;
       }
-      chunk = std::min(chunk * 2, 2);
+      chunk = std::min(chunk * 2, kChunk);
     }
     HZ_TRY(poll.wait(poll.posted - 1));
     hst = poll.state<BlSt>(poll.posted - 1);

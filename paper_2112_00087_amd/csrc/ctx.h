@@ -93,6 +93,16 @@ struct TensorDev {
   bool have_eta = false;
 };
 
+// A captured run of a solver's iterations (ops.h).
+struct Replay {
+  std::string key;                   // every argument of its kernels
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
+  int failed = 0;                    // captures that did not work
+  ~Replay() { drop(); }
+  void drop();
+};
+
 struct hz_ctx_s {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -172,6 +182,9 @@ struct hz_ctx_s {
   std::map<std::string, std::unique_ptr<DevBuf>> ws;
   std::unique_ptr<SegHost> single_seg;
   hipEvent_t poll_ev[2] = {nullptr, nullptr};   // StatePoll
+  std::map<std::string, Replay> replays;        // per solver tag
+  hipStream_t cap = nullptr;         // capture stream of the replays
+  bool graphs_on = true;             // HZ_GRAPH=0 in the environment turns them off
   void* pinned = nullptr;            // small pinned host buffer for status reads
   size_t pinned_bytes = 0;
 

@@ -61,6 +61,16 @@ hz_ctx_s::~hz_ctx_s() {
   if (pinned) (void)hipHostFree(pinned);
   for (hipEvent_t e : poll_ev)
     if (e) (void)hipEventDestroy(e);
+  replays.clear();
+  if (cap) (void)hipStreamDestroy(cap);
+}
+
+void Replay::drop() {
+  if (exec) (void)hipGraphExecDestroy(exec);
+  if (graph) (void)hipGraphDestroy(graph);
+  exec = nullptr;
+  graph = nullptr;
+  key.clear();
 }
 
 int ctx_pinned(hz_ctx ctx, size_t bytes, void** out) {
@@ -156,6 +166,8 @@ int ctx_upload(hz_ctx ctx) {
     // Split-form pattern.  Without an absorption field, entry (i, j) of the
     // (column-scaled) operator is complex only if it carries a wall term or
     // column j's diagonal does (then 1/diag_j is complex).
+    const char* genv = std::getenv("HZ_GRAPH");
+    ctx->graphs_on = !(genv && genv[0] == '0');
     const char* env = std::getenv("HZ_SPLIT");
     ctx->split_on = !(env && env[0] == '0');
     std::vector<int32_t> csr2b(a.col.size(), -1);

@@ -874,13 +874,13 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   std::vector<int64_t> mv(S.nseg, 0);
   int64_t mv_max = 0;
   const int grid = S.nblk;
-  for (;;) {
+  // one restart cycle of mc steps (0: the residual alone)
+  auto enqueue_cycle = [&](int mc) -> int {
     // residual of the current iterate; converged segments stop here
     HZ_BY_FORM(A, k_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, f, u, V, pt));
     k_beta_fin<<<S.nseg, kFinBlock, 0, s>>>(P, st, G, pt);
     if (A.tz.on) k_gs_start<T><<<grid, kBlock, 0, s>>>(L, A.tz, V, in);
     HZ_HIP(hipGetLastError());
-    int mc = int(std::min<int64_t>(m, ctl.max_matvec - mv_max - 1));
     if (mc >= 1) {
       if (few) HZ_TRY(few_cycle<T>(s, A, st, G, V, ld, mc, in, pt));
       for (int j = 0; j < mc && !few; ++j) {
@@ -910,6 +910,24 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
       HZ_BY_SCALING(A, k_update<T, F><<<grid, kBlock, 0, s>>>(L, A.tz, st, G, V, ld, u));
       HZ_HIP(hipGetLastError());
     }
+    return HZ_OK;
+  };
+  auto run_cycle = [&](hipStream_t on) -> int {
+    s = on;
+    const int crc = enqueue_cycle(m);
+    s = ctx->stream;
+    return crc;
+  };
+  ReplayKey key;
+  key.op(A).add(f).add(u).add(L).add(P).add(st).add(G.H).add(G.cs).add(G.sn).add(G.g).add(G.y).add(G.h1).add(G.h2).add(G.vs).add(G.m).add(V).add(ld).add(in).add(pt).add(S.nseg);
+  bool first = true;
+  for (;;) {
+    const int mc = int(std::min<int64_t>(m, ctl.max_matvec - mv_max - 1));
+    bool ran = false;
+    // (a capture pays from the second cycle on)
+    if (mc == m) HZ_TRY(replay(ctx, p, key, run_cycle, &ran, !first));
+    if (!ran) HZ_TRY(enqueue_cycle(mc));
+    first = false;
     HZ_HIP(hipMemcpyAsync(hst, st, sizeof(GmSt) * S.nseg, hipMemcpyDeviceToHost, s));
     HZ_HIP(hipStreamSynchronize(s));
     bool all_done = true;

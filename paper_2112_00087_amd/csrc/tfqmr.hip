@@ -388,10 +388,20 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     HZ_BY_FORM(A, k_tq_odd3<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pa.raw));
     HZ_TRY(pa.close<2>(s));
     HZ_HIP(hipGetLastError());
-    ++pairs;
     return HZ_OK;
   };
 
+  constexpr int kChunk = 8;          // pairs between reports
+  ReplayKey key;
+  key.op(A).add(V).add(P).add(W).add(st).add(S.nseg);
+  for (const PartBuf* b : {&pa, &pe, &po}) b->key(&key);
+  auto run_chunk = [&](hipStream_t on) -> int {
+    s = on;
+    int crc = HZ_OK;
+    for (int c = 0; c < kChunk && crc == HZ_OK; ++c) crc = enqueue_pair();
+    s = ctx->stream;
+    return crc;
+  };
   HZ_TRY(enqueue_restart(1));
   const TqSt* hst = poll.state<TqSt>(poll.posted - 1);
   int chunk = 2;
@@ -424,7 +434,10 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     const int first = poll.posted;
     for (bool stop = false; !stop && left > 0;) {
       const int n_pair = int(std::min<int64_t>(chunk, left));
-      for (int c = 0; c < n_pair; ++c) HZ_TRY(enqueue_pair());
+      bool ran = false;
+      if (n_pair == kChunk) HZ_TRY(replay(ctx, p, key, run_chunk, &ran));
+      for (int c = 0; c < n_pair && !ran; ++c) HZ_TRY(enqueue_pair());
+      pairs += n_pair;
       left -= n_pair;
       HZ_TRY(report());
       if (poll.posted - 1 > first) {
@@ -437,7 +450,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
         }
         stop = off || brk;
       }
-      chunk = std::min(chunk * 2, 8);
+      chunk = std::min(chunk * 2, kChunk);
     }
     HZ_TRY(poll.wait(poll.posted - 1));
     hst = poll.state<TqSt>(poll.posted - 1);
