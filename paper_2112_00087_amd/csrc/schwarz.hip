@@ -582,6 +582,13 @@ __global__ void k_axpy_z(int64_t n, z_t a, const z_t* __restrict__ x, z_t* __res
   if (i < n) y[i] = y[i] + a * x[i];
 }
 
+// y -= h x, h on the device (the coefficient of the dot product before it)
+__global__ void k_orth_z(int64_t n, const double* __restrict__ h, const z_t* __restrict__ x, z_t* __restrict__ y) {
+  int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  const z_t a = {-h[0], -h[1]};
+  if (i < n) y[i] = y[i] + a * x[i];
+}
+
 __global__ void k_scal_z(int64_t n, z_t a, const z_t* __restrict__ x, z_t* __restrict__ y) {
   int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
   if (i < n) y[i] = a * x[i];
@@ -697,6 +704,23 @@ void dd_optimised_alpha(double k, double Hsub, double h, int sides, std::complex
     lam.push_back(xi > k ? std::complex<double>(std::sqrt(xi * xi - k * k), 0.0)
                          : std::complex<double>(0.0, std::sqrt(k * k - xi * xi)));
   }
+  // Largest f over the modes, given up (with a value >= stop) as soon as one
+  // mode reaches stop, the mode that did so last being tried first: a
+  // candidate only matters if it stays below the best so far.  Same choice
+  // as evaluating every mode of every candidate, which took 190 ms a solve.
+  size_t hint = 0;
+  auto worst_below = [&](auto f, double stop) {
+    double worst = lam.empty() ? 0.0 : std::max(0.0, f(lam[hint]));
+    if (worst >= stop) return worst;
+    for (size_t i = 0; i < lam.size(); ++i) {
+      worst = std::max(worst, f(lam[i]));
+      if (worst >= stop) {
+        hint = i;
+        return worst;
+      }
+    }
+    return worst;
+  };
   const int ng = 80;
   double lo = xmin / 10.0, best = 1e300;
   std::complex<double> arg(0.0, k);
@@ -705,8 +729,7 @@ void dd_optimised_alpha(double k, double Hsub, double h, int sides, std::complex
     for (int iq = 0; iq < ng; ++iq) {
       double qv = lo * std::pow(xmax / lo, double(iq) / (ng - 1));
       std::complex<double> a(pv, qv);
-      double worst = 0.0;
-      for (const auto& l : lam) worst = std::max(worst, std::abs((l - a) / (l + a)));
+      const double worst = worst_below([&](std::complex<double> l) { return std::abs((l - a) / (l + a)); }, best);
       if (worst < best) {
         best = worst;
         arg = a;
@@ -716,24 +739,23 @@ void dd_optimised_alpha(double k, double Hsub, double h, int sides, std::complex
   out[0] = out[1] = arg;
   if (sides != 2 || lam.empty()) return;
   const double q = arg.imag();
-  auto factor = [&](const double* v) {   // v = log p_lo, log p_hi
+  auto factor = [&](const double* v, double stop) {   // v = log p_lo, log p_hi
     const std::complex<double> a1(std::exp(v[0]), q), a2(std::exp(v[1]), q);
-    double worst = 0.0;
-    for (const auto& l : lam) worst = std::max(worst, std::abs((l - a1) * (l - a2) / ((l + a1) * (l + a2))));
-    return worst;
+    return worst_below([&](std::complex<double> l) { return std::abs((l - a1) * (l - a2) / ((l + a1) * (l + a2))); },
+                       stop);
   };
   double bestv[2] = {std::log(arg.real()), std::log(arg.real())};
-  double bestf = factor(bestv);
+  double bestf = factor(bestv, HUGE_VAL);
   for (double split : {1.0, 2.0, 4.0, 8.0, 16.0}) {
     double v[2] = {std::log(arg.real() / split), std::log(arg.real() * split)};
-    double fv = factor(v);
+    double fv = factor(v, HUGE_VAL);
     for (double step = std::log(2.0); step > 1e-3;) {
       bool moved = false;
       for (int c = 0; c < 2; ++c)
         for (double sg : {1.0, -1.0}) {
           double t[2] = {v[0], v[1]};
           t[c] += sg * step;
-          const double ft = factor(t);
+          const double ft = factor(t, fv);
           if (ft < fv) {
             fv = ft;
             v[0] = t[0];
@@ -884,6 +906,10 @@ int schwarz_solve(hz_ctx ctx, const hz_solve_opts& o, const z_t* f, z_t* p, hz_s
       HZ_TRY(glue_and_residual(&rel));
     } else {
       // restarted GMRES on (I - B) lam = c, MGS Arnoldi with host Hessenberg
+      DevBuf* hb = ctx->buf("dd.h", 16 * size_t(m + 1), &rc);
+      if (rc) return rc;
+      double* hd = hb->as<double>();
+      std::vector<std::complex<double>> hcol(m + 1);
       std::complex<double> cc;
       HZ_TRY(host_dot(ctx, nl, c, c, &cc));
       const double cnorm = std::sqrt(cc.real());
@@ -915,15 +941,18 @@ int schwarz_solve(hz_ctx ctx, const hz_solve_opts& o, const z_t* f, z_t* p, hz_s
             HZ_TRY(R.apply(V + int64_t(j) * nl, vj1, nullptr));
             if_mv += 1;
             inf.iters += 1;
+            // the coefficients stay on the device until the column is complete (a
+            // host round trip for each took 15 us, 23 of them a step)
             for (int i = 0; i <= j; ++i) {
-              std::complex<double> h;
-              HZ_TRY(host_dot(ctx, nl, V + int64_t(i) * nl, vj1, &h));
-              H[i + (m + 1) * j] = h;
-              k_axpy_z<<<ceil_div(nl, kBlock), kBlock, 0, s>>>(nl, z_t{-h.real(), -h.imag()}, V + int64_t(i) * nl, vj1);
+              HZ_TRY(op_dotc(ctx, nl, V + int64_t(i) * nl, vj1, hd + 2 * i));
+              k_orth_z<<<ceil_div(nl, kBlock), kBlock, 0, s>>>(nl, hd + 2 * i, V + int64_t(i) * nl, vj1);
             }
-            std::complex<double> hh;
-            HZ_TRY(host_dot(ctx, nl, vj1, vj1, &hh));
-            double hn = std::sqrt(hh.real());
+            HZ_TRY(op_dotc(ctx, nl, vj1, vj1, hd + 2 * (j + 1)));
+            HZ_HIP(hipGetLastError());
+            HZ_HIP(hipMemcpyAsync(hcol.data(), hd, 16 * size_t(j + 2), hipMemcpyDeviceToHost, s));
+            HZ_HIP(hipStreamSynchronize(s));
+            for (int i = 0; i <= j; ++i) H[i + (m + 1) * j] = hcol[i];
+            double hn = std::sqrt(hcol[j + 1].real());
             H[j + 1 + (m + 1) * j] = hn;
             for (int i = 0; i < j; ++i) {
               std::complex<double> a = H[i + (m + 1) * j], b = H[i + 1 + (m + 1) * j];
