@@ -160,14 +160,22 @@ int hz_apply(hz_ctx ctx, const hz_c128* x_dev, hz_c128* y_dev) {
   if (!ctx->have_freq) return hz_fail(HZ_ERR_STATE, "no frequency set");
   const int64_t n = ctx->h.n, nr = ctx->sell.n_rows;
   const z_t* x = reinterpret_cast<const z_t*>(x_dev);
-  if (ctx->tz) {   // the mesh's own numbering, no scaling folded in: x and y as they are
+  z_t* y = reinterpret_cast<z_t*>(y_dev);
+  const bool apart = x + n <= y || y + n <= x;
+  int rc = 0;
+  if (ctx->tz && apart) {   // the mesh's own numbering, no scaling folded in: x and y as they are
     SellOp<double> A = op_A(ctx);
     A.tz.scale = 0;
-    return op_spmv<double>(ctx->stream, nr, n, A, x, reinterpret_cast<z_t*>(y_dev));
+    return op_spmv<double>(ctx->stream, nr, n, A, x, y);
   }
-  int rc = 0;
   DevBuf* t = ctx->buf("apply.x", sizeof(z_t) * nr, &rc);
   if (rc) return rc;
+  if (ctx->tz) {            // in place: from a copy
+    HZ_TRY(pad_in(ctx, n, nr, x, nullptr, t->as<z_t>()));
+    SellOp<double> A = op_A(ctx);
+    A.tz.scale = 0;
+    return op_spmv<double>(ctx->stream, nr, n, A, t->as<z_t>(), y);
+  }
   // a column-scaled operator A D^-1 is applied to D x
   HZ_TRY(pad_in(ctx, n, nr, x, ctx->scaled == HZ_JACOBI ? ctx->d_d.as<z_t>() : nullptr, t->as<z_t>()));
   if (ctx->perm.empty()) {

@@ -379,7 +379,8 @@ __device__ __forceinline__ const St& advance(const Part& P, const St* in, St* ou
   const int b0 = P.nseg == 1 ? 0 : P.seg_blk[t.seg], b1 = P.nseg == 1 ? P.nblk : P.seg_blk[t.seg + 1];
   // the order of a kFinBlock-thread finalize kernel (seg_sums): thread u takes
   // blocks u, u + kFinBlock, ..., here threads u of pass m stand for u + 256 m
-  const int passes = b1 - b0 > kBlock ? kPasses : 1;
+  // (passes without blocks would add zeros)
+  const int passes = min(kPasses, (b1 - b0 + kBlock - 1) / kBlock);
   double acc[kPasses][NQ];
 #pragma unroll
   for (int m = 0; m < kPasses; ++m) {
@@ -408,10 +409,16 @@ __device__ __forceinline__ const St& advance(const Part& P, const St* in, St* ou
     }
   }
   __syncthreads();
-  const int waves = passes * (kBlock / kWave);
+  // (unrolled: the LDS reads issue together; one after the other they were
+  // 2 us of a 9.7 us kernel at 16 waves and 4 sums)
   auto total = [&](int q) {
     double s = 0.0;
-    for (int i = 0; i < waves; ++i) s += lds[q][i];
+#pragma unroll
+    for (int m = 0; m < kPasses; ++m)
+      if (m < passes) {
+#pragma unroll
+        for (int i = 0; i < kBlock / kWave; ++i) s += lds[q][m * (kBlock / kWave) + i];
+      }
     return s;
   };
   if (NQ > 4) {

@@ -253,6 +253,23 @@ __device__ __forceinline__ double tz_rcp(double v) {
   r = fma(r, fma(-v, r, 1.0), r);
   return fma(r, fma(-v, r, 1.0), r);
 }
+// y + a x and y - a x: in the tensor form with one rounding per term, in the
+// stored forms as these expressions always were compiled there.
+template <int F>
+__device__ __forceinline__ z_t tz_axpy(z_t a, z_t x, z_t y) {
+  if constexpr (F == kFormTensor || F == kFormTensorExt)
+    return z_t{fma(a.re, x.re, fma(-a.im, x.im, y.re)), fma(a.re, x.im, fma(a.im, x.re, y.im))};
+  else
+    return y + a * x;
+}
+template <int F>
+__device__ __forceinline__ z_t tz_axmy(z_t a, z_t x, z_t y) {
+  if constexpr (F == kFormTensor || F == kFormTensorExt)
+    return z_t{fma(-a.re, x.re, fma(a.im, x.im, y.re)), fma(-a.re, x.im, fma(-a.im, x.re, y.im))};
+  else
+    return y - a * x;
+}
+
 // D^-1 v and D v of the right-Jacobi operator A D^-1 in the tensor form; in
 // the stored forms D is folded into the values and both are v itself.
 template <int F>

@@ -201,11 +201,11 @@ __global__ void __launch_bounds__(kBlock) k_tq_even1(Seg L, TzOp Z, Part P, cons
   vec_rows(L, t, [&](int64_t row) {
     const z_t u = zd(V.u[row]);
     const z_t av = a * zd(V.v[row]);
-    const cx<T> w = zt<T>(zd(V.w[row]) - a * zd(V.uh[row]));
-    const z_t d = zd(V.d[row]);
+    const z_t w0 = zd(V.w[row]), uh = zd(V.uh[row]), d = zd(V.d[row]);
+    const cx<T> w = zt<T>(tz_axmy<F>(a, uh, w0));
     V.un[row] = zt<T>(u - tz_pre<F>(Z, B, row, av));
     V.w[row] = w;
-    V.d[row] = zt<T>(u + g * d);
+    V.d[row] = zt<T>(tz_axpy<F>(g, d, u));
     q[0] += norm2(zd(w));
   });
   store_partials<1>(q, part, t);
@@ -222,14 +222,14 @@ __global__ void HZ_PRODUCT_BOUNDS k_tq_even2(Seg L, SellOp<T> A, Part P, const T
   const bool done = S.done;
   for_rows<F>(A, t, V.un, [=](int64_t row) { return TqPair<T>{V.x[row], V.d[row]}; },
               [=](int64_t row, cx<T> y, TqPair<T> a) {
-                V.x[row] = zt<T>(zd(a.a) + eta * zd(a.b));
+                V.x[row] = zt<T>(tz_axpy<F>(eta, zd(a.b), zd(a.a)));
                 if (!done) V.uh[row] = y;
               });
 }
 
 // ---------------------------------------------------------------- odd half-step
 // w -= alpha uhat; d = u' + (theta^2/alpha) eta d; partials ||w||^2, r*^H w
-template <typename T>
+template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_tq_odd1(Seg L, const TqSt* st, TqV<T> V, double* part) {
   const SumTile t = vec_tile_sums(L);
   const TqSt& S = st[t.seg];
@@ -238,8 +238,9 @@ __global__ void __launch_bounds__(kBlock) k_tq_odd1(Seg L, const TqSt* st, TqV<T
   const z_t g = (S.theta * S.theta) * cdiv(S.eta, a);
   double q[3] = {0.0, 0.0, 0.0};
   vec_rows(L, t, [&](int64_t row) {
-    const cx<T> w = zt<T>(zd(V.w[row]) - a * zd(V.uh[row]));
-    const z_t d = zd(V.un[row]) + g * zd(V.d[row]), rs = zd(V.rs[row]);
+    const z_t w0 = zd(V.w[row]), uh = zd(V.uh[row]), un = zd(V.un[row]), d0 = zd(V.d[row]), rs = zd(V.rs[row]);
+    const cx<T> w = zt<T>(tz_axmy<F>(a, uh, w0));
+    const z_t d = tz_axpy<F>(g, d0, un);
     V.w[row] = w;
     V.d[row] = zt<T>(d);
     const z_t wv = zd(w);
@@ -264,8 +265,8 @@ __global__ void __launch_bounds__(kBlock) k_tq_odd2(Seg L, TzOp Z, Part P, const
   const z_t eta = S.eta, beta = S.beta;
   vec_rows(L, t, [&](int64_t row) {
     const z_t x = zd(V.x[row]), d = zd(V.d[row]), w = zd(V.w[row]), un = zd(V.un[row]);
-    V.x[row] = zt<T>(x + eta * d);
-    V.u[row] = zt<T>(tz_pre<F>(Z, B, row, w) + beta * un);
+    V.x[row] = zt<T>(tz_axpy<F>(eta, d, x));
+    V.u[row] = zt<T>(tz_axpy<F>(beta, un, tz_pre<F>(Z, B, row, w)));
   });
 }
 
@@ -382,7 +383,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     HZ_BY_SCALING(A, k_tq_even1<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st, st_a, V, pe.raw));
     HZ_TRY(pe.close<1>(s));
     HZ_BY_FORM(A, k_tq_even2<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, st_e, V));
-    k_tq_odd1<T><<<W.nblk, kBlock, 0, s>>>(W, st_e, V, po.raw);
+    HZ_BY_SCALING(A, k_tq_odd1<T, F><<<W.nblk, kBlock, 0, s>>>(W, st_e, V, po.raw));
     HZ_TRY(po.close<3>(s));
     HZ_BY_SCALING(A, k_tq_odd2<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, st_e, st, V));
     HZ_BY_FORM(A, k_tq_odd3<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pa.raw));

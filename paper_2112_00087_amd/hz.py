@@ -267,6 +267,11 @@ class Helmholtz:
             return torch.zeros(self.n, dtype=torch.complex128, device=self.device)
         return torch.as_tensor(x, dtype=torch.complex128, device=self.device).contiguous()
 
+    def _new(self):
+        """A vector that the library writes whole."""
+        import torch
+        return torch.empty(self.n, dtype=torch.complex128, device=self.device)
+
     def close(self):
         if getattr(self, "ctx", None):
             lib().hz_destroy(self.ctx)
@@ -328,12 +333,12 @@ class Helmholtz:
 
     def apply(self, x, out=None):
         x = self._vec(x)
-        y = self._vec() if out is None else out
+        y = self._new() if out is None else out
         check(lib().hz_apply(self.ctx, _dev(x, x.dtype), _dev(y, y.dtype)), False)
         return y
 
     def diag(self):
-        d = self._vec()
+        d = self._new()
         check(lib().hz_get_diag(self.ctx, _dev(d, d.dtype)), False)
         return d
 
