@@ -365,6 +365,14 @@ inline const Seg& prod_seg(const SellOp<T>& A, const Seg& L) { return A.tz.on ? 
     else { constexpr int F = kFormComplex; __VA_ARGS__; }                    \
   } while (0)
 
+// Run the statement with F set to the operator's stored form.
+#define HZ_BY_STORED(A, ...)                                                 \
+  do {                                                                       \
+    if ((A).val) { constexpr int F = kFormComplex; __VA_ARGS__; }            \
+    else if ((A).st) { constexpr int F = kFormStencil; __VA_ARGS__; }        \
+    else { constexpr int F = kFormSplit; __VA_ARGS__; }                      \
+  } while (0)
+
 // Run the statement with F set to the operator's storage form.
 #define HZ_BY_FORM(A, ...)                                                   \
   do {                                                                       \
