@@ -1315,18 +1315,14 @@ int launch_tz(hipStream_t stream, int chunks, int64_t nrows, const RowOp<T>& A, 
               cx<T>* Y) {
   const TwOp& W = A.tw;
   const int64_t n = int64_t(W.nx) * W.ny * W.nz;
-  if (nrows > n) {
-    const int64_t tail = (nrows - n) << LS;
-    k_zero_tail<T><<<ceil_div(tail, kBlock), kBlock, 0, stream>>>(tail, Y + (n << LS));
-    HZ_HIP(hipGetLastError());
-  }
+  const int64_t tail = (nrows - n) << LS;
   const int npx = ceil_div(W.nx, kTwI * (kWave >> LS) * kTwWaves), npy = ceil_div(W.ny, kTwJ);
   const int zc = ceil_div(W.nz, std::min(chunks, W.nz));
   const int64_t nblk = int64_t(npx) * npy * ceil_div(W.nz, zc);
   if (nblk > INT32_MAX) return hz_fail(HZ_ERR_INVALID, "tensor product grid too large");
   const dim3 grid = dim3(unsigned(nblk)), block = dim3(kTwWaves * kWave);
-  if (W.eta) k_spmm_tz<T, LS, true><<<grid, block, 0, stream>>>(W, npx, npy, zc, kc, Z, Y);
-  else k_spmm_tz<T, LS, false><<<grid, block, 0, stream>>>(W, npx, npy, zc, kc, Z, Y);
+  if (W.eta) k_spmm_tz<T, LS, true><<<grid, block, 0, stream>>>(W, npx, npy, zc, tail, kc, Z, Y);
+  else k_spmm_tz<T, LS, false><<<grid, block, 0, stream>>>(W, npx, npy, zc, tail, kc, Z, Y);
   HZ_HIP(hipGetLastError());
   return HZ_OK;
 }

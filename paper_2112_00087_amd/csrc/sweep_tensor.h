@@ -16,14 +16,15 @@
 // the frequency enters through m_c and, on the wall nodes, i k_c beta.  In
 // complex128 Kx x is formed from differences (its rows sum to zero but for the
 // walls), so it rounds relative to the result; FP64 sums of complex64 vectors
-// need no such care.  The product is bound by the block's read and write (67 us of copy at 80x48x40
-// and 64 columns, where it takes 92; the stencil form took 163 us, streaming
-// 27 pairs a row through the broadcast unit); the patch is 2 x 2 because its
-// 4 rows in 16 loads (4 from L1 / L2 per row, against 9 in the stencil form)
-// still leave two waves per SIMD with the next plane's loads in flight.
-// At few columns it is a chain of plane steps: 13 : 126 us at 4 columns,
-// 10.8 : 13.4 us at 37x25x19 and 13 columns.  With an absorption field
-// 122 : 201 us at 80x48x40 and 64 columns.
+// need no such care.  The product is bound by the block's read and write
+// (67 us of copy at 80x48x40 and 64 columns, where it takes 92; the stencil
+// form took 163 us, streaming 27 pairs a row through the broadcast unit); the
+// patch is 2 x 2 because its 4 rows in 16 loads (4 from L1 / L2 per row,
+// against 9 in the stencil form) still leave two waves per SIMD with the next
+// plane's loads in flight.  With an absorption field 122 : 201 us there.
+// On small blocks the march is a chain of load latencies: 13 : 126 us at
+// 80x48x40 and 4 columns, 10.8 : 13.4 us at 37x25x19 and 13.  (One plane a
+// wave with all its loads at once took 11.2 us there, and 6.9 : 7.3 us at 4.)
 // Arithmetic is FP64 for both vector types.
 #pragma once
 
@@ -44,11 +45,19 @@ __device__ __forceinline__ void tw_wall(z_t& acc, double k, z_t beta, z_t v) {
   cfma(acc, z_t{-k * beta.im, k * beta.re}, v);
 }
 
+// The rows of the padding beyond the box's nodes stay zero.
+template <typename T>
+__device__ __forceinline__ void tw_zero_tail(int64_t n, int64_t tail, cx<T>* __restrict__ Y) {
+  for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < tail; e += int64_t(gridDim.x) * blockDim.x)
+    Y[n + e] = cx<T>{T(0), T(0)};
+}
+
 template <typename T, int LS, bool ETA>
 __global__ void __launch_bounds__(kTwWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
-    k_spmm_tz(TwOp A, int npx, int npy, int zc, const double* __restrict__ kc, const cx<T>* __restrict__ X,
-              cx<T>* __restrict__ Y) {
+    k_spmm_tz(TwOp A, int npx, int npy, int zc, int64_t tail, const double* __restrict__ kc,
+              const cx<T>* __restrict__ X, cx<T>* __restrict__ Y) {
   constexpr int S = 1 << LS, G = kWave >> LS;
+  tw_zero_tail((int64_t(A.nx) * A.ny * A.nz) << LS, tail, Y);
   constexpr bool AHEAD = LS == 6 && !ETA;
   const int lane = threadIdx.x & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
