@@ -75,6 +75,7 @@ struct DDData {
   int64_t nsrow = 0;
   DevBuf g2r_ptr, g2r_row;           // glue: stacked rows of every global node
   DevBuf l2g, winv;                  // stacked row -> global node, 1 / multiplicity
+  std::unique_ptr<TensorDev> tz;     // tensor form of the stacked boxes (with the context's)
   double alpha_k = -1.0;             // k and coefficients the operator was formed for
   std::complex<double> alpha_lo, alpha_hi;
 };
@@ -269,6 +270,30 @@ int build_dd(hz_ctx ctx, DDData* D) {
   HZ_TRY(up(ctx, D->diag, dpos));
   HZ_TRY(up(ctx, D->l2g, l2g));
   HZ_TRY(up(ctx, D->winv, winv));
+  if (ctx->tz) {
+    // the subdomains of a tensor-product box are such boxes; interface terms
+    // are corner terms like the walls'
+    std::vector<TensorGrid> grids(D->nsub);
+    std::vector<int64_t> r0, nr;
+    std::vector<double> eta;
+    for (int s = 0; s < D->nsub; ++s) {
+      const DDSub& U = D->subs[s];
+      for (int d = 0; d < 3; ++d) {
+        const auto at = ctx->tgrid.c[d].begin() + U.lo[d];
+        grids[s].c[d].assign(at, at + U.ln[d] + 1);
+      }
+      r0.push_back(U.row_off);
+      nr.push_back(U.nrows);
+      if (D->eta)
+        for (int64_t k = 0; k < U.ln[2]; ++k)
+          for (int64_t j = 0; j < U.ln[1]; ++j)
+            for (int64_t i = 0; i < U.ln[0]; ++i)
+              eta.push_back(ctx->eta_field[(i + U.lo[0]) + nx * ((j + U.lo[1]) + ny * (k + U.lo[2]))]);
+    }
+    D->tz.reset(new TensorDev());
+    HZ_TRY(tensor_build(ctx, grids, r0, nr, "ddtz", D->tz.get()));
+    HZ_TRY(tensor_eta(ctx, D->tz.get(), D->eta ? eta.data() : nullptr, int64_t(eta.size())));
+  }
   {
     // split form (the global operator's layout, section of ctx_upload)
     const char* env = std::getenv("HZ_SPLIT");
@@ -482,6 +507,23 @@ int form_dd_operator(hz_ctx ctx, DDData* D, std::complex<double> a_lo, std::comp
                      bool want32) {
   const double k = ctx->k;
   const std::complex<double> ik(0.0, k);
+  if (D->tz) {
+    std::vector<TzCorner> corner(D->nsub, TzCorner{});
+    for (int s = 0; s < D->nsub; ++s)
+      for (int w = 0; w < 6; ++w) {
+        const DDSub& U = D->subs[s];
+        const int d = w / 2;
+        const bool wall = w % 2 ? U.lo[d] + U.ln[d] == ctx->elems[d] : U.lo[d] == 0;
+        std::complex<double> v = k > 0.0 ? (w % 2 ? a_lo : a_hi) : 0.0;
+        if (wall) v = ctx->tgrid.tag[w] >= 0 ? ik * ctx->beta[ctx->tgrid.tag[w]] : 0.0;
+        corner[s].v[w] = z_t{v.real(), v.imag()};
+      }
+    HZ_TRY(tensor_tables(ctx, D->tz.get(), corner, k * k));
+    D->alpha_k = k;
+    D->alpha_lo = a_lo;
+    D->alpha_hi = a_hi;
+    return HZ_OK;
+  }
   const std::complex<double> b_lo = (k > 0.0) ? a_lo / ik : 0.0, b_hi = (k > 0.0) ? a_hi / ik : 0.0;
   const int64_t nbe = int64_t(D->bmass.size()) / NTAG;
   std::vector<z_t> Bb(std::max<int64_t>(nbe, 1), z_t{0.0, 0.0});
@@ -629,13 +671,15 @@ struct DDRun {
     SellOp<double> A64;
     A64.ptr = D->sptr.as<int>();
     A64.col = D->scol.as<int>();
-    if (D->split) split_op(D->R.as<double>(), D->I.as<double>(), A64);
+    if (D->tz) A64.tz = tensor_op(*D->tz, ctx->k * ctx->k, true);
+    else if (D->split) split_op(D->R.as<double>(), D->I.as<double>(), A64);
     else A64.val = D->A.as<z_t>();
     if (mixed) {
       SellOp<float> A32;
       A32.ptr = A64.ptr;
       A32.col = A64.col;
-      if (D->split) split_op(D->R32.as<float>(), D->I32.as<float>(), A32);
+      if (D->tz) A32.tz = A64.tz;
+      else if (D->split) split_op(D->R32.as<float>(), D->I32.as<float>(), A32);
       else A32.val = D->A32.as<c_t>();
       IrOut io;
       HZ_TRY(ir_run(ctx, D->S, A64, A32, rhs, u, lo, &io, "dd"));
@@ -653,6 +697,7 @@ struct DDRun {
       local_mv += mx;
     }
     nlocal += 1;
+    if (D->tz) return HZ_OK;           // u is the solution itself
     k_dd_unscale<<<ceil_div(nr, kBlock), kBlock, 0, s>>>(nr, D->dinv.as<z_t>(), u);
     HZ_HIP(hipGetLastError());
     return HZ_OK;
