@@ -536,14 +536,15 @@ __global__ void __launch_bounds__(kBlock) k_update(Seg L, TzOp Z, const GmSt* st
   u[t.row] = ccast<T>(acc);
 }
 
-// ---- one small system in the tensor form (few_blocks)
+// ---- one small system in the tensor form (few_cycle)
 // A step of the path above is seven launches there, each a few us of latency.
 // Here it is four: the sums are added by the kernel that needs them, and the
 // Givens step of a column runs in a block of its own beside the next column's
 // product.  A block takes 64 rows with four threads each (a quarter of the
 // basis per thread, 16 rows a wave), so 3,003 rows are 47 blocks whose loads
-// are all in flight at once.  Measured at 21x13x11 nodes, m = 30: 53 -> 26 us
-// a step.
+// are all in flight at once.  Measured at 21x13x11 nodes, m = 30: 33 -> 24 us of
+// kernels a step; a solve of 857 steps 46 ms with the seven launches, 29 ms with
+// these replayed as a graph.
 constexpr int kFewRows = 64, kFewParts = kBlock / kFewRows;
 constexpr int kFewBlocks = 256;      // at most; four partials a lane
 constexpr int kFewMaxM = 56;         // basis vectors per thread: 14

@@ -3,9 +3,10 @@
 // Row layout.  A solve works on one system, or on a batch of independent
 // systems ("segments") stacked one after the other, each padded to a whole
 // number of 256-row blocks.  Every vector kernel runs one block per 256 rows,
-// so each block belongs to exactly one segment; reductions write one partial
-// per block and a finalize kernel (one block per segment) sums that segment's
-// partials in block order.  Sums are therefore reproducible bit for bit, and
+// so each block belongs to exactly one segment (in the tensor form a vector
+// kernel's block takes a run of 256-row tiles); reductions write one partial
+// per block, and the kernel that needs the sum (advance), or one block per
+// segment, adds that segment's partials in block order.  Sums are therefore reproducible bit for bit, and
 // every segment carries its own Krylov scalars and convergence flag: a batch
 // of subdomain solves advances in lock-step but each one is its own Krylov
 // iteration.  Padding rows hold zero matrix rows and zero vector entries.

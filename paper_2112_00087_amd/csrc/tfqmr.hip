@@ -9,17 +9,20 @@
 //   odd:   w -= alpha uhat;  d = u' + (theta^2/alpha) eta d;  theta, c, tau, eta as above
 //          x += eta d;  rho' = r*^H w, beta = rho'/rho;  u = w + beta u'
 //          v = beta uhat + beta^2 v + B u;  uhat = B u;  alpha = rho' / r*^H v
-// Kernels: 3 vector and 2 product (with fused dot) per pair.  The scalar
-// steps run at the start of the kernel that needs them (advance), on a state
-// that moves through three slots.  In the tensor form u, u', d and x are kept scaled by D^-1 (x
-// is the solution itself), so only w and v are scaled where they enter u and
-// u' and the product's inputs need no pass of their own.  u' lives in its own buffer for the odd half-step (it
-// is never copied back into u), and the odd product reads B u' from uhat
-// and writes B u over it row by row, so v needs no staging buffer: 29
-// vector passes per pair.  A segment whose quasi-residual bound tau sqrt(m+1)
-// meets the target makes its last x update in the kernel that finds it and stops; the host confirms
-// with the true residual (restarting a segment that has not converged), and
-// restarts segments that broke down (r*^H v or rho zero).
+// Kernels: 3 vector and 2 product (with fused dot) per pair; in the tensor form
+// the odd update rides on the even product, 2 vector and 2 product kernels.
+// The scalar steps run at the start of the kernel that needs them (advance),
+// on a state that moves through three slots.  In the tensor form u, u', d and
+// x are kept scaled by D^-1 (x is the solution itself), so only w and v are
+// scaled where they enter u and u' and the product's inputs need no pass of
+// their own.  u' lives in its own buffer for the odd half-step (it is never
+// copied back into u), and the odd product reads B u' from uhat and writes B u
+// over it row by row, so v needs no staging buffer: 32 vector passes per pair
+// with the products' own, 29 in the tensor form.  A segment whose
+// quasi-residual bound tau sqrt(m+1) meets the target makes its last x update
+// in the kernel that finds it and stops; the host confirms with the true
+// residual (restarting a segment that has not converged), and restarts
+// segments that broke down (r*^H v or rho zero).
 #include <chrono>
 
 #include "ops.h"
