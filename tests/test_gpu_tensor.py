@@ -372,3 +372,18 @@ def test_schwarz_subdomains(P, monkeypatch, parts, inner, eta, precision):
         x.append(p)
         m.close()
     assert float((x[0] - x[1]).norm()) <= 2e-6 * float(x[1].norm())
+
+
+def test_apply_in_place(P):
+    """y = A x into x itself and into a vector that overlaps x."""
+    rng = np.random.default_rng(31)
+    mesh = graded_box(20, 9, 8, seed=3)
+    m = P.Helmholtz(mesh, _beta(rng))
+    m.set_frequency(FREQ)
+    buf = torch.as_tensor(rng.standard_normal(m.n + 5) + 1j * rng.standard_normal(m.n + 5), device="cuda")
+    for x, y in ((slice(0, m.n), slice(0, m.n)), (slice(0, m.n), slice(5, m.n + 5)), (slice(5, m.n + 5), slice(0, m.n))):
+        b = buf.clone()
+        want = m.apply(b[x].clone())
+        m.apply(b[x], out=b[y])
+        assert torch.equal(torch.view_as_real(b[y]), torch.view_as_real(want))
+    m.close()
