@@ -111,31 +111,36 @@ int hz_assemble(const hz_mesh* mesh, const hz_c128* beta, const double* eta, voi
 int hz_set_params(hz_ctx ctx, const hz_c128* beta, const double* eta) {
   HZ_GUARD_BEGIN
   HZ_TRY(check_ctx(ctx));
-  if (beta) {
-    for (int w = 0; w < 6; ++w)
+  // everything is checked before anything of the context changes
+  std::vector<std::complex<double>> b(ctx->beta);
+  if (beta)
+    for (int w = 0; w < 6; ++w) {
       if (!std::isfinite(beta[w].re) || !std::isfinite(beta[w].im)) return hz_fail(HZ_ERR_INVALID, "beta not finite");
-    for (int w = 0; w < 6; ++w) ctx->beta[w] = std::complex<double>(beta[w].re, beta[w].im);
-  }
-  if (eta) {
-    if (ctx->tz) {   // the matrix itself is assembled when something needs it
-      for (int64_t e = 0; e < ctx->h.ne; ++e)
-        if (!std::isfinite(eta[e])) return hz_fail(HZ_ERR_INVALID, "eta[%lld] is not finite", (long long)e);
-    } else {
-      HZ_TRY(host_assemble_meta(&ctx->h, eta));
+      b[w] = std::complex<double>(beta[w].re, beta[w].im);
     }
-    ctx->meta_host = !ctx->tz;
-    ctx->have_eta = true;
-    ctx->eta_field.assign(eta, eta + ctx->h.ne);
+  std::vector<double> field;
+  if (eta) {
+    for (int64_t e = 0; e < ctx->h.ne; ++e)
+      if (!std::isfinite(eta[e])) return hz_fail(HZ_ERR_INVALID, "eta[%lld] is not finite", (long long)e);
+    field.assign(eta, eta + ctx->h.ne);
   }
   HZ_HIP(hipStreamSynchronize(ctx->stream));
-  HZ_TRY(ctx_upload_params(ctx));
+  ctx->beta.swap(b);
+  if (eta) {
+    ctx->eta_field.swap(field);
+    ctx->have_eta = true;
+    ctx->meta_host = false;   // assembled when something needs it: below, or on demand in the tensor form
+  }
+  // (from here on no earlier operator or sweep is used again; an upload that
+  // fails is made up for before the next one is formed)
+  ctx->params_dev = false;
   ctx->params_version += 1;
   ctx->have_freq = false;
   ctx->scaled = -1;
   ctx->have_A32 = false;
   ctx->have_split = ctx->have_split32 = false;
   ctx->have_stencil = ctx->have_stencil32 = false;
-  return HZ_OK;
+  return ctx_upload_params(ctx);
   HZ_GUARD_END
 }
 
@@ -143,6 +148,7 @@ int hz_set_frequency(hz_ctx ctx, double freq_hz) {
   HZ_GUARD_BEGIN
   HZ_TRY(check_ctx(ctx));
   if (!std::isfinite(freq_hz) || freq_hz < 0.0) return hz_fail(HZ_ERR_INVALID, "frequency must be finite and >= 0");
+  HZ_TRY(ctx_upload_params(ctx));
   ctx->freq = freq_hz;
   ctx->k = 2.0 * M_PI * freq_hz / ctx->c;
   HZ_TRY(op_set_frequency(ctx, ctx->k, 1, false));

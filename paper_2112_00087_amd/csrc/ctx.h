@@ -168,6 +168,7 @@ struct hz_ctx_s {
   std::vector<std::complex<double>> beta;   // [6]
   bool have_eta = false;
   int params_version = 0;            // bumped by hz_set_params
+  bool params_dev = false;           // the device holds beta and the absorption field
 
   // row-wise (CSR) copy of the real parts for the multi-vector product of
   // the frequency sweep, built on first use for a params_version

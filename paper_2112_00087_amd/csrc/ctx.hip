@@ -98,6 +98,7 @@ int put(hz_ctx ctx, DevBuf& b, const T* src, size_t count) {
 }  // namespace
 
 int ctx_upload_params(hz_ctx ctx) {
+  if (ctx->params_dev) return HZ_OK;
   const HostAsm& a = ctx->h;
   const int64_t nbe = int64_t(a.bpos.size());
   std::vector<z_t> Bb(std::max<int64_t>(nbe, 1), z_t{0.0, 0.0});
@@ -113,8 +114,10 @@ int ctx_upload_params(hz_ctx ctx) {
   }
   HZ_TRY(put(ctx, ctx->d_Bb, Bb.data(), Bb.size()));
   ctx->meta_dev = false;
-  if (ctx->tz) return tensor_eta(ctx, ctx->tz.get(), ctx->have_eta ? ctx->eta_field.data() : nullptr, a.ne);
-  return ctx_need_meta(ctx, true);
+  if (ctx->tz) HZ_TRY(tensor_eta(ctx, ctx->tz.get(), ctx->have_eta ? ctx->eta_field.data() : nullptr, a.ne));
+  else HZ_TRY(ctx_need_meta(ctx, true));
+  ctx->params_dev = true;
+  return HZ_OK;
 }
 
 int ctx_need_meta(hz_ctx ctx, bool on_device) {

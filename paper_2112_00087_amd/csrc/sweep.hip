@@ -1508,6 +1508,7 @@ int build_sweep_data(hz_ctx ctx, SweepData* D) {
       bnd[row].push_back({a.col[pos], z_t{re, im}});
     }
   }
+  HZ_TRY(ctx_upload_params(ctx));
   if (ctx->tz) {
     HZ_TRY(tensor_axes(ctx, *ctx->tz, &D->tztab));
     TwOp& W = D->tw;

@@ -278,7 +278,7 @@ int tensor_diag(hz_ctx ctx, const TensorDev& D, double k2, z_t* d, z_t* dinv) {
 }
 
 int tensor_eta(hz_ctx ctx, TensorDev* D, const double* eta_host, int64_t count) {
-  D->have_eta = eta_host != nullptr;
+  D->have_eta = false;
   if (!eta_host) return HZ_OK;
   HZ_TRY(put(ctx, D->eta, eta_host, size_t(count)));
   HZ_TRY(put<double>(ctx, D->ed, nullptr, size_t(D->lay.nrows)));
@@ -286,6 +286,7 @@ int tensor_eta(hz_ctx ctx, TensorDev* D, const double* eta_host, int64_t count) 
     k_tz_eta_diag<<<ceil_div(D->segs[s].nrows, kBlock), kBlock, 0, ctx->stream>>>(
         D->segs[s], D->coord.as<double>() + D->cat[s], D->eta.as<double>(), D->ed.as<double>());
   HZ_HIP(hipGetLastError());
+  D->have_eta = true;
   return HZ_OK;
 }
 
