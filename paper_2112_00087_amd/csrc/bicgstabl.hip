@@ -151,8 +151,7 @@ __global__ void __launch_bounds__(kBlock) k_bl_report(Part P, const BlSt* in, Bl
 }
 // At a restart the slot a cycle starts from takes up the pending sums.
 __global__ void __launch_bounds__(kBlock) k_bl_settle(Part P, BlSt* st, int all) {
-  advance_alone<3>(P, st, st, bl_pending, bl_cycle);
-  if (threadIdx.x == 0) st[blockIdx.x].restart = all ? 1 : st[blockIdx.x].brk;
+  settle<3>(P, st, all, bl_pending, bl_cycle);
 }
 
 // ---------------------------------------------------------------- restart

@@ -453,6 +453,18 @@ __device__ __forceinline__ void advance_alone(const Part& P, const St* in, St* o
   advance<NQ>(P, in, out, t, true, cond, fin);
 }
 
+// Takes up a segment's pending sums (fin) in place and sets which segments
+// restart: all of them, or those that broke down.  Both in the one scalar step,
+// on the state in LDS: the words of the stored state are written by different
+// threads, so none may be read or written again after advance.
+template <int NQ, class St, class Cond, class Fin>
+__device__ __forceinline__ void settle(const Part& P, St* st, int all, Cond pending, Fin fin) {
+  advance_alone<NQ>(P, st, st, [](const St&) { return true; }, [=](St& S, const double* tot) {
+    if (pending(S)) fin(S, tot);
+    S.restart = all ? 1 : S.brk;
+  });
+}
+
 // Vector layout: block b works on rows [blk_row[b], blk_row[b + 1]) of one
 // segment, a whole number of 256-row tiles.
 __device__ __forceinline__ Tile vec_tile(const Seg& L) {

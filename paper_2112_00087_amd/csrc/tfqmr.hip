@@ -144,8 +144,7 @@ __global__ void __launch_bounds__(kBlock) k_tq_resid_fin(Part P, TqSt* st) {
 // At a restart the slot a pair starts from takes up the pending sums; the
 // segments that restart are all of them, or those that broke down.
 __global__ void __launch_bounds__(kBlock) k_tq_settle(Part P, TqSt* st, int all) {
-  advance_alone<2>(P, st, st, tq_pending, tq_alpha);
-  if (threadIdx.x == 0) st[blockIdx.x].restart = all ? 1 : st[blockIdx.x].brk;
+  settle<2>(P, st, all, tq_pending, tq_alpha);
 }
 __global__ void __launch_bounds__(kBlock) k_tq_report(Part P, const TqSt* in, TqSt* out) {
   advance_alone<2>(P, in, out, tq_pending, tq_alpha);
