@@ -464,6 +464,11 @@ int hz_spmv_bytes(hz_ctx ctx, int32_t precision, int32_t format, int64_t* bytes)
 int hz_sizes(hz_ctx ctx, int64_t* n_nodes, int64_t* n_elems, int64_t* nnz,
              int64_t* device_bytes);
 
+/* Runs of solver iterations that this context has captured as HIP graphs and
+ * replayed so far (HZ_GRAPH=0 in the environment when the context is created:
+ * none).  Host results. */
+int hz_replay_counts(hz_ctx ctx, int64_t* captures, int64_t* replays);
+
 /* Host-only (no GPU call): the internal numbering hz_assemble uses for this
  * mesh's order and sigma fields.  Reads n_nodes, n_elems, hex, elem_type,
  * order and sigma; writes perm[n_nodes] (host), perm[p] = the mesh node of internal

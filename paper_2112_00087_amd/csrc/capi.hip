@@ -498,6 +498,13 @@ int hz_sizes(hz_ctx ctx, int64_t* n_nodes, int64_t* n_elems, int64_t* nnz, int64
   return HZ_OK;
 }
 
+int hz_replay_counts(hz_ctx ctx, int64_t* captures, int64_t* replays) {
+  if (!ctx) return hz_fail(HZ_ERR_INVALID, "ctx is NULL");
+  if (captures) *captures = ctx->n_captures;
+  if (replays) *replays = ctx->n_replays;
+  return HZ_OK;
+}
+
 void hz_destroy(hz_ctx ctx) {
   if (!ctx) return;
   int dev = -1;

@@ -89,7 +89,7 @@ struct TensorDev {
   std::vector<TzSeg> segs;
   std::vector<int64_t> cat;          // coordinates of each box in coord
   SegHost lay;                       // blocks of the product kernels
-  DevBuf coord, tab, dx, lt, dsegs, eta, ed;
+  DevBuf coord, tab, dx, lt, dsegs, k2, eta, ed;
   bool have_eta = false;
 };
 
@@ -186,6 +186,7 @@ struct hz_ctx_s {
   std::map<std::string, Replay> replays;        // per solver tag
   hipStream_t cap = nullptr;         // capture stream of the replays
   bool graphs_on = true;             // HZ_GRAPH=0 in the environment turns them off
+  int64_t n_captures = 0, n_replays = 0;
   void* pinned = nullptr;            // small pinned host buffer for status reads
   size_t pinned_bytes = 0;
 

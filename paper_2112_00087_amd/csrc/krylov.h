@@ -80,7 +80,7 @@ struct TzOp {
   const TzLine* lt = nullptr;
   const double* eta = nullptr;    // absorption field per element (NULL: none)
   const double* ed = nullptr;     // its mass diagonal per row
-  double k2 = 0.0;
+  const double* k2 = nullptr;     // [1], beside the tables (read with an absorption field only)
   Seg lp;                         // layout of the product kernels
 };
 struct TzCorner {                 // what each wall adds to its corner of the 1-D stiffness

@@ -87,17 +87,17 @@ bool tensor_detect(const HostAsm& a, const int32_t elems[3], TensorGrid* g);
 // Layout, tables and buffers of stacked boxes; rows of box s: [row0[s], row0[s] + nrows[s]).
 int tensor_build(hz_ctx ctx, const std::vector<TensorGrid>& grids, const std::vector<int64_t>& row0,
                  const std::vector<int64_t>& nrows, const std::string& name, TensorDev* D);
-// The tables for mass coefficient m and the walls' corner terms (stream-ordered).
-int tensor_tables(hz_ctx ctx, TensorDev* D, const std::vector<TzCorner>& corners, double m);
+// The tables for mass coefficient m, k^2 and the walls' corner terms (stream-ordered).
+int tensor_tables(hz_ctx ctx, TensorDev* D, const std::vector<TzCorner>& corners, double m, double k2);
 int tensor_axes(hz_ctx ctx, const TensorDev& D, DevBuf* tab);   // without frequency and walls
 int tensor_diag(hz_ctx ctx, const TensorDev& D, double k2, z_t* d, z_t* dinv);
 int tensor_eta(hz_ctx ctx, TensorDev* D, const double* eta_host, int64_t count);
-TzOp tensor_op(const TensorDev& D, double k2, bool scale);
+TzOp tensor_op(const TensorDev& D, bool scale);
 
 // The operator the solvers use: the tensor form, else the stencil form, else
 // the split form, when formed.
 inline TzOp op_tensor(hz_ctx ctx) {
-  return tensor_op(*ctx->tz, ctx->k * ctx->k, ctx->scaled == HZ_JACOBI);
+  return tensor_op(*ctx->tz, ctx->scaled == HZ_JACOBI);
 }
 inline SellOp<double> op_A(hz_ctx ctx) {
   if (ctx->tz) {
@@ -189,8 +189,10 @@ struct StatePoll {
 // The capture is kept in the context under the solver's tag together with
 // every argument its kernels take (ReplayKey), so a later solve replays it
 // only if it would launch exactly that; there is one per tag, the next
-// differing solve replaces it.  Only kernels are captured, and a capture
-// that fails leaves the solver launching them one by one.
+// differing solve replaces it.  What a frequency or new parameters change is
+// in device memory at the same addresses, so a loop over frequencies captures
+// once.  Only kernels are captured, and a capture that fails leaves the solver
+// launching them one by one.
 struct ReplayKey {
   std::string s;
   template <typename V>
@@ -237,8 +239,10 @@ int replay(hz_ctx ctx, const std::string& tag, const ReplayKey& key, Body body, 
       return HZ_OK;
     }
     R.key = key.s;
+    ++ctx->n_captures;
   }
   HZ_HIP(hipGraphLaunch(R.exec, ctx->stream));
+  ++ctx->n_replays;
   *ran = true;
   return HZ_OK;
 }

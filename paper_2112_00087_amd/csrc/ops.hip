@@ -118,7 +118,7 @@ int op_set_frequency(hz_ctx ctx, double k, int scale, bool want32) {
       corner[0].v[w] = z_t{-k * b.imag(), k * b.real()};
     }
   ctx->have_stored = false;
-  HZ_TRY(tensor_tables(ctx, ctx->tz.get(), corner, mass_coefficient(k, ctx->h.gls_h)));
+  HZ_TRY(tensor_tables(ctx, ctx->tz.get(), corner, mass_coefficient(k, ctx->h.gls_h), k * k));
   return tensor_diag(ctx, *ctx->tz, k * k, ctx->d_d.as<z_t>(), ctx->d_dinv.as<z_t>());
 }
 

@@ -518,7 +518,7 @@ int form_dd_operator(hz_ctx ctx, DDData* D, std::complex<double> a_lo, std::comp
         if (wall) v = ctx->tgrid.tag[w] >= 0 ? ik * ctx->beta[ctx->tgrid.tag[w]] : 0.0;
         corner[s].v[w] = z_t{v.real(), v.imag()};
       }
-    HZ_TRY(tensor_tables(ctx, D->tz.get(), corner, k * k));
+    HZ_TRY(tensor_tables(ctx, D->tz.get(), corner, k * k, k * k));
     D->alpha_k = k;
     D->alpha_lo = a_lo;
     D->alpha_hi = a_hi;
@@ -671,7 +671,7 @@ struct DDRun {
     SellOp<double> A64;
     A64.ptr = D->sptr.as<int>();
     A64.col = D->scol.as<int>();
-    if (D->tz) A64.tz = tensor_op(*D->tz, ctx->k * ctx->k, true);
+    if (D->tz) A64.tz = tensor_op(*D->tz, true);
     else if (D->split) split_op(D->R.as<double>(), D->I.as<double>(), A64);
     else A64.val = D->A.as<z_t>();
     if (mixed) {

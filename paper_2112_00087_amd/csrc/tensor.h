@@ -140,6 +140,8 @@ __device__ __forceinline__ void tz_wave(const TzOp& A, const TzSeg& S, int wave,
 #pragma unroll
     for (int t = 0; t < kTzJ; ++t)
       if (in_z(c + 1) && in_j(t + 1) && outx) ax[c][t] = aux(row_of(c + 1, t + 1));
+  double k2 = 0.0;
+  if constexpr (EXT) k2 = *tz_const(A.k2);
   TzAxis cy[kTzJ], cz[kTzZ];
 #pragma unroll
   for (int t = 0; t < kTzJ; ++t) cy[t] = tz_uniform(A.tab, S.yt + (j0 + t < NY ? j0 + t : NY - 1));
@@ -203,7 +205,7 @@ __device__ __forceinline__ void tz_wave(const TzOp& A, const TzSeg& S, int wave,
             tz_add(ar, el, sv);
           }
         }
-        const double wr = A.k2 * cx_.mh, wl = A.k2 * cx_.ml;
+        const double wr = k2 * cx_.mh, wl = k2 * cx_.ml;
         tz_addi(own, 2.0 * wr, al);
         tz_addi(own, 2.0 * wl, ar);
         tz_addi(to_r, wr, al);
@@ -244,7 +246,7 @@ __device__ __forceinline__ z_t tz_diag_at(const TzOp& A, const TzSeg& S, int64_t
   }
   const TzLine d = A.dx[S.xt + i], c = A.lt[S.lt + l];
   z_t v = {fma(d.a, c.a, d.b * c.b), fma(d.c, c.a, d.b * c.c)};
-  if (A.ed) v.im = fma(A.k2, A.ed[row], v.im);
+  if (A.ed) v.im = fma(*tz_const(A.k2), A.ed[row], v.im);
   return v;
 }
 // 1 / v: the hardware estimate and two Newton steps (full FP64 precision)

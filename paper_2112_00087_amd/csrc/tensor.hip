@@ -36,11 +36,13 @@ __device__ __forceinline__ TzAxis minus_mass(TzAxis a, double m) {
   return a;
 }
 
-// Axis tables (x, y with K - m M, z) and the line table of one box; c holds
-// the axes' coordinates one after the other.
-__global__ void k_tz_tables(TzSeg S, const double* __restrict__ c, TzCorner w, double m, TzAxis* __restrict__ tab,
-                            TzLine* __restrict__ dx, TzLine* __restrict__ lt) {
+// Axis tables (x, y with K - m M, z) and the line table of one box, and k^2; c
+// holds the axes' coordinates one after the other.
+__global__ void k_tz_tables(TzSeg S, const double* __restrict__ c, TzCorner w, double m, double k2,
+                            TzAxis* __restrict__ tab, TzLine* __restrict__ dx, TzLine* __restrict__ lt,
+                            double* __restrict__ k2_out) {
   const int t = blockIdx.x * kBlock + threadIdx.x;
+  if (t == 0) *k2_out = k2;
   const double *cx = c, *cy = c + S.nx, *cz = c + S.nx + S.ny;
   const int na = S.nx + S.ny + S.nz;
   if (t < S.nx) {
@@ -241,6 +243,7 @@ int tensor_build(hz_ctx ctx, const std::vector<TensorGrid>& grids, const std::ve
   HZ_TRY(put<TzLine>(ctx, D->dx, nullptr, tab));
   HZ_TRY(put<TzLine>(ctx, D->lt, nullptr, lines));
   HZ_TRY(put(ctx, D->dsegs, D->segs.data(), D->segs.size()));
+  HZ_TRY(put<double>(ctx, D->k2, nullptr, 1));
   D->lay.nseg = ns;
   D->lay.nblk = blk;
   D->lay.nrows = rows;
@@ -249,12 +252,13 @@ int tensor_build(hz_ctx ctx, const std::vector<TensorGrid>& grids, const std::ve
   return seg_upload(ctx, &D->lay, name);
 }
 
-int tensor_tables(hz_ctx ctx, TensorDev* D, const std::vector<TzCorner>& corners, double m) {
+int tensor_tables(hz_ctx ctx, TensorDev* D, const std::vector<TzCorner>& corners, double m, double k2) {
   for (size_t s = 0; s < D->segs.size(); ++s) {
     const TzSeg& S = D->segs[s];
     const int count = S.nx + S.ny + S.nz + S.ny * S.nz;
-    k_tz_tables<<<ceil_div(count, kBlock), kBlock, 0, ctx->stream>>>(S, D->coord.as<double>() + D->cat[s], corners[s], m,
-                                                                    D->tab.as<TzAxis>(), D->dx.as<TzLine>(), D->lt.as<TzLine>());
+    k_tz_tables<<<ceil_div(count, kBlock), kBlock, 0, ctx->stream>>>(
+        S, D->coord.as<double>() + D->cat[s], corners[s], m, k2, D->tab.as<TzAxis>(), D->dx.as<TzLine>(),
+        D->lt.as<TzLine>(), D->k2.as<double>());
   }
   HZ_HIP(hipGetLastError());
   return HZ_OK;
@@ -290,7 +294,7 @@ int tensor_eta(hz_ctx ctx, TensorDev* D, const double* eta_host, int64_t count) 
   return HZ_OK;
 }
 
-TzOp tensor_op(const TensorDev& D, double k2, bool scale) {
+TzOp tensor_op(const TensorDev& D, bool scale) {
   TzOp o;
   o.on = D.have_eta ? 2 : 1;
   o.scale = scale;
@@ -302,7 +306,7 @@ TzOp tensor_op(const TensorDev& D, double k2, bool scale) {
   o.lt = D.lt.as<TzLine>();
   o.eta = D.have_eta ? D.eta.as<double>() : nullptr;
   o.ed = D.have_eta ? D.ed.as<double>() : nullptr;
-  o.k2 = k2;
+  o.k2 = D.k2.as<double>();
   o.lp = D.lay.dev;
   return o;
 }

@@ -120,6 +120,7 @@ def lib():
         "hz_node_order": (C.c_int, [P(hz_mesh), P(C.c_int32)]),
         "hz_layout": (C.c_int, [VP, P(C.c_int32), P(C.c_int64), P(C.c_int64), P(C.c_int64)]),
         "hz_sizes": (C.c_int, [VP, P(C.c_int64), P(C.c_int64), P(C.c_int64), P(C.c_int64)]),
+        "hz_replay_counts": (C.c_int, [VP, P(C.c_int64), P(C.c_int64)]),
         "hz_destroy": (None, [VP]),
         "hz_last_error": (C.c_char_p, []),
     }
@@ -287,6 +288,12 @@ class Helmholtz:
         a, b, c_, d = C.c_int64(), C.c_int64(), C.c_int64(), C.c_int64()
         check(lib().hz_sizes(self.ctx, C.byref(a), C.byref(b), C.byref(c_), C.byref(d)))
         return dict(n_nodes=a.value, n_elems=b.value, nnz=c_.value, device_bytes=d.value)
+
+    def replay_counts(self):
+        """(captures, replays) of solver iterations as HIP graphs so far."""
+        a, b = C.c_int64(), C.c_int64()
+        check(lib().hz_replay_counts(self.ctx, C.byref(a), C.byref(b)), False)
+        return a.value, b.value
 
     def layout(self):
         """Internal numbering (``perm[p]`` = mesh node of internal row p),
