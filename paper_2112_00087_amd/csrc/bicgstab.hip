@@ -316,6 +316,7 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
   };
 
   constexpr int kChunk = 8;          // iterations between reports
+  const bool replays = nr <= (A.tz.on ? kReplayRowsTensor : kReplayRowsStored);
   ReplayKey key;
   key.op(A).add(V).add(P).add(W).add(st).add(S.nseg);
   for (const PartBuf* b : {&pa, &po, &pn}) b->key(&key);
@@ -356,7 +357,7 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
     for (bool stop = false; !stop && left > 0;) {
       const int n_it = int(std::min<int64_t>(chunk, left));
       bool ran = false;
-      if (n_it == kChunk) HZ_TRY(replay(ctx, p, key, run_chunk, &ran));
+      if (n_it == kChunk && replays) HZ_TRY(replay(ctx, p, key, run_chunk, &ran, kReplayAfter));
       for (int it = 0; it < n_it && !ran; ++it) HZ_TRY(enqueue_iter());
       left -= n_it;
       HZ_TRY(report());

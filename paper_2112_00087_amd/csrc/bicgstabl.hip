@@ -467,6 +467,7 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
   };
 
   constexpr int kChunk = 2;          // cycles between reports
+  const bool replays = nr <= (A.tz.on ? kReplayRowsTensor : kReplayRowsStored);
   ReplayKey key;
   key.op(A).add(V).add(P).add(W).add(st).add(S.nseg).add(l);
   for (const PartBuf* b : {&pa, &pb, &pg, &pc}) b->key(&key);
@@ -511,7 +512,7 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     for (bool stop = false; !stop && left > 0;) {
       const int n_cyc = int(std::min<int64_t>(chunk, left));
       bool ran = false;
-      if (n_cyc == kChunk) HZ_TRY(replay(ctx, p, key, run_chunk, &ran));
+      if (n_cyc == kChunk && replays) HZ_TRY(replay(ctx, p, key, run_chunk, &ran, kReplayAfter));
       for (int c = 0; c < n_cyc && !ran; ++c) HZ_TRY(enqueue_cycle());
       left -= n_cyc;
       HZ_TRY(report());

@@ -99,6 +99,8 @@ struct Replay {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   int failed = 0;                    // captures that did not work
+  std::string seen_key;              // the run launched last without a capture, and how often
+  int seen = 0;
   ~Replay() { drop(); }
   void drop();
 };

@@ -921,14 +921,11 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   };
   ReplayKey key;
   key.op(A).add(f).add(u).add(L).add(P).add(st).add(G.H).add(G.cs).add(G.sn).add(G.g).add(G.y).add(G.h1).add(G.h2).add(G.vs).add(G.m).add(V).add(ld).add(in).add(pt).add(S.nseg);
-  bool first = true;
   for (;;) {
     const int mc = int(std::min<int64_t>(m, ctl.max_matvec - mv_max - 1));
     bool ran = false;
-    // (a capture pays from the second cycle on)
-    if (mc == m) HZ_TRY(replay(ctx, p, key, run_cycle, &ran, !first));
+    if (mc == m && ld <= kReplayRowsGmres) HZ_TRY(replay(ctx, p, key, run_cycle, &ran, kReplayAfterGmres));
     if (!ran) HZ_TRY(enqueue_cycle(mc));
-    first = false;
     HZ_HIP(hipMemcpyAsync(hst, st, sizeof(GmSt) * S.nseg, hipMemcpyDeviceToHost, s));
     HZ_HIP(hipStreamSynchronize(s));
     bool all_done = true;

@@ -193,6 +193,26 @@ struct StatePoll {
 // in device memory at the same addresses, so a loop over frequencies captures
 // once.  Only kernels are captured, and a capture that fails leaves the solver
 // launching them one by one.
+//
+// A capture takes 40 us (BiCGStab, 40 kernels) to 100 us (GMRES(30), 123
+// kernels) of host time and saves 10 us a chunk of 8 BiCGStab iterations and
+// 140 us a GMRES(30) cycle, so runs are captured once the same one has been
+// launched kReplayAfter times, in one solve or over several: a loop over 16
+// frequencies at 20x12x10, BiCGStab(2) to 20 products, took 7.2 ms capturing at
+// each solve's first full chunk and 6.4 ms so (6.5 without graphs), to 60 products
+// 15.1 and 14.3 ms (15.0 without), GMRES(30) to 200 products 87.3 and 75.6 ms
+// (86.4 without).
+//
+// On larger systems the device is the slower of the two and the gap between a
+// graph's kernels a little longer than between launches.  600 products,
+// launched : replayed, ms, BiCGStab / BiCGStab(2) / BiCGStab(8) / TFQMR / mixed
+// TFQMR: tensor form at 102,900 rows 9.11:8.78 9.23:8.96 12.4:12.4 9.86:9.69
+// 11.4:11.2, at 162,729 11.2:10.9 11.4:11.5 16.6:16.7 11.8:11.9 13.7:13.0, at
+// 308,050 13.0:13.2 13.6:13.9 21.4:21.2 13.3:13.6 14.2:14.4; stored forms at
+// 29,725 9.90:9.40 10.3:9.48 10.3:9.88 10.2:10.0 10.6:9.87, at 64,800 10.8:10.8
+// 11.3:11.4 13.5:13.6 11.5:11.6 10.9:10.6, at 162,729 17.0:17.0 17.3:17.6
+// 23.0:23.1 17.9:18.0 15.4:15.3.  GMRES(30), which has six launches a step:
+// 35.7:33.0 at 162,729 (tensor), 44.9:44.2 at 308,050, 35.8:35.8 at 162,729 (stored).
 struct ReplayKey {
   std::string s;
   template <typename V>
@@ -209,16 +229,23 @@ struct ReplayKey {
     return add(Z.ed).add(Z.k2).add(Z.lp);
   }
 };
-// Replays the run of body on the context's stream (capture: capturing it first
-// if need be); *ran = false if it has to be launched directly.  body(stream) launches only kernels.
+constexpr int kReplayAfter = 3, kReplayAfterGmres = 1;
+constexpr int64_t kReplayRowsTensor = 196608, kReplayRowsStored = 49152, kReplayRowsGmres = 262144;
+// Replays the run of body on the context's stream, capturing it first if the
+// same run has come up more than `after` times; *ran = false if it has to be
+// launched directly.  body(stream) launches only kernels.
 template <class Body>
-int replay(hz_ctx ctx, const std::string& tag, const ReplayKey& key, Body body, bool* ran, bool capture = true) {
+int replay(hz_ctx ctx, const std::string& tag, const ReplayKey& key, Body body, bool* ran, int after) {
   *ran = false;
   if (!ctx->graphs_on) return HZ_OK;
   Replay& R = ctx->replays[tag];
   if (R.failed > 2) return HZ_OK;
   if (!R.exec || R.key != key.s) {
-    if (!capture) return HZ_OK;
+    if (R.seen_key != key.s) {
+      R.seen_key = key.s;
+      R.seen = 0;
+    }
+    if (R.seen++ < after) return HZ_OK;
     R.drop();
     if (!ctx->cap && hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking) != hipSuccess) {
       (void)hipGetLastError();

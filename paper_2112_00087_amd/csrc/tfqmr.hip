@@ -437,6 +437,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   };
 
   constexpr int kChunk = 8;          // pairs between reports
+  const bool replays = nr <= (A.tz.on ? kReplayRowsTensor : kReplayRowsStored);
   ReplayKey key;
   key.op(A).add(V).add(P).add(W).add(st).add(S.nseg);
   for (const PartBuf* b : {&pa, &pe, &po}) b->key(&key);
@@ -480,7 +481,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     for (bool stop = false; !stop && left > 0;) {
       const int n_pair = int(std::min<int64_t>(chunk, left));
       bool ran = false;
-      if (n_pair == kChunk) HZ_TRY(replay(ctx, p, key, run_chunk, &ran));
+      if (n_pair == kChunk && replays) HZ_TRY(replay(ctx, p, key, run_chunk, &ran, kReplayAfter));
       for (int c = 0; c < n_pair && !ran; ++c) HZ_TRY(enqueue_pair());
       pairs += n_pair;
       left -= n_pair;

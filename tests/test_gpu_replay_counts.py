@@ -1,7 +1,8 @@
 """When solver iterations are captured as HIP graphs and when a kept capture is
-replayed: one capture serves a loop over frequencies and parameters.  (That
-replays give the launches' bits: test_gpu_replay.py; here also for captures kept
-from an earlier solve.)"""
+replayed: one capture serves a loop over frequencies and parameters,
+and none is made before the same run has come up a few times.  (That replays
+give the launches' bits: test_gpu_replay.py; here also for captures kept from an
+earlier solve.)"""
 import numpy as np
 import pytest
 
@@ -52,5 +53,24 @@ def test_one_capture_serves_all_frequencies(monkeypatch, form, method, kw):
         assert captures == 1 and replays > last, (step, captures, replays)
         last = replays
     assert off.replay_counts() == (0, 0)
+    for m in (on, off):
+        m.close()
+
+
+@pytest.mark.parametrize("method,kw", METHODS)
+def test_short_solves_capture_on_repetition(monkeypatch, method, kw):
+    """Two full chunks (one GMRES cycle) a solve: the first solve captures
+    nothing, a few alike make one capture."""
+    rng = np.random.default_rng(7)
+    mesh = W.box_mesh(12, 9, 8)
+    on, off = _pair(monkeypatch, mesh, 0.02 * np.ones(6), None)
+    f = torch.as_tensor(rng.standard_normal(on.n) + 0j, device="cuda")
+    for step, freq in enumerate((70.0, 85.0, 100.0)):
+        on.set_frequency(freq)
+        on.solve(f, method=method, tol=1e-14, max_matvec=9 if method == "gmres" else 48, **kw)
+        captures, replays = on.replay_counts()
+        if step == 0:
+            assert (captures, replays) == (0, 0)
+    assert captures == 1 and replays >= 1
     for m in (on, off):
         m.close()
