@@ -100,21 +100,22 @@ __device__ __forceinline__ void bi_rho(BiSt& S, const double* o) {
   S.beta = cdiv(S.rho, S.rho_old) * cdiv(S.alpha, S.omega);
 }
 
-__device__ __forceinline__ bool bi_on(const BiSt& S) { return !S.done; }
-__device__ __forceinline__ bool bi_pending(const BiSt& S) { return S.pend; }
-
-// The state after the sums formed last: in place after k_resid (the slot the
-// next iteration starts from), for the host after k_xr.
-__global__ void __launch_bounds__(kBlock) k_bi_resid(Part P, BiSt* st) {
-  advance_alone<1>(P, st, st, [](const BiSt&) { return true; }, bi_resid);
-}
-// Before a restart the slot an iteration starts from takes up the pending sums.
-__global__ void __launch_bounds__(kBlock) k_bi_settle(Part P, BiSt* st) {
-  advance_alone<3>(P, st, st, bi_pending, bi_rho);
-}
-__global__ void __launch_bounds__(kBlock) k_bi_report(Part P, const BiSt* in, BiSt* out) {
-  advance_alone<3>(P, in, out, bi_pending, bi_rho);
-}
+struct BiResid {
+  __device__ bool on(const BiSt&) const { return true; }
+  __device__ void operator()(BiSt& S, const double* o) const { bi_resid(S, o); }
+};
+struct BiAlpha {
+  __device__ bool on(const BiSt& S) const { return !S.done; }
+  __device__ void operator()(BiSt& S, const double* o) const { bi_alpha(S, o); }
+};
+struct BiOmega {
+  __device__ bool on(const BiSt& S) const { return !S.done; }
+  __device__ void operator()(BiSt& S, const double* o) const { bi_omega(S, o); }
+};
+struct BiRho {
+  __device__ bool on(const BiSt& S) const { return S.pend; }
+  __device__ void operator()(BiSt& S, const double* o) const { bi_rho(S, o); }
+};
 
 // r = f - A u; restart: rhat = r, p = v = 0.  Partial ||r||^2.
 template <typename T, int F>
@@ -138,7 +139,7 @@ __global__ void __launch_bounds__(kBlock) k_resid(Seg L, SellOp<T> A, BiV<T> V, 
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_p(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V) {
   const Tile t = vec_tile(L);
-  const BiSt& S = advance<3>(P, in, out, t, first_block(L, t), bi_pending, bi_rho);
+  const BiSt& S = advance<3>(P, in, out, t, first_block(L, t), BiRho{});
   if (S.done) return;
   const TzSeg B = form_seg<F>(Z, t);
   if (S.reset) {
@@ -178,7 +179,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_v(Seg L, SellOp<T> A, const BiSt* st, BiV<T>
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_s(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V) {
   const Tile t = vec_tile(L);
-  const BiSt& S = advance<2>(P, in, out, t, first_block(L, t), bi_on, bi_alpha);
+  const BiSt& S = advance<2>(P, in, out, t, first_block(L, t), BiAlpha{});
   if (S.done) return;
   const TzSeg B = form_seg<F>(Z, t);
   const z_t alpha = S.alpha;
@@ -210,7 +211,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_t(Seg L, SellOp<T> A, const BiSt* st, BiV<T>
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_xr(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V, double* part) {
   const SumTile t = vec_tile_sums(L);
-  const BiSt& S = advance<4>(P, in, out, t, first_block(L, t), bi_on, bi_omega);
+  const BiSt& S = advance<4>(P, in, out, t, first_block(L, t), BiOmega{});
   if (S.done) return;
   const TzSeg B = form_seg<F>(Z, t);
   double q[3] = {0.0, 0.0, 0.0};
@@ -289,28 +290,28 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
   int64_t resid_calls = 0;
 
   auto report = [&]() -> int {
-    k_bi_report<<<S.nseg, kBlock, 0, s>>>(pn.part, st, poll.slot<BiSt>());
-    HZ_HIP(hipGetLastError());
+    HZ_TRY(pn.step_now<3>(s, st, poll.slot<BiSt>(), BiRho{}));
     return poll.posted_one();
   };
   auto enqueue_resid = [&]() -> int {
-    k_bi_settle<<<S.nseg, kBlock, 0, s>>>(pn.part, st);
+    // the slot an iteration starts from takes up the pending sums
+    HZ_TRY(pn.step_now<3>(s, st, st, BiRho{}));
     HZ_BY_FORM(A, k_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, V, pr.raw));
-    HZ_TRY(pr.close<1>(s));
-    k_bi_resid<<<S.nseg, kBlock, 0, s>>>(pr.part, st);
     HZ_HIP(hipGetLastError());
+    HZ_TRY(pr.step_now<1>(s, st, st, BiResid{}));
+    HZ_TRY(pn.step<3>(s, st, st_a, BiRho{}));   // (nothing pending: the state the next iteration starts from)
     ++resid_calls;
     return report();
   };
   auto enqueue_iter = [&]() -> int {
     HZ_BY_SCALING(A, k_p<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pn.part, st, st_a, V));
     HZ_BY_FORM(A, k_v<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st_a, V, pa.raw));
-    HZ_TRY(pa.close<2>(s));
+    HZ_TRY(pa.step<2>(s, st_a, st_b, BiAlpha{}));
     HZ_BY_SCALING(A, k_s<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st_a, st_b, V));
     HZ_BY_FORM(A, k_t<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st_b, V, po.raw));
-    HZ_TRY(po.close<4>(s));
+    HZ_TRY(po.step<4>(s, st_b, st, BiOmega{}));
     HZ_BY_SCALING(A, k_xr<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, st_b, st, V, pn.raw));
-    HZ_TRY(pn.close<3>(s));
+    HZ_TRY(pn.step<3>(s, st, st_a, BiRho{}));
     HZ_HIP(hipGetLastError());
     return HZ_OK;
   };

@@ -138,21 +138,28 @@ __device__ __forceinline__ void bl_cycle(BlSt& S, const double* tot) {
   S.rho0 = rho1;
 }
 
-__device__ __forceinline__ bool bl_on(const BlSt& S) { return !bl_off(S); }
-__device__ __forceinline__ bool bl_pending(const BlSt& S) { return S.pend; }
-
-// The state after the sums formed last: in place after k_bl_resid, for the
-// host at the end of a cycle.
-__global__ void __launch_bounds__(kBlock) k_bl_resid_fin(Part P, BlSt* st) {
-  advance_alone<1>(P, st, st, [](const BlSt& S) { return S.restart != 0; }, bl_resid);
-}
-__global__ void __launch_bounds__(kBlock) k_bl_report(Part P, const BlSt* in, BlSt* out) {
-  advance_alone<3>(P, in, out, bl_pending, bl_cycle);
-}
-// At a restart the slot a cycle starts from takes up the pending sums.
-__global__ void __launch_bounds__(kBlock) k_bl_settle(Part P, BlSt* st, int all) {
-  settle<3>(P, st, all, bl_pending, bl_cycle);
-}
+struct BlResid {
+  __device__ bool on(const BlSt& S) const { return S.restart != 0; }
+  __device__ void operator()(BlSt& S, const double* o) const { bl_resid(S, o); }
+};
+struct BlAlpha {
+  __device__ bool on(const BlSt& S) const { return !bl_off(S); }
+  __device__ void operator()(BlSt& S, const double* o) const { bl_alpha(S, o); }
+};
+struct BlBeta {
+  __device__ bool on(const BlSt& S) const { return !bl_off(S); }
+  __device__ void operator()(BlSt& S, const double* o) const { bl_beta(S, o); }
+};
+template <int LL>
+struct BlMr {
+  double piv;
+  __device__ bool on(const BlSt& S) const { return !bl_off(S); }
+  __device__ void operator()(BlSt& S, const double* o) const { bl_mr<LL>(S, o, piv); }
+};
+struct BlCycle {
+  __device__ bool on(const BlSt& S) const { return S.pend; }
+  __device__ void operator()(BlSt& S, const double* o) const { bl_cycle(S, o); }
+};
 
 // ---------------------------------------------------------------- restart
 // x += D^-1 e, e = 0 (tensor form): the segments that restart, or all.
@@ -203,8 +210,8 @@ template <typename T, int F, int J>
 __global__ void __launch_bounds__(kBlock) k_bl_u(Seg L, TzOp Z, Part P, Part Pc, const BlSt* in, BlSt* out, BlV<T> V,
                                                  int j) {
   const Tile t = vec_tile(L);
-  const BlSt& S = j == 0 ? advance<3>(Pc, in, out, t, first_block(L, t), bl_pending, bl_cycle)
-                         : advance<2>(P, in, out, t, first_block(L, t), bl_on, bl_beta);
+  const BlSt& S = j == 0 ? advance<3>(Pc, in, out, t, first_block(L, t), BlCycle{})
+                         : advance<2>(P, in, out, t, first_block(L, t), BlBeta{});
   if (bl_off(S)) return;
   const TzSeg B = form_seg<F>(Z, t);
   const z_t b = S.beta;
@@ -250,7 +257,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_bl_prod(Seg L, SellOp<T> A, const BlSt* st, 
 template <typename T, int F, int J>
 __global__ void __launch_bounds__(kBlock) k_bl_r(Seg L, TzOp Z, Part P, const BlSt* in, BlSt* out, BlV<T> V, int j) {
   const Tile t = vec_tile(L);
-  const BlSt& S = advance<2>(P, in, out, t, first_block(L, t), bl_on, bl_alpha);
+  const BlSt& S = advance<2>(P, in, out, t, first_block(L, t), BlAlpha{});
   if (bl_off(S)) return;
   const TzSeg B = form_seg<F>(Z, t);
   const z_t a = S.alpha;
@@ -313,7 +320,10 @@ __global__ void __launch_bounds__(kBlock) k_bl_gram(Seg L, const BlSt* st, BlV<T
 // add in every block, and its registers would limit k_bl_update.
 template <int LL>
 __global__ void __launch_bounds__(kBlock) k_bl_mr(Part P, const BlSt* in, BlSt* out, double piv) {
-  advance_alone<gram_nq<LL>()>(P, in, out, bl_on, [=](BlSt& S, const double* o) { bl_mr<LL>(S, o, piv); });
+  Tile t;
+  t.tile = t.seg = blockIdx.x;
+  t.row = 0;
+  advance<gram_nq<LL>()>(P, in, out, t, true, BlMr<LL>{piv});
 }
 
 // x += sum gamma_j r_{j-1}; r_0 -= sum gamma_j r_j; u_0 -= sum gamma_j u_j;
@@ -355,14 +365,13 @@ __global__ void k_bl_set_thr(int nseg, BlSt* st, const double* fn2, double tol) 
 }
 
 template <typename T, int LL>
-int enqueue_mr(hipStream_t q, const Seg& W, const BlSt* in, BlSt* out, const BlV<T>& V, const PartBuf& pg,
+int enqueue_mr(hipStream_t q, const Seg& W, const BlSt* in, BlSt* out, BlSt* next, const BlV<T>& V, const PartBuf& pg,
                const PartBuf& pc) {
   k_bl_gram<T, LL><<<W.nblk, kBlock, 0, q>>>(W, in, V, pg.raw);
   k_bl_mr<LL><<<W.nseg, kBlock, 0, q>>>(pg.part, in, out, 1e-13);
   k_bl_update<T, LL><<<W.nblk, kBlock, 0, q>>>(W, out, V, pc.raw);
-  HZ_TRY(pc.close<3>(q));
   HZ_HIP(hipGetLastError());
-  return HZ_OK;
+  return pc.step<3>(q, out, next, BlCycle{});
 }
 
 }  // namespace
@@ -417,23 +426,22 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
   HZ_TRY(pr.init(ctx, S, P, 1, W.nblk, p + "part.r"));
   HZ_TRY(pa.init(ctx, S, P, 2, W.nblk, p + "part.a"));
   HZ_TRY(pb.init(ctx, S, P, 2, W.nblk, p + "part.b"));
-  HZ_TRY(pg.init(ctx, S, W, 2 * l + l * (l + 1), 1, p + "part.g"));
+  HZ_TRY(pg.init(ctx, S, W, 2 * l + l * (l + 1), 0, p + "part.g"));   // (k_bl_mr adds them)
   HZ_TRY(pc.init(ctx, S, W, 3, W.nblk, p + "part.c"));
   int64_t resid_calls = 0;
   if (A.tz.on) HZ_HIP(hipMemsetAsync(V.e, 0, vb, s));
 
   auto report = [&]() -> int {
-    k_bl_report<<<S.nseg, kBlock, 0, s>>>(pc.part, st, poll.slot<BlSt>());
-    HZ_HIP(hipGetLastError());
+    HZ_TRY(pc.step_now<3>(s, st, poll.slot<BlSt>(), BlCycle{}));
     return poll.posted_one();
   };
   auto enqueue_resid = [&](int all) -> int {
-    k_bl_settle<<<S.nseg, kBlock, 0, s>>>(pc.part, st, all);
+    HZ_TRY(pc.step_now<3>(s, st, st, Settle<BlCycle>{{}, all}));
     if (A.tz.on && resid_calls > 0) k_bl_fold<T><<<W.nblk, kBlock, 0, s>>>(W, A.tz, st, V, 0);
     HZ_BY_FORM(A, k_bl_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pr.raw));
-    HZ_TRY(pr.close<1>(s));
-    k_bl_resid_fin<<<S.nseg, kBlock, 0, s>>>(pr.part, st);
     HZ_HIP(hipGetLastError());
+    HZ_TRY(pr.step_now<1>(s, st, st, BlResid{}));
+    HZ_TRY(pc.step<3>(s, st, st_b, BlCycle{}));   // (nothing pending: the state the next cycle starts from)
     ++resid_calls;
     HZ_TRY(report());
     return poll.wait(poll.posted - 1);
@@ -444,25 +452,25 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
       HZ_BY_STEP(j, HZ_BY_SCALING(A, k_bl_u<T, F, J><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pb.part, pc.part, from, st_b, V, j)));
       const cx<T>* uj = A.tz.on ? V.in : V.u[j];
       HZ_BY_FORM(A, k_bl_prod<T, F, true><<<P.nblk, kBlock, 0, s>>>(P, A, st_b, uj, V.u[j + 1], V.rt, pa.raw));
-      HZ_TRY(pa.close<2>(s));
+      HZ_TRY(pa.step<2>(s, st_b, st_a, BlAlpha{}));
       HZ_BY_STEP(j, HZ_BY_SCALING(A, k_bl_r<T, F, J><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st_b, st_a, V, j)));
       const cx<T>* rj = A.tz.on ? V.in : V.r[j];
       if (j + 1 < l) {
         HZ_BY_FORM(A, k_bl_prod<T, F, true><<<P.nblk, kBlock, 0, s>>>(P, A, st_a, rj, V.r[j + 1], V.rt, pb.raw));
-        HZ_TRY(pb.close<2>(s));
+        HZ_TRY(pb.step<2>(s, st_a, st_b, BlBeta{}));
       } else {
         HZ_BY_FORM(A, k_bl_prod<T, F, false><<<P.nblk, kBlock, 0, s>>>(P, A, st_a, rj, V.r[j + 1], V.rt, nullptr));
       }
     }
     switch (l) {
-      case 1: return enqueue_mr<T, 1>(s, W, st_a, st, V, pg, pc);
-      case 2: return enqueue_mr<T, 2>(s, W, st_a, st, V, pg, pc);
-      case 3: return enqueue_mr<T, 3>(s, W, st_a, st, V, pg, pc);
-      case 4: return enqueue_mr<T, 4>(s, W, st_a, st, V, pg, pc);
-      case 5: return enqueue_mr<T, 5>(s, W, st_a, st, V, pg, pc);
-      case 6: return enqueue_mr<T, 6>(s, W, st_a, st, V, pg, pc);
-      case 7: return enqueue_mr<T, 7>(s, W, st_a, st, V, pg, pc);
-      default: return enqueue_mr<T, 8>(s, W, st_a, st, V, pg, pc);
+      case 1: return enqueue_mr<T, 1>(s, W, st_a, st, st_b, V, pg, pc);
+      case 2: return enqueue_mr<T, 2>(s, W, st_a, st, st_b, V, pg, pc);
+      case 3: return enqueue_mr<T, 3>(s, W, st_a, st, st_b, V, pg, pc);
+      case 4: return enqueue_mr<T, 4>(s, W, st_a, st, st_b, V, pg, pc);
+      case 5: return enqueue_mr<T, 5>(s, W, st_a, st, st_b, V, pg, pc);
+      case 6: return enqueue_mr<T, 6>(s, W, st_a, st, st_b, V, pg, pc);
+      case 7: return enqueue_mr<T, 7>(s, W, st_a, st, st_b, V, pg, pc);
+      default: return enqueue_mr<T, 8>(s, W, st_a, st, st_b, V, pg, pc);
     }
   };
 

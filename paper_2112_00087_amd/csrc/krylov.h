@@ -349,7 +349,8 @@ __device__ __forceinline__ void store_partials_qmajor(double (&v)[NQ], double* p
 constexpr int kFinBlock = 1024;
 
 // Partial sums of a segmented reduction, NQ per block: blocks
-// [seg_blk[s], seg_blk[s + 1]) belong to segment s.
+// [seg_blk[s], seg_blk[s + 1]) belong to segment s.  NULL: the scalar step has
+// been made by a kernel of its own (k_step).
 struct Part {
   double* p = nullptr;
   const int* seg_blk = nullptr;
@@ -363,20 +364,31 @@ struct Part {
 // state it starts from is read from one slot and the state it reaches is
 // written to another by the segment's first block, so no block reads what
 // another one writes in the same kernel.  Against a finalize kernel between
-// the two (4 to 6 us: a launch and one block's chain of loads) this costs
-// about 1 us; against finishing in the producing kernel's last block, which
-// pays a store, two atomic arrivals and a reload one after the other across
-// the XCDs, it saved 3 us per reduction at 20 to 160 thousand rows.
+// the two (4 to 6 us: a launch and one block's chain of loads) this costs the
+// kernel 2.5 to 3 us; against finishing in the producing kernel's last block,
+// which pays a store, two atomic arrivals and a reload one after the other
+// across the XCDs, it saved 3 us per reduction at 20 to 160 thousand rows.
+//
+// A step f of a state St: f.on(state) says whether it is due, f(state, sums) makes it.
 //
 // All threads of the block call it; the state is in LDS afterwards.
-template <int NQ, class St, class Cond, class Fin>
-__device__ __forceinline__ const St& advance(const Part& P, const St* in, St* out, const Tile& t, bool first, Cond cond,
-                                             Fin fin) {
+template <int NQ, class St, class Step>
+__device__ __forceinline__ const St& advance(const Part& P, const St* in, St* out, const Tile& t, bool first, Step f) {
   constexpr int kPasses = kFinBlock / kBlock, kWaves = kFinBlock / kWave;
   __shared__ double lds[NQ][kWaves];
   __shared__ double tot[NQ];
   __shared__ St st;
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  // the state goes through LDS word by word: a private copy of the struct would
+  // live in scratch memory, which alone costs a kernel 10 us
+  static_assert(sizeof(St) % sizeof(int) == 0, "state is copied by words");
+  constexpr int kWords = sizeof(St) / sizeof(int);
+  int* sw = reinterpret_cast<int*>(&st);
+  if (!P.p) {
+    for (int u = threadIdx.x; u < kWords; u += kBlock) sw[u] = reinterpret_cast<const int*>(out + t.seg)[u];
+    __syncthreads();
+    return st;
+  }
   const int b0 = P.nseg == 1 ? 0 : P.seg_blk[t.seg], b1 = P.nseg == 1 ? P.nblk : P.seg_blk[t.seg + 1];
   // the order of a kFinBlock-thread finalize kernel (seg_sums): thread u takes
   // blocks u, u + kFinBlock, ..., here threads u of pass m stand for u + 256 m
@@ -393,11 +405,6 @@ __device__ __forceinline__ const St& advance(const Part& P, const St* in, St* ou
         for (int q = 0; q < NQ; ++q) acc[m][q] += P.p[int64_t(b) * NQ + q];
       }
   }
-  // the state through LDS word by word: a private copy of the struct would
-  // live in scratch memory, which alone costs a kernel 10 us
-  static_assert(sizeof(St) % sizeof(int) == 0, "state is copied by words");
-  constexpr int kWords = sizeof(St) / sizeof(int);
-  int* sw = reinterpret_cast<int*>(&st);
   for (int u = threadIdx.x; u < kWords; u += kBlock) sw[u] = reinterpret_cast<const int*>(in + t.seg)[u];
 #pragma unroll
   for (int m = 0; m < kPasses; ++m) {
@@ -426,12 +433,12 @@ __device__ __forceinline__ const St& advance(const Part& P, const St* in, St* ou
     for (int q = threadIdx.x; q < NQ; q += kBlock) tot[q] = total(q);
     __syncthreads();
   }
-  if (threadIdx.x == 0 && cond(st)) {
+  if (threadIdx.x == 0 && f.on(st)) {
     if (NQ <= 4) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) tot[q] = total(q);
     }
-    fin(st, static_cast<const double*>(tot));
+    f(st, static_cast<const double*>(tot));
   }
   __syncthreads();
   if (first)
@@ -441,28 +448,6 @@ __device__ __forceinline__ const St& advance(const Part& P, const St* in, St* ou
 // First block of its segment in layout L.
 __device__ __forceinline__ bool first_block(const Seg& L, const Tile& t) {
   return t.tile == (L.nseg == 1 ? 0 : L.seg_blk[t.seg]);
-}
-
-// The same step by one block per segment, in place (restarts) or into a
-// copy for the host (out).
-template <int NQ, class St, class Cond, class Fin>
-__device__ __forceinline__ void advance_alone(const Part& P, const St* in, St* out, Cond cond, Fin fin) {
-  Tile t;
-  t.tile = t.seg = blockIdx.x;
-  t.row = 0;
-  advance<NQ>(P, in, out, t, true, cond, fin);
-}
-
-// Takes up a segment's pending sums (fin) in place and sets which segments
-// restart: all of them, or those that broke down.  Both in the one scalar step,
-// on the state in LDS: the words of the stored state are written by different
-// threads, so none may be read or written again after advance.
-template <int NQ, class St, class Cond, class Fin>
-__device__ __forceinline__ void settle(const Part& P, St* st, int all, Cond pending, Fin fin) {
-  advance_alone<NQ>(P, st, st, [](const St&) { return true; }, [=](St& S, const double* tot) {
-    if (pending(S)) fin(S, tot);
-    S.restart = all ? 1 : S.brk;
-  });
 }
 
 // Vector layout: block b works on rows [blk_row[b], blk_row[b + 1]) of one
@@ -524,6 +509,39 @@ __device__ __forceinline__ void seg_sums(const Seg& L, const double* partial, in
   }
   __syncthreads();
 }
+
+// A scalar step by a kernel of its own, one block per segment, in place
+// (restarts), into the slot of the kernels that need it (PartBuf::step) or into
+// a copy for the host.  The sums' order and the step are advance's, so the state
+// has the same bits either way.
+template <int NQ, class St, class Step>
+__global__ void __launch_bounds__(kFinBlock) k_step(Seg L, const double* part, const St* in, St* out, Step f) {
+  __shared__ St st;
+  const int s = blockIdx.x;
+  constexpr int kWords = sizeof(St) / sizeof(int);
+  int* sw = reinterpret_cast<int*>(&st);
+  if (threadIdx.x < kWords) sw[threadIdx.x] = reinterpret_cast<const int*>(in + s)[threadIdx.x];
+  static_assert(kWords <= kFinBlock, "one word a thread");
+  double o[NQ];
+  seg_sums<NQ>(L, part, s, o);   // (its barriers also order the state's words)
+  if (threadIdx.x == 0 && f.on(st)) f(st, static_cast<const double*>(o));
+  __syncthreads();
+  if (threadIdx.x < kWords) reinterpret_cast<int*>(out + s)[threadIdx.x] = sw[threadIdx.x];
+}
+// Takes up a segment's pending sums and sets which segments restart: all of
+// them, or those that broke down.  One step on the state in LDS: the words of
+// the stored state are written by different threads, so none may be read or
+// written again behind it.
+template <class Step>
+struct Settle {
+  Step f;
+  int all;
+  template <class St> __device__ bool on(const St&) const { return true; }
+  template <class St> __device__ void operator()(St& S, const double* tot) const {
+    if (f.on(S)) f(S, tot);
+    S.restart = all ? 1 : S.brk;
+  }
+};
 
 // In a finalize kernel (one block per segment): sum quantity q of this
 // segment's partials; valid in thread 0.
@@ -606,5 +624,4 @@ struct SegHost {
   // forms), and runs of tiles, about 1,000 blocks (four per CU) at most, so
   // that advance has few partials to add (tensor form)
   Seg vec, vec_runs;
-  const int* iota = nullptr;      // [nseg + 1] 0, 1, ... (device)
 };

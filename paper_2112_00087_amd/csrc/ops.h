@@ -276,20 +276,33 @@ int replay(hz_ctx ctx, const std::string& tag, const ReplayKey& key, Body body, 
 
 // Block partials of one reduction.  The kernels that need the sums add the
 // partials themselves (advance) as long as their blocks together read no more
-// than kMaxConsumed of them: 1,024 blocks of a tensor-form vector kernel each
-// adding 2,560 partials of 4 sums move 84 MB from L2, about the 5 us of a
-// kernel of its own.  Beyond (stored forms of large meshes, 4,942 blocks that
-// would each add 4,942 partials at 160x96x80) every block would read more
-// partials than rows, and close() adds them once with a kernel of its own;
-// it is called after every kernel that forms the sums.
-constexpr int64_t kMaxConsumed = int64_t(2560) * 1024;
+// than kMaxConsumed of them; beyond, every block would read more partials than
+// rows, and step() makes the scalar step once with a kernel of its own (4.6 us),
+// whose state the others only copy.  It is called after every kernel that forms
+// the sums.  Measured, us a product, consumed : stepped, BiCGStab / TFQMR: stored
+// forms (as many consuming as producing blocks, 256 rows each) at 162,729 rows
+// 28.9:29.5 30.4:31.0, at 308,050 40.1:38.8 42.4:41.8, at 608,076 68.8:61.0
+// 75.4:67.2, at 1,264,977 130:105 144:117; tensor form (912, 1,506 and 2,520
+// product blocks, 800 to 1,000 vector blocks) at 608,076 32.9:32.8 37.2:36.7, at
+// 1,264,977 47.0:46.8 58.1:56.6, at 2,456,421 85.9:83.8 129:125.
+constexpr int64_t kMaxConsumed = int64_t(1024) * 1024;
 struct PartBuf {
   double* raw = nullptr;             // where the producing kernel stores
-  Part part;                         // what the consuming kernels add
+  Part part;                         // what the consuming kernels add (p NULL: nothing, step has run)
   Seg lay;
-  bool many = false;
+  // consumers: blocks of the kernels that would add the partials (0: one block
+  // per segment does, by advance)
   int init(hz_ctx ctx, const SegHost& S, const Seg& L, int nq, int consumers, const std::string& name);
-  template <int NQ> int close(hipStream_t s) const;
+  // The scalar step from state in to out, if the consumers do not make it
+  // themselves; always, at a restart or for the host.
+  template <int NQ, class St, class Step>
+  int step(hipStream_t s, const St* in, St* out, Step f) const { return part.p ? HZ_OK : step_now<NQ>(s, in, out, f); }
+  template <int NQ, class St, class Step>
+  int step_now(hipStream_t s, const St* in, St* out, Step f) const {
+    k_step<NQ, St, Step><<<lay.nseg, kFinBlock, 0, s>>>(lay, raw, in, out, f);
+    HZ_HIP(hipGetLastError());
+    return HZ_OK;
+  }
   void key(ReplayKey* k) const { k->add(raw).add(part).add(lay); }
 };
 

@@ -94,42 +94,19 @@ int StatePoll::wait(int k) {
   return HZ_OK;
 }
 
-// One total per segment and quantity (layouts of many blocks).
-namespace {
-template <int NQ>
-__global__ void k_totals(Seg L, const double* part, double* out) {
-  double o[NQ];
-  seg_sums<NQ>(L, part, blockIdx.x, o);
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) out[int64_t(blockIdx.x) * NQ + q] = o[q];
-  }
-}
-}  // namespace
 int PartBuf::init(hz_ctx ctx, const SegHost& S, const Seg& L, int nq, int consumers, const std::string& name) {
   int rc = 0;
-  many = int64_t(L.nblk) * consumers > kMaxConsumed * S.nseg;
-  DevBuf* b = ctx->buf(name, sizeof(double) * nq * (size_t(L.nblk) + S.nseg), &rc);
+  const bool many = int64_t(L.nblk) * consumers > kMaxConsumed * S.nseg;
+  DevBuf* b = ctx->buf(name, sizeof(double) * nq * size_t(L.nblk), &rc);
   if (rc) return rc;
   raw = b->as<double>();
   lay = L;
   part.nseg = S.nseg;
-  part.p = many ? raw + size_t(L.nblk) * nq : raw;
-  part.seg_blk = many ? S.iota : L.seg_blk;
-  part.nblk = many ? S.nseg : L.nblk;
+  part.p = many ? nullptr : raw;
+  part.seg_blk = L.seg_blk;
+  part.nblk = L.nblk;
   return HZ_OK;
 }
-template <int NQ>
-int PartBuf::close(hipStream_t s) const {
-  if (!many) return HZ_OK;
-  k_totals<NQ><<<lay.nseg, kFinBlock, 0, s>>>(lay, raw, part.p);
-  HZ_HIP(hipGetLastError());
-  return HZ_OK;
-}
-template int PartBuf::close<1>(hipStream_t) const;
-template int PartBuf::close<2>(hipStream_t) const;
-template int PartBuf::close<3>(hipStream_t) const;
-template int PartBuf::close<4>(hipStream_t) const;
 
 int seg_upload(hz_ctx ctx, SegHost* S, const std::string& tag) {
   int rc = 0;
@@ -175,13 +152,6 @@ int seg_upload(hz_ctx ctx, SegHost* S, const std::string& tag) {
   HZ_TRY(layout(1, ".vec", &S->vec));
   if (per > 1) HZ_TRY(layout(per, ".vecr", &S->vec_runs));
   else S->vec_runs = S->vec;
-  // one total per segment
-  std::vector<int> iota(S->nseg + 1);
-  for (int i = 0; i <= S->nseg; ++i) iota[i] = i;
-  DevBuf* ib = ctx->buf(tag + ".iota", sizeof(int) * (S->nseg + 1), &rc);
-  if (rc) return rc;
-  HZ_HIP(hipMemcpy(ib->p, iota.data(), sizeof(int) * (S->nseg + 1), hipMemcpyHostToDevice));
-  S->iota = ib->as<int>();
   S->dev.nseg = S->nseg;
   S->dev.nblk = S->nblk;
   S->dev.nrows = S->nrows;

@@ -133,22 +133,22 @@ __device__ __forceinline__ void tq_odd(TqSt& S, const double* o) {
   S.pend = !tq_off(S);   // k_tq_odd3 forms the sums of the alpha step
 }
 __device__ __forceinline__ void tq_even(TqSt& S, const double* o) { tq_qmr(S, o[0]); }
-__device__ __forceinline__ bool tq_on(const TqSt& S) { return !tq_off(S); }
-__device__ __forceinline__ bool tq_pending(const TqSt& S) { return S.pend; }
-
-// The state after the sums formed last: in place after k_tq_resid, for the
-// host after k_tq_odd3.
-__global__ void __launch_bounds__(kBlock) k_tq_resid_fin(Part P, TqSt* st) {
-  advance_alone<1>(P, st, st, [](const TqSt& S) { return S.restart == 1; }, tq_resid);
-}
-// At a restart the slot a pair starts from takes up the pending sums; the
-// segments that restart are all of them, or those that broke down.
-__global__ void __launch_bounds__(kBlock) k_tq_settle(Part P, TqSt* st, int all) {
-  settle<2>(P, st, all, tq_pending, tq_alpha);
-}
-__global__ void __launch_bounds__(kBlock) k_tq_report(Part P, const TqSt* in, TqSt* out) {
-  advance_alone<2>(P, in, out, tq_pending, tq_alpha);
-}
+struct TqResid {
+  __device__ bool on(const TqSt& S) const { return S.restart == 1; }
+  __device__ void operator()(TqSt& S, const double* o) const { tq_resid(S, o); }
+};
+struct TqAlpha {
+  __device__ bool on(const TqSt& S) const { return S.pend; }
+  __device__ void operator()(TqSt& S, const double* o) const { tq_alpha(S, o); }
+};
+struct TqEven {
+  __device__ bool on(const TqSt& S) const { return !tq_off(S); }
+  __device__ void operator()(TqSt& S, const double* o) const { tq_even(S, o); }
+};
+struct TqOdd {
+  __device__ bool on(const TqSt& S) const { return !tq_off(S); }
+  __device__ void operator()(TqSt& S, const double* o) const { tq_odd(S, o); }
+};
 
 // ---------------------------------------------------------------- restart
 // r0 = f - B x; r* = w = u = r0; d = 0; partial ||r0||^2
@@ -198,7 +198,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_tq_resid_prod(Seg L, SellOp<T> A, const TqSt
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_tq_even1(Seg L, TzOp Z, Part P, const TqSt* in, TqSt* out, TqV<T> V, double* part) {
   const SumTile t = vec_tile_sums(L);
-  const TqSt& S = advance<2>(P, in, out, t, first_block(L, t), tq_pending, tq_alpha);
+  const TqSt& S = advance<2>(P, in, out, t, first_block(L, t), TqAlpha{});
   if (tq_off(S)) return;
   const TzSeg B = form_seg<F>(Z, t);
   const z_t a = S.alpha;
@@ -217,20 +217,19 @@ __global__ void __launch_bounds__(kBlock) k_tq_even1(Seg L, TzOp Z, Part P, cons
   store_partials<1>(q, part, t);
 }
 
-// theta, tau, eta; x += eta d; then (unless stopping) uhat = B u'
+// theta, tau, eta; x += eta d; then (unless stopping) uhat = B u' (stored forms).
+// x is updated ahead of the product: with eta and the stop flag held across it
+// the kernel took 98 VGPRs instead of 92 and lost a wave per SIMD (38.5 -> 42.3
+// us at 289,937 rows in split form).
 template <typename T, int F>
 __global__ void HZ_PRODUCT_BOUNDS k_tq_even2(Seg L, SellOp<T> A, Part P, const TqSt* in, TqSt* out, TqV<T> V) {
-  Tile t = prod_tile<F>(L);
+  const Tile t = tile_of(L);
   const bool was_done = in[t.seg].done;
-  const TqSt& S = advance<1>(P, in, out, t, first_block(L, t), tq_on, tq_even);
+  const TqSt& S = advance<1>(P, in, out, t, first_block(L, t), TqEven{});
   if (S.brk || S.nan || was_done) return;
-  const z_t eta = S.eta;
-  const bool done = S.done;
-  for_rows<F>(A, t, V.un, [=](int64_t row) { return TqPair<T>{V.x[row], V.d[row]}; },
-              [=](int64_t row, cx<T> y, TqPair<T> a) {
-                V.x[row] = zt<T>(zd(a.a) + eta * zd(a.b));
-                if (!done) V.uh[row] = y;
-              });
+  V.x[t.row] = zt<T>(zd(V.x[t.row]) + S.eta * zd(V.d[t.row]));
+  if (S.done) return;
+  V.uh[t.row] = sell_row_form<F>(A, t.row, V.un);
 }
 
 // ---------------------------------------------------------------- odd half-step
@@ -265,7 +264,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_tq_even2_odd1(Seg L, SellOp<T> A, Part P, co
                                                   double* part) {
   const SumTile t = prod_tile_sums<F>(L);
   const bool was_done = in[t.seg].done;
-  const TqSt& S = advance<1>(P, in, out, t, first_block(L, t), tq_on, tq_even);
+  const TqSt& S = advance<1>(P, in, out, t, first_block(L, t), TqEven{});
   if (S.brk || S.nan || was_done) return;
   const z_t eta = S.eta, a = S.alpha;
   const z_t g = (S.theta * S.theta) * cdiv(eta, a);
@@ -293,7 +292,7 @@ template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_tq_odd2(Seg L, TzOp Z, Part P, const TqSt* in, TqSt* out, TqV<T> V) {
   const Tile t = vec_tile(L);
   const bool was_done = in[t.seg].done;
-  const TqSt& S = advance<3>(P, in, out, t, first_block(L, t), tq_on, tq_odd);
+  const TqSt& S = advance<3>(P, in, out, t, first_block(L, t), TqOdd{});
   if (S.nan || (S.brk && !S.done) || was_done) return;
   const TzSeg B = form_seg<F>(Z, t);
   if (S.done) {
@@ -399,19 +398,17 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   int64_t restarts = 0, pairs = 0;
 
   auto report = [&]() -> int {
-    k_tq_report<<<S.nseg, kBlock, 0, s>>>(pa.part, st, poll.slot<TqSt>());
-    HZ_HIP(hipGetLastError());
+    HZ_TRY(pa.step_now<2>(s, st, poll.slot<TqSt>(), TqAlpha{}));
     return poll.posted_one();
   };
   auto enqueue_restart = [&](int all) -> int {
-    k_tq_settle<<<S.nseg, kBlock, 0, s>>>(pa.part, st, all);
+    HZ_TRY(pa.step_now<2>(s, st, st, Settle<TqAlpha>{{}, all}));
     HZ_BY_FORM(A, k_tq_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pr.raw));
-    HZ_TRY(pr.close<1>(s));
-    k_tq_resid_fin<<<S.nseg, kBlock, 0, s>>>(pr.part, st);
+    HZ_TRY(pr.step_now<1>(s, st, st, TqResid{}));
     // u = r_0 is the first product's input
     if (A.tz.on) HZ_BY_SCALING(A, k_tq_start<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, st, V));
     HZ_BY_FORM(A, k_tq_resid_prod<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pa.raw));
-    HZ_TRY(pa.close<2>(s));
+    HZ_TRY(pa.step<2>(s, st, st_a, TqAlpha{}));
     HZ_HIP(hipGetLastError());
     ++restarts;
     HZ_TRY(report());
@@ -419,7 +416,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   };
   auto enqueue_pair = [&]() -> int {
     HZ_BY_SCALING(A, k_tq_even1<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st, st_a, V, pe.raw));
-    HZ_TRY(pe.close<1>(s));
+    HZ_TRY(pe.step<1>(s, st_a, st_e, TqEven{}));
     if (A.tz.on == 1) {
       k_tq_even2_odd1<T, kFormTensor><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, st_e, V, po.raw);
     } else if (A.tz.on) {
@@ -428,10 +425,10 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
       HZ_BY_STORED(A, k_tq_even2<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, st_e, V));
       k_tq_odd1<T><<<W.nblk, kBlock, 0, s>>>(W, st_e, V, po.raw);
     }
-    HZ_TRY(po.close<3>(s));
+    HZ_TRY(po.step<3>(s, st_e, st, TqOdd{}));
     HZ_BY_SCALING(A, k_tq_odd2<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, st_e, st, V));
     HZ_BY_FORM(A, k_tq_odd3<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pa.raw));
-    HZ_TRY(pa.close<2>(s));
+    HZ_TRY(pa.step<2>(s, st, st_a, TqAlpha{}));
     HZ_HIP(hipGetLastError());
     return HZ_OK;
   };

@@ -1,4 +1,4 @@
-// The settle kernels of the BiCGStab(l) and TFQMR recursions, block by block
+// The settle step of the BiCGStab(l) and TFQMR recursions, block by block
 // with the threads in either order: the state left must be the same, and a
 // segment restarts if it broke down or if all do.  DEVICE_PART is the device
 // part of the solver's source.
@@ -10,13 +10,13 @@
 using St = BlSt;
 constexpr int kSums = 3;
 static void start(St& S) { S.rho0 = S.omega = z_t{1.0, 0.5}; }
-static void settle(Part P, St* st, int all) { k_bl_settle(P, st, all); }
+using Pending = BlCycle;
 static void breaks(St& S, double* sums) { S.trunc = 1; sums[0] = sums[2] = 2.0; }   // a truncated Gram matrix
 #else
 using St = TqSt;
 constexpr int kSums = 2;
 static void start(St& S) { S.rho = z_t{1.0, 0.5}; }
-static void settle(Part P, St* st, int all) { k_tq_settle(P, st, all); }
+using Pending = TqAlpha;
 static void breaks(St& S, double* sums) { sums[0] = sums[1] = 0.0; }                // r*^H v = 0
 #endif
 
@@ -39,12 +39,13 @@ int main() {
             if (brk && pend) breaks(st[s], part[s]);
             if (brk && !pend) st[s].brk = 1;
           }
-          Part P;
-          P.p = &part[0][0];
-          P.seg_blk = seg_blk;
-          P.nseg = 2;
-          P.nblk = 2;
-          for (int b = 0; b < 2; ++b) fiber::run_block(b, kBlock, down, [&] { settle(P, st, all); });
+          Seg L;
+          L.seg_blk = seg_blk;
+          L.nseg = 2;
+          L.nblk = 2;
+          for (int b = 0; b < 2; ++b)
+            fiber::run_block(b, kFinBlock, down,
+                             [&] { k_step<kSums, St>(L, &part[0][0], st, st, Settle<Pending>{{}, all}); });
           for (int s = 0; s < 2; ++s) {
             out[down][s] = st[s];
             if (st[s].restart != (all || brk) || st[s].brk != brk || st[s].pend) {
