@@ -295,13 +295,13 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
   };
   auto enqueue_resid = [&]() -> int {
     // the slot an iteration starts from takes up the pending sums
-    HZ_TRY(pn.step_now<3>(s, st, st, BiRho{}));
+    if (resid_calls > 0) HZ_TRY(pn.step_now<3>(s, st, st, BiRho{}));
     HZ_BY_FORM(A, k_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, V, pr.raw));
     HZ_HIP(hipGetLastError());
-    HZ_TRY(pr.step_now<1>(s, st, st, BiResid{}));
-    HZ_TRY(pn.step<3>(s, st, st_a, BiRho{}));   // (nothing pending: the state the next iteration starts from)
+    // (nothing is pending: st_a is what the next iteration's first step would make of st)
+    HZ_TRY(pr.step_now<1>(s, st, st, BiResid{}, poll.slot<BiSt>(), st_a));
     ++resid_calls;
-    return report();
+    return poll.posted_one();
   };
   auto enqueue_iter = [&]() -> int {
     HZ_BY_SCALING(A, k_p<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pn.part, st, st_a, V));
@@ -318,6 +318,7 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
 
   constexpr int kChunk = 8;          // iterations between reports
   const bool replays = nr <= (A.tz.on ? kReplayRowsTensor : kReplayRowsStored);
+  const Pace pace = {4, 2, kChunk, replays ? 12 : 4, replays};
   ReplayKey key;
   key.op(A).add(V).add(P).add(W).add(st).add(S.nseg);
   for (const PartBuf* b : {&pa, &po, &pn}) b->key(&key);
@@ -331,7 +332,7 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
   HZ_TRY(enqueue_resid());
   HZ_TRY(poll.wait(0));
   const BiSt* hst = poll.state<BiSt>(0);
-  int chunk = 2;
+  int64_t queued = 0;                // iterations so far
   for (;;) {
     // everything queued has run: hst is the state
     bool all_done = true;
@@ -356,19 +357,20 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
     if (left < 1) break;
     const int first = poll.posted;
     for (bool stop = false; !stop && left > 0;) {
-      const int n_it = int(std::min<int64_t>(chunk, left));
+      const int n_it = int(std::min<int64_t>(pace.next(queued), left));
       bool ran = false;
       if (n_it == kChunk && replays) HZ_TRY(replay(ctx, p, key, run_chunk, &ran, kReplayAfter));
       for (int it = 0; it < n_it && !ran; ++it) HZ_TRY(enqueue_iter());
       left -= n_it;
+      queued += n_it;
       HZ_TRY(report());
-      if (poll.posted - 1 > first) {
-        HZ_TRY(poll.wait(poll.posted - 2));
-        const BiSt* h = poll.state<BiSt>(poll.posted - 2);
+      const int k = poll.posted - (pace.at_once(queued) ? 1 : 2);
+      if (k >= first) {
+        HZ_TRY(poll.wait(k));
+        const BiSt* h = poll.state<BiSt>(k);
         stop = true;
         for (int i = 0; i < S.nseg; ++i) stop = stop && h[i].done;
       }
-      chunk = std::min(chunk * 2, kChunk);
     }
     HZ_TRY(poll.wait(poll.posted - 1));
     hst = poll.state<BiSt>(poll.posted - 1);

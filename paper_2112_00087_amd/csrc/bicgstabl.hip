@@ -362,6 +362,7 @@ __global__ void k_bl_set_thr(int nseg, BlSt* st, const double* fn2, double tol) 
   if (s >= nseg) return;
   st[s].thr2 = tol * tol * fn2[s];
   st[s].iter = 0;
+  st[s].restart = 1;
 }
 
 template <typename T, int LL>
@@ -436,14 +437,14 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     return poll.posted_one();
   };
   auto enqueue_resid = [&](int all) -> int {
-    HZ_TRY(pc.step_now<3>(s, st, st, Settle<BlCycle>{{}, all}));
+    if (resid_calls > 0) HZ_TRY(pc.step_now<3>(s, st, st, Settle<BlCycle>{{}, all}));
     if (A.tz.on && resid_calls > 0) k_bl_fold<T><<<W.nblk, kBlock, 0, s>>>(W, A.tz, st, V, 0);
     HZ_BY_FORM(A, k_bl_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pr.raw));
     HZ_HIP(hipGetLastError());
-    HZ_TRY(pr.step_now<1>(s, st, st, BlResid{}));
-    HZ_TRY(pc.step<3>(s, st, st_b, BlCycle{}));   // (nothing pending: the state the next cycle starts from)
+    // (nothing is pending: st_b is what the next cycle's first step would make of st)
+    HZ_TRY(pr.step_now<1>(s, st, st, BlResid{}, poll.slot<BlSt>(), st_b));
     ++resid_calls;
-    HZ_TRY(report());
+    HZ_TRY(poll.posted_one());
     return poll.wait(poll.posted - 1);
   };
   auto enqueue_cycle = [&]() -> int {
@@ -474,8 +475,9 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     }
   };
 
-  constexpr int kChunk = 2;          // cycles between reports
+  const int kChunk = l >= 4 ? 1 : 2;   // cycles between reports
   const bool replays = nr <= (A.tz.on ? kReplayRowsTensor : kReplayRowsStored);
+  const Pace pace = {1, 1, kChunk, l >= 4 ? 4 : replays ? 3 : 1, replays};
   ReplayKey key;
   key.op(A).add(V).add(P).add(W).add(st).add(S.nseg).add(l);
   for (const PartBuf* b : {&pa, &pb, &pg, &pc}) b->key(&key);
@@ -488,7 +490,7 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
   };
   HZ_TRY(enqueue_resid(1));
   const BlSt* hst = poll.state<BlSt>(poll.posted - 1);
-  int chunk = 1;
+  int64_t queued = 0;                // cycles so far
   for (;;) {
     // everything queued has run: hst is the state
     bool all_done = true, any_brk = false;
@@ -518,15 +520,17 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     int64_t left = (ctl.max_matvec - mv) / (2 * l);   // cycles that may still be queued
     const int first = poll.posted;
     for (bool stop = false; !stop && left > 0;) {
-      const int n_cyc = int(std::min<int64_t>(chunk, left));
+      const int n_cyc = int(std::min<int64_t>(pace.next(queued), left));
       bool ran = false;
-      if (n_cyc == kChunk && replays) HZ_TRY(replay(ctx, p, key, run_chunk, &ran, kReplayAfter));
+      if (n_cyc == kChunk && replays) HZ_TRY(replay(ctx, p, key, run_chunk, &ran, kReplayAfter * 2 / kChunk));
       for (int c = 0; c < n_cyc && !ran; ++c) HZ_TRY(enqueue_cycle());
       left -= n_cyc;
+      queued += n_cyc;
       HZ_TRY(report());
-      if (poll.posted - 1 > first) {
-        HZ_TRY(poll.wait(poll.posted - 2));
-        const BlSt* h = poll.state<BlSt>(poll.posted - 2);
+      const int k = poll.posted - (pace.at_once(queued) ? 1 : 2);
+      if (k >= first) {
+        HZ_TRY(poll.wait(k));
+        const BlSt* h = poll.state<BlSt>(k);
         bool off = true, brk = false;
         for (int i = 0; i < S.nseg; ++i) {
           off = off && h[i].done;
@@ -534,7 +538,6 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
         }
         stop = off || brk;
       }
-      chunk = std::min(chunk * 2, kChunk);
     }
     HZ_TRY(poll.wait(poll.posted - 1));
     hst = poll.state<BlSt>(poll.posted - 1);

@@ -511,11 +511,12 @@ __device__ __forceinline__ void seg_sums(const Seg& L, const double* partial, in
 }
 
 // A scalar step by a kernel of its own, one block per segment, in place
-// (restarts), into the slot of the kernels that need it (PartBuf::step) or into
-// a copy for the host.  The sums' order and the step are advance's, so the state
-// has the same bits either way.
+// (restarts), into the slot of the kernels that need it (PartBuf::step) or for
+// the host; copy and next (or NULL) take the state too.  The sums' order and the
+// step are advance's, so the state has the same bits either way.
 template <int NQ, class St, class Step>
-__global__ void __launch_bounds__(kFinBlock) k_step(Seg L, const double* part, const St* in, St* out, Step f) {
+__global__ void __launch_bounds__(kFinBlock) k_step(Seg L, const double* part, const St* in, St* out, St* copy, St* next,
+                                                    Step f) {
   __shared__ St st;
   const int s = blockIdx.x;
   constexpr int kWords = sizeof(St) / sizeof(int);
@@ -527,6 +528,8 @@ __global__ void __launch_bounds__(kFinBlock) k_step(Seg L, const double* part, c
   if (threadIdx.x == 0 && f.on(st)) f(st, static_cast<const double*>(o));
   __syncthreads();
   if (threadIdx.x < kWords) reinterpret_cast<int*>(out + s)[threadIdx.x] = sw[threadIdx.x];
+  if (copy && threadIdx.x < kWords) reinterpret_cast<int*>(copy + s)[threadIdx.x] = sw[threadIdx.x];
+  if (next && threadIdx.x < kWords) reinterpret_cast<int*>(next + s)[threadIdx.x] = sw[threadIdx.x];
 }
 // Takes up a segment's pending sums and sets which segments restart: all of
 // them, or those that broke down.  One step on the state in LDS: the words of

@@ -344,6 +344,7 @@ __global__ void k_tq_set_thr(int nseg, TqSt* st, const double* fn2, double tol, 
   st[s].thr2 = tol * tol * fn2[s];
   st[s].thr = tol * sqrt(fn2[s]);
   st[s].iter = 0;
+  st[s].restart = 1;
   st[s].stall_win = stall_win;
   st[s].stalled = 0;
 }
@@ -402,7 +403,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     return poll.posted_one();
   };
   auto enqueue_restart = [&](int all) -> int {
-    HZ_TRY(pa.step_now<2>(s, st, st, Settle<TqAlpha>{{}, all}));
+    if (restarts > 0) HZ_TRY(pa.step_now<2>(s, st, st, Settle<TqAlpha>{{}, all}));
     HZ_BY_FORM(A, k_tq_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pr.raw));
     HZ_TRY(pr.step_now<1>(s, st, st, TqResid{}));
     // u = r_0 is the first product's input
@@ -435,6 +436,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
 
   constexpr int kChunk = 8;          // pairs between reports
   const bool replays = nr <= (A.tz.on ? kReplayRowsTensor : kReplayRowsStored);
+  const Pace pace = {4, 2, kChunk, replays ? 12 : 4, replays};
   ReplayKey key;
   key.op(A).add(V).add(P).add(W).add(st).add(S.nseg);
   for (const PartBuf* b : {&pa, &pe, &po}) b->key(&key);
@@ -447,7 +449,6 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   };
   HZ_TRY(enqueue_restart(1));
   const TqSt* hst = poll.state<TqSt>(poll.posted - 1);
-  int chunk = 2;
   for (;;) {
     // everything queued has run: hst is the state
     bool all_done = true, any_brk = false, any_stalled = false;
@@ -476,16 +477,17 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     int64_t left = (ctl.max_matvec - mv) / 2;   // pairs that may still be queued
     const int first = poll.posted;
     for (bool stop = false; !stop && left > 0;) {
-      const int n_pair = int(std::min<int64_t>(chunk, left));
+      const int n_pair = int(std::min<int64_t>(pace.next(pairs), left));
       bool ran = false;
       if (n_pair == kChunk && replays) HZ_TRY(replay(ctx, p, key, run_chunk, &ran, kReplayAfter));
       for (int c = 0; c < n_pair && !ran; ++c) HZ_TRY(enqueue_pair());
       pairs += n_pair;
       left -= n_pair;
       HZ_TRY(report());
-      if (poll.posted - 1 > first) {
-        HZ_TRY(poll.wait(poll.posted - 2));
-        const TqSt* h = poll.state<TqSt>(poll.posted - 2);
+      const int k = poll.posted - (pace.at_once(pairs) ? 1 : 2);
+      if (k >= first) {
+        HZ_TRY(poll.wait(k));
+        const TqSt* h = poll.state<TqSt>(k);
         bool off = true, brk = false;
         for (int i = 0; i < S.nseg; ++i) {
           off = off && h[i].done;
@@ -493,7 +495,6 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
         }
         stop = off || brk;
       }
-      chunk = std::min(chunk * 2, kChunk);
     }
     HZ_TRY(poll.wait(poll.posted - 1));
     hst = poll.state<TqSt>(poll.posted - 1);

@@ -45,7 +45,7 @@ int main() {
           L.nblk = 2;
           for (int b = 0; b < 2; ++b)
             fiber::run_block(b, kFinBlock, down,
-                             [&] { k_step<kSums, St>(L, &part[0][0], st, st, Settle<Pending>{{}, all}); });
+                             [&] { k_step<kSums, St>(L, &part[0][0], st, st, nullptr, nullptr, Settle<Pending>{{}, all}); });
           for (int s = 0; s < 2; ++s) {
             out[down][s] = st[s];
             if (st[s].restart != (all || brk) || st[s].brk != brk || st[s].pend) {
