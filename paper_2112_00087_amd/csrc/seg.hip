@@ -150,8 +150,10 @@ int seg_upload(hz_ctx ctx, SegHost* S, const std::string& tag) {
   };
   const int per = std::max(1, ceil_div(S->nblk, 1024));
   HZ_TRY(layout(1, ".vec", &S->vec));
+  S->vec.xcd_runs = 1;
   if (per > 1) HZ_TRY(layout(per, ".vecr", &S->vec_runs));
   else S->vec_runs = S->vec;
+  S->vec_runs.xcd_runs = 0;
   S->dev.nseg = S->nseg;
   S->dev.nblk = S->nblk;
   S->dev.nrows = S->nrows;
