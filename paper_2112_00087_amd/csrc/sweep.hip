@@ -1809,10 +1809,14 @@ int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T
   }
   if (ctx->tuned.empty()) load_tune_cache(ctx);
   const char* force = std::getenv("HZ_SPMM_STAGED");   // "1": staged variants only, "0": none
+  const bool tensor = A.tw.tab && !force;
   auto it = ctx->tuned.find(key);
   if (it != ctx->tuned.end() && !force) {
-    *best = variant_decode(it->second);
-    return HZ_OK;
+    const Variant v = variant_decode(it->second);
+    if ((v.tz > 0) == tensor) {     // (an entry of another kind: tuned again)
+      *best = v;
+      return HZ_OK;
+    }
   }
   // The tensor form is the only candidate kind where there is one: against the
   // best of the others it took 92 : 163 us (80x48x40, 64 columns, complex128),
@@ -1820,7 +1824,6 @@ int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T
   // in complex64 69 : 85 (80x48x40, 64); few planes per wave where the box is
   // small, whole runs where it fills the chip.
   std::vector<Variant> cands;
-  const bool tensor = A.tw.tab && !force;
   if (tensor)
     for (int nzc : {1, 2, 4, 8, 16, 32, 64}) {
       Variant v;
@@ -1884,6 +1887,7 @@ int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
+  if (force) return HZ_OK;          // the winner of some kinds only: not what later calls should take
   const int code = variant_code(*best);
   ctx->tuned[key] = code;
   save_tune_entry(key, code);
