@@ -546,7 +546,15 @@ __global__ void __launch_bounds__(kBlock) k_update(Seg L, TzOp Z, const GmSt* st
 // kernels a step; a solve of 857 steps 46 ms with the seven launches, 29 ms with
 // these replayed as a graph.
 constexpr int kFewRows = 64, kFewParts = kBlock / kFewRows;
-constexpr int kFewBlocks = 256;      // at most; four partials a lane
+//
+// Every block adds every block's partials, which ends the gain at 160 blocks, with
+// short cycles, whose vector work is small against it, at 96: 600 products, ms, the
+// general path : this one, at 48, 96, 140, 244 and 336 blocks (3,003 to 21,450
+// rows): restart 5 15.4:13.3 15.4:15.1 15.4:16.2 15.8:21.2 15.7:24.2, restart 16
+// 16.9:13.1 17.0:14.9 16.9:16.3 17.0:22.0 17.2:25.8, restart 30 19.1:13.9 19.2:15.7
+// 19.2:17.2 19.5:23.1 19.5:27.3, restart 56 23.0:16.5 23.2:19.0 23.4:21.8 24.7:29.6
+// 24.5:36.8.
+constexpr int few_blocks(int m) { return m < 16 ? 96 : 160; }
 constexpr int kFewMaxM = 56;         // basis vectors per thread: 14
 
 // Sum of nb partials, by one wave; the same value in every lane.
@@ -820,10 +828,10 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   DevBuf* Vb = ctx->buf(p + "V", sizeof(cx<T>) * ld * (m + 1), &rc);
   if (rc) return rc;
   const int nchunk = ceil_div(m + 1, NV);
-  // One small system in the tensor form takes its own kernels: up to 256 blocks
-  // of 64 rows and 56 basis vectors, beyond which adding the partials in every
-  // block costs more than the launches it saves.
-  const bool few = A.tz.on && S.nseg == 1 && m <= kFewMaxM && ld <= int64_t(kFewBlocks) * kFewRows;
+  // One small system in the tensor form takes its own kernels: up to few_blocks
+  // blocks of 64 rows, beyond which adding the partials in every block costs more than
+  // the launches it saves, and 56 basis vectors (14 a thread, in registers).
+  const bool few = A.tz.on && S.nseg == 1 && m <= kFewMaxM && ld <= int64_t(few_blocks(m)) * kFewRows;
   int64_t np = std::max(int64_t(nchunk) * S.nblk * 2 * NV, int64_t(prod_seg(A, S.dev).nblk));
   if (few) np = std::max(np, (4 * kFewMaxM + 1) * (ld / kFewRows));
   DevBuf* part = ctx->buf(p + "part", sizeof(double) * np, &rc);
