@@ -880,7 +880,10 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   void* hp = nullptr;
   HZ_TRY(ctx_pinned(ctx, sizeof(GmSt) * S.nseg, &hp));
   GmSt* hst = static_cast<GmSt*>(hp);
-  std::vector<int64_t> mv(S.nseg, 0);
+  std::vector<int64_t> mv(S.nseg, 0), chk_mv(S.nseg, 0);
+  std::vector<double> chk(S.nseg, -1.0);   // residual norm at the last stall checkpoint
+  std::vector<int> stalled(S.nseg, 0), met(S.nseg, 0), missed(S.nseg, 0);
+  constexpr int kMissed = 4;
   int64_t mv_max = 0;
   const int grid = S.nblk;
   // one restart cycle of mc steps (0: the residual alone)
@@ -936,14 +939,28 @@ int gmres_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     if (!ran) HZ_TRY(enqueue_cycle(mc));
     HZ_HIP(hipMemcpyAsync(hst, st, sizeof(GmSt) * S.nseg, hipMemcpyDeviceToHost, s));
     HZ_HIP(hipStreamSynchronize(s));
-    bool all_done = true;
+    bool all_done = true, all_ended = true;   // ended: done, or stalled
     for (int i = 0; i < S.nseg; ++i) {
       mv[i] += 1;
       if (!hst[i].done) mv[i] += hst[i].k;
       mv_max = std::max(mv_max, mv[i]);
       all_done = all_done && (hst[i].done || hst[i].nan);
+      if (ctl.stall_halfsteps > 0) {
+        // beta: the residual this cycle began with; a residual at its rounding level shows as
+        // cycles whose estimate meets the target and whose residual then does not
+        missed[i] += met[i];
+        if (chk[i] < 0.0) chk[i] = hst[i].beta;
+        if (mv[i] - chk_mv[i] >= ctl.stall_halfsteps || missed[i] >= kMissed) {
+          stalled[i] = hst[i].beta > 0.5 * chk[i];
+          chk[i] = hst[i].beta;
+          chk_mv[i] = mv[i];
+          missed[i] = 0;
+        }
+        met[i] = hst[i].est * hst[i].est <= hst[i].thr2;
+      }
+      all_ended = all_ended && (hst[i].done || hst[i].nan || stalled[i]);
     }
-    if (all_done || mc < 1 || mv_max >= ctl.max_matvec) break;
+    if (all_done || all_ended || mc < 1 || mv_max >= ctl.max_matvec) break;
   }
   out->iters.resize(S.nseg);
   out->matvecs.resize(S.nseg);

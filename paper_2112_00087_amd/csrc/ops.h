@@ -151,8 +151,11 @@ struct KrylovCtl {
   int restart = 30;               // GMRES
   int ell = 4;                    // BiCGStab(l)
   // TFQMR: a quasi-residual bound that has not halved over this many
-  // half-steps ends the solve (0: never).  Set for complex64 inner solves
-  // of the refinement, whose bound can stall above the inner tolerance.
+  // half-steps ends the solve (0: never); GMRES: a residual over as many
+  // products, or over four cycles that met the target by their estimate alone, on
+  // every segment that is not done.  Set for complex64 inner solves
+  // of the refinement, which can stall above the inner tolerance (a GMRES solve
+  // restarted from its iterate loses nothing by it).
   int stall_halfsteps = 0;
 };
 struct KrylovOut {
