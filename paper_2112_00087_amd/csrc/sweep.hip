@@ -1764,10 +1764,10 @@ inline Variant variant_decode(int code) {
   v.lds = un(code % 10);
   return v;
 }
-// (contexts with a tensor form have their own entries)
-std::string tune_key(int64_t n, int64_t nnz, int s, int bytes, bool tensor) {
+// (contexts with a tensor form have their own entries, with an absorption field others again)
+std::string tune_key(int64_t n, int64_t nnz, int s, int bytes, const TwOp& W) {
   std::ostringstream o;
-  o << (tensor ? "spmm6 n=" : "spmm5 n=") << n << " nnz=" << nnz << " s=" << s << " t=" << bytes;
+  o << (!W.tab ? "spmm5 n=" : W.eta ? "spmm7 n=" : "spmm6 n=") << n << " nnz=" << nnz << " s=" << s << " t=" << bytes;
   return o.str();
 }
 
@@ -1793,44 +1793,49 @@ void save_tune_entry(const std::string& key, int code) {
 template <typename T>
 int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T>& A, const double* st,
              const cx<T>* Z, cx<T>* Y, Variant* best) {
-  const std::string key = tune_key(ctx->h.n, int64_t(ctx->h.col.size()), s, int(sizeof(T)),
-                                   A.tw.tab != nullptr);
+  const std::string key = tune_key(ctx->h.n, int64_t(ctx->h.col.size()), s, int(sizeof(T)), A.tw);
+  auto fits = [&](const Variant& v) {
+    return v.tz > 0    ? A.tw.tab != nullptr
+           : v.zl > 0  ? zl_fits<T>(v, s, A)
+           : v.lds > 0 ? (A.hblocks > 0 && s % v.lds == 0 && lds_bytes(A, v.lds) <= lds_limit())
+                       : (v.cpl <= s && v.bs >= s / v.cpl);
+  };
   if (const char* fv = std::getenv("HZ_SPMM_VARIANT")) {
     // one given variant (tests and measurements), if it fits this width
     const Variant v = variant_decode(std::atoi(fv));
-    const bool fits = v.tz > 0    ? A.tw.tab != nullptr
-                      : v.zl > 0  ? zl_fits<T>(v, s, A)
-                      : v.lds > 0 ? (A.hblocks > 0 && s % v.lds == 0 && lds_bytes(A, v.lds) <= lds_limit())
-                                  : (v.cpl <= s && v.bs >= s / v.cpl);
-    if (fits) {
+    if (fits(v)) {
       *best = v;
       return HZ_OK;
     }
   }
   if (ctx->tuned.empty()) load_tune_cache(ctx);
   const char* force = std::getenv("HZ_SPMM_STAGED");   // "1": staged variants only, "0": none
-  const bool tensor = A.tw.tab && !force;
+  // The tensor form is the only candidate kind where there is one without an
+  // absorption field: against the best of the others it took 92 : 163 us (80x48x40,
+  // 64 columns, complex128), 22.5 : 43 (60x36x30, 32), 13 : 126 (80x48x40, 4), 5.4 :
+  // 10.4 (20x12x10, 1) and in complex64 69 : 85 (80x48x40, 64), 6.2 : 6.2 (8x6x5, 64).
+  // The field's element sums cost it more than the 8 or 4 bytes an entry that they
+  // cost the others: 118 : 200 (80x48x40, 64), 76 : 101 (32), 18 : 184 (4), 8.0 : 8.5
+  // (20x12x10, 16), but in complex64 98 : 98, 76 : 74, 19 : 153, 8.3 : 7.8; there all
+  // kinds are timed, from 1,024 nodes on (below, they differ by less than 3 us).
+  const bool tensor = A.tw.tab && !force, tensor_only = tensor && (!A.tw.eta || ctx->h.n <= 1024);
   auto it = ctx->tuned.find(key);
   if (it != ctx->tuned.end() && !force) {
     const Variant v = variant_decode(it->second);
-    if ((v.tz > 0) == tensor) {     // (an entry of another kind: tuned again)
+    if (tensor_only ? v.tz > 0 : fits(v)) {     // (an entry of another kind: tuned again)
       *best = v;
       return HZ_OK;
     }
   }
-  // The tensor form is the only candidate kind where there is one: against the
-  // best of the others it took 92 : 163 us (80x48x40, 64 columns, complex128),
-  // 24 : 46 (57x43x31, 32), 13 : 126 (80x48x40, 4), 8.4 : 10.3 (20x12x10, 1) and
-  // in complex64 69 : 85 (80x48x40, 64); few planes per wave where the box is
-  // small, whole runs where it fills the chip.
   std::vector<Variant> cands;
+  // few planes per wave where the box is small, whole runs where it fills the chip
   if (tensor)
     for (int nzc : {1, 2, 4, 8, 16, 32, 64}) {
       Variant v;
       v.tz = nzc;
       if (nzc < 2 * A.tw.nz) cands.push_back(v);
     }
-  if (!tensor && !(force && force[0] == '1'))
+  if (!tensor_only && !(force && force[0] == '1'))
     for (int xcd : {0, 1})
       for (int cpl : {1, 2})
         for (int bs : {128, 256, 512}) {
@@ -1842,7 +1847,7 @@ int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T
           v.xcd = xcd;
           cands.push_back(v);
         }
-  if (!tensor && !(force && force[0] == '0'))
+  if (!tensor_only && !(force && force[0] == '0'))
     for (int cg : {1, 2, 4, 8, 16})
       if (A.hblocks > 0 && cg <= s && lds_bytes(A, cg) <= lds_limit()) {
         Variant v;
@@ -1850,7 +1855,7 @@ int autotune(hz_ctx ctx, hipStream_t stream, int64_t nrows, int s, const RowOp<T
         v.lds = cg;
         cands.push_back(v);
       }
-  if (!tensor && !(force && force[0] == '1'))
+  if (!tensor_only && !(force && force[0] == '1'))
     for (int bc : {0, 1})
       for (const ZlShape& h : kZlShapes)
         for (int nzc : {2, 4, 8, 16}) {

@@ -21,7 +21,9 @@
 // form took 163 us, streaming 27 pairs a row through the broadcast unit); the
 // patch is 2 x 2 because its 4 rows in 16 loads (4 from L1 / L2 per row,
 // against 9 in the stencil form) still leave two waves per SIMD with the next
-// plane's loads in flight.  With an absorption field 122 : 201 us there.
+// plane's loads in flight.  With an absorption field 118 : 200 us there; fewer
+// columns then leave one wave per SIMD: at two, 54 registers went to scratch memory
+// (32 columns at 80x48x40 124 -> 76 us, 16 at 20x12x10 12.1 -> 8.0 us).
 // On small blocks the march is a chain of load latencies: 13 : 126 us at
 // 80x48x40 and 4 columns, 10.8 : 13.4 us at 37x25x19 and 13.  (One plane a
 // wave with all its loads at once took 11.2 us there, and 6.9 : 7.3 us at 4.)
@@ -53,8 +55,8 @@ __device__ __forceinline__ void tw_zero_tail(int64_t n, int64_t tail, cx<T>* __r
 }
 
 template <typename T, int LS, bool ETA>
-__global__ void __launch_bounds__(kTwWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
-    k_spmm_tz(TwOp A, int npx, int npy, int zc, int64_t tail, const double* __restrict__ kc,
+__global__ void __launch_bounds__(kTwWaves * kWave)
+    __attribute__((amdgpu_waves_per_eu(ETA && LS < 6 ? 1 : 2, ETA && LS < 6 ? 1 : 2))) k_spmm_tz(TwOp A, int npx, int npy, int zc, int64_t tail, const double* __restrict__ kc,
               const cx<T>* __restrict__ X, cx<T>* __restrict__ Y) {
   constexpr int S = 1 << LS, G = kWave >> LS;
   tw_zero_tail((int64_t(A.nx) * A.ny * A.nz) << LS, tail, Y);

@@ -35,3 +35,32 @@ def test_forced_variants_are_not_kept(monkeypatch, tmp_path):
     m = P.Helmholtz(mesh, 0.02 * np.ones(6))
     assert m.apply_sweep(freqs, X)[1] > TENSOR
     m.close()
+
+
+@pytest.mark.parametrize("size,tensor", [((8, 8, 8), True), ((16, 10, 9), None)])
+def test_absorption_field_variants(monkeypatch, size, tensor):
+    """With an absorption field small boxes take the tensor form untimed, others
+    the fastest kind; a context that gains a field does not keep the plain
+    form's choice.  Every kind gives the same product (FP64 sums of at most 27
+    products a row, each below 2e-15 of the row's largest term, and 1e-13 of the
+    norm for their rounding)."""
+    import paper_2112_00087_amd as P
+    mesh = W.box_mesh(*size)
+    rng = np.random.default_rng(2)
+    eta = rng.uniform(0.0, 0.02, mesh["n_elems"])
+    for nf in (3, 64):
+        freqs = np.linspace(50.0, 120.0, nf)
+        X = torch.randn(mesh["n_nodes"], nf, dtype=torch.complex128, device="cuda",
+                        generator=torch.Generator("cuda").manual_seed(5))
+        m = P.Helmholtz(mesh, 0.02 * np.ones(6))
+        assert m.apply_sweep(freqs, X)[1] > TENSOR
+        m.set_params(None, eta)
+        Y, code = m.apply_sweep(freqs, X)
+        if tensor:
+            assert code > TENSOR
+        monkeypatch.setenv("HZ_SPMM_VARIANT", "1128" if code > TENSOR else str(TENSOR + 2))
+        Z, other = m.apply_sweep(freqs, X)
+        monkeypatch.delenv("HZ_SPMM_VARIANT")
+        assert (other > TENSOR) != (code > TENSOR)
+        assert float((Y - Z).norm() / Z.norm()) < 1e-13
+        m.close()
