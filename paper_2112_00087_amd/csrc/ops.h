@@ -218,13 +218,16 @@ struct Pace {
 // launching them one by one.
 //
 // A capture takes 40 us (BiCGStab, 40 kernels) to 100 us (GMRES(30), 123
-// kernels) of host time and saves 10 us a chunk of 8 BiCGStab iterations and
-// 140 us a GMRES(30) cycle, so runs are captured once the same one has been
-// launched kReplayAfter times, in one solve or over several: a loop over 16
-// frequencies at 20x12x10, BiCGStab(2) to 20 products, took 7.2 ms capturing at
-// each solve's first full chunk and 6.4 ms so (6.5 without graphs), to 60 products
-// 15.1 and 14.3 ms (15.0 without), GMRES(30) to 200 products 87.3 and 75.6 ms
-// (86.4 without).
+// kernels) of host time, the first of a context 0.2 to 0.9 ms, and saves 10 us a
+// chunk of 8 BiCGStab iterations and 140 us a GMRES(30) cycle, so runs are captured
+// once the same one has been launched kReplayAfter (Gmres) times, in one solve or
+// over several: about where a capture pays for itself.  GMRES(30) to 100 products
+// in a new context took 4.2 ms at 40x24x20 before there were replays, 4.4 ms
+// captured at its second cycle, 4.1 ms so, and 3.35 ms once captured.  A loop over
+// 16 frequencies at 20x12x10: BiCGStab(2) to 20 products 7.2 ms capturing at each
+// solve's first full chunk and 6.4 ms so (6.5 without graphs), to 60 products 15.1
+// and 14.3 ms (15.0 without), GMRES(30) to 200 products 87.3 and 75.6 ms (86.4
+// without).
 //
 // On larger systems the device is the slower of the two and the gap between a
 // graph's kernels a little longer than between launches.  600 products,
@@ -252,7 +255,7 @@ struct ReplayKey {
     return add(Z.ed).add(Z.k2).add(Z.lp);
   }
 };
-constexpr int kReplayAfter = 3, kReplayAfterGmres = 1;
+constexpr int kReplayAfter = 8, kReplayAfterGmres = 6;
 constexpr int64_t kReplayRowsTensor = 196608, kReplayRowsStored = 49152, kReplayRowsGmres = 262144;
 // Replays the run of body on the context's stream, capturing it first if the
 // same run has come up more than `after` times; *ran = false if it has to be

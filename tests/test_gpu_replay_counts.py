@@ -65,7 +65,7 @@ def test_short_solves_capture_on_repetition(monkeypatch, method, kw):
     mesh = W.box_mesh(12, 9, 8)
     on, off = _pair(monkeypatch, mesh, 0.02 * np.ones(6), None)
     f = torch.as_tensor(rng.standard_normal(on.n) + 0j, device="cuda")
-    for step, freq in enumerate((70.0, 85.0, 100.0)):
+    for step, freq in enumerate((70.0, 85.0, 100.0) * 3):
         on.set_frequency(freq)
         on.solve(f, method=method, tol=1e-30, max_matvec={"gmres": 9, "bicgstabl": 48}.get(method, 72), **kw)
         captures, replays = on.replay_counts()
