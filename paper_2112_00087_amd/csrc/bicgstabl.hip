@@ -475,8 +475,8 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     }
   };
 
-  const int kChunk = l >= 4 ? 1 : 2;   // cycles between reports
   const bool replays = nr <= (A.tz.on ? kReplayRowsTensor : kReplayRowsStored);
+  const int kChunk = l >= 4 && !replays ? 1 : 2;   // cycles between reports
   const Pace pace = {1, 1, kChunk, l >= 4 ? 4 : replays ? 3 : 1, replays};
   ReplayKey key;
   key.op(A).add(V).add(P).add(W).add(st).add(S.nseg).add(l);
