@@ -15,12 +15,13 @@
 
 namespace {
 
+enum { kBiNone = 0, kBiAlpha, kBiOmega, kBiRho };
 struct BiSt {
   z_t rho, rho_old, alpha, omega;
   z_t beta;                       // (rho / rho_old) (alpha / omega) for the next p update
   double rr, ss, thr2, rhat2;
   int iter, done, early, reset;
-  int nan, pend;                  // pend: the sums of the rho step are formed
+  int nan, due;                   // due: the step that the sums formed next (or last) are for
 };
 
 template <typename T>
@@ -48,12 +49,13 @@ __device__ __forceinline__ void bi_resid(BiSt& S, const double* o) {
   S.rhat2 = rr;
   S.early = 0;
   S.reset = 0;
-  S.pend = 0;
+  S.due = kBiAlpha;
   S.nan = !isfinite(rr);
   S.done = (rr <= S.thr2) || S.nan;
 }
 __device__ __forceinline__ void bi_alpha(BiSt& S, const double* o) {
   S.reset = 0;
+  S.due = kBiOmega;
   const z_t rv = {o[0], o[1]};
   if (norm2(rv) == 0.0 || !isfinite(o[0]) || !isfinite(o[1])) {
     S.alpha = z_t{0.0, 0.0};   // minimal-residual step this iteration, restart after it
@@ -69,10 +71,10 @@ __device__ __forceinline__ void bi_omega(BiSt& S, const double* o) {
   S.ss = ss;
   S.early = (ss <= S.thr2) ? 1 : 0;
   S.omega = (tt > 0.0 && !S.early) ? z_t{re / tt, im / tt} : z_t{0.0, 0.0};
-  S.pend = 1;                // k_xr forms the sums of the rho step
+  S.due = kBiRho;            // k_xr forms the sums of the rho step
 }
 __device__ __forceinline__ void bi_rho(BiSt& S, const double* o) {
-  S.pend = 0;
+  S.due = kBiAlpha;
   if (S.early) {
     S.iter += 1;
     S.rr = S.ss;
@@ -105,15 +107,15 @@ struct BiResid {
   __device__ void operator()(BiSt& S, const double* o) const { bi_resid(S, o); }
 };
 struct BiAlpha {
-  __device__ bool on(const BiSt& S) const { return !S.done; }
+  __device__ bool on(const BiSt& S) const { return !S.done && S.due == kBiAlpha; }
   __device__ void operator()(BiSt& S, const double* o) const { bi_alpha(S, o); }
 };
 struct BiOmega {
-  __device__ bool on(const BiSt& S) const { return !S.done; }
+  __device__ bool on(const BiSt& S) const { return !S.done && S.due == kBiOmega; }
   __device__ void operator()(BiSt& S, const double* o) const { bi_omega(S, o); }
 };
 struct BiRho {
-  __device__ bool on(const BiSt& S) const { return S.pend; }
+  __device__ bool on(const BiSt& S) const { return S.due == kBiRho; }
   __device__ void operator()(BiSt& S, const double* o) const { bi_rho(S, o); }
 };
 
@@ -139,7 +141,7 @@ __global__ void __launch_bounds__(kBlock) k_resid(Seg L, SellOp<T> A, BiV<T> V, 
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_p(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V) {
   const Tile t = vec_tile(L);
-  const BiSt& S = advance<3>(P, in, out, t, first_block(L, t), BiRho{});
+  const BiSt& S = advance<3, (F < kFormTensor)>(P, in, out, t, first_block(L, t), BiRho{});
   if (S.done) return;
   const TzSeg B = form_seg<F>(Z, t);
   if (S.reset) {
@@ -179,7 +181,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_v(Seg L, SellOp<T> A, const BiSt* st, BiV<T>
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_s(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V) {
   const Tile t = vec_tile(L);
-  const BiSt& S = advance<2>(P, in, out, t, first_block(L, t), BiAlpha{});
+  const BiSt& S = advance<2, (F < kFormTensor)>(P, in, out, t, first_block(L, t), BiAlpha{});
   if (S.done) return;
   const TzSeg B = form_seg<F>(Z, t);
   const z_t alpha = S.alpha;
@@ -211,7 +213,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_t(Seg L, SellOp<T> A, const BiSt* st, BiV<T>
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_xr(Seg L, TzOp Z, Part P, const BiSt* in, BiSt* out, BiV<T> V, double* part) {
   const SumTile t = vec_tile_sums(L);
-  const BiSt& S = advance<4>(P, in, out, t, first_block(L, t), BiOmega{});
+  const BiSt& S = advance<4, (F < kFormTensor)>(P, in, out, t, first_block(L, t), BiOmega{});
   if (S.done) return;
   const TzSeg B = form_seg<F>(Z, t);
   double q[3] = {0.0, 0.0, 0.0};
@@ -259,12 +261,12 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
     if (rc) return rc;
     *vecs[i] = b->as<cx<T>>();
   }
-  // state slots: after rho (start of an iteration), alpha, omega
-  DevBuf* stb = ctx->buf(p + "st", sizeof(BiSt) * 3 * S.nseg, &rc);
+  // state slots: after rho (start of an iteration), alpha, omega; one nobody reads
+  DevBuf* stb = ctx->buf(p + "st", sizeof(BiSt) * 4 * S.nseg, &rc);
   if (rc) return rc;
   DevBuf* fnb = ctx->buf(p + "fn2", sizeof(double) * S.nseg, &rc);
   if (rc) return rc;
-  BiSt *st = stb->as<BiSt>(), *st_a = st + S.nseg, *st_b = st_a + S.nseg;   // st: what an iteration starts from
+  BiSt *st = stb->as<BiSt>(), *st_a = st + S.nseg, *st_b = st_a + S.nseg, *st_u = st_b + S.nseg;   // st: what an iteration starts from
   hipStream_t s = ctx->stream;
   const Seg& L = S.dev;
   const Seg& P = prod_seg(A, L);   // the products' layout
@@ -275,7 +277,7 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
   out->fnorm.resize(S.nseg);
   for (int i = 0; i < S.nseg; ++i) out->fnorm[i] = std::sqrt(fn2[i]);
   HZ_HIP(hipMemcpyAsync(fnb->p, fn2.data(), sizeof(double) * S.nseg, hipMemcpyHostToDevice, s));
-  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(BiSt) * 3 * S.nseg, s));
+  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(BiSt) * 4 * S.nseg, s));
   k_set_thr<<<ceil_div(S.nseg, kBlock), kBlock, 0, s>>>(S.nseg, st, fnb->as<double>(), ctl.tol, 1);
   HZ_HIP(hipGetLastError());
 
@@ -304,13 +306,13 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
     return poll.posted_one();
   };
   auto enqueue_iter = [&]() -> int {
-    HZ_BY_SCALING(A, k_p<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pn.part, st, st_a, V));
+    HZ_BY_SCALING(A, k_p<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pn.part, pn.from(st, st_a), pn.to(st_a, st_u), V));
     HZ_BY_FORM(A, k_v<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st_a, V, pa.raw));
     HZ_TRY(pa.step<2>(s, st_a, st_b, BiAlpha{}));
-    HZ_BY_SCALING(A, k_s<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st_a, st_b, V));
+    HZ_BY_SCALING(A, k_s<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, pa.from(st_a, st_b), pa.to(st_b, st_u), V));
     HZ_BY_FORM(A, k_t<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st_b, V, po.raw));
     HZ_TRY(po.step<4>(s, st_b, st, BiOmega{}));
-    HZ_BY_SCALING(A, k_xr<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, st_b, st, V, pn.raw));
+    HZ_BY_SCALING(A, k_xr<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, po.from(st_b, st), po.to(st, st_u), V, pn.raw));
     HZ_TRY(pn.step<3>(s, st, st_a, BiRho{}));
     HZ_HIP(hipGetLastError());
     return HZ_OK;

@@ -33,12 +33,13 @@ namespace {
 
 constexpr int kMaxL = 8;
 
+enum { kBlNone = 0, kBlAlpha, kBlBeta, kBlCycle };
 struct BlSt {
   z_t rho0, alpha, omega, beta;
   z_t gam[kMaxL + 1];   // gamma_1..gamma_l
   double rr, thr2, rhat2;
   int iter, done, brk, nan, restart, trunc;
-  int pend, pad;        // pend: the sums of the cycle's end are formed
+  int due, pad;         // due: the step that the sums formed next (or last) are for
 };
 
 template <typename T>
@@ -77,16 +78,18 @@ __device__ __forceinline__ void bl_resid(BlSt& S, const double* tot) {
   S.brk = 0;
   S.trunc = 0;
   S.restart = 0;
-  S.pend = 0;
+  S.due = kBlAlpha;
 }
 // alpha = rho0 / rt^H u_{j+1}
 __device__ __forceinline__ void bl_alpha(BlSt& S, const double* tot) {
+  S.due = kBlBeta;
   const z_t sg = {tot[0], tot[1]};
   if (norm2(sg) == 0.0 || !isfinite(sg.re) || !isfinite(sg.im)) S.brk = 1;
   else S.alpha = cdiv(S.rho0, sg);
 }
 // rho1 = rt^H r_{j+1}; beta = alpha rho1 / rho0; rho0 = rho1
 __device__ __forceinline__ void bl_beta(BlSt& S, const double* tot) {
+  S.due = kBlAlpha;
   const z_t rho1 = {tot[0], tot[1]};
   if (norm2(S.rho0) == 0.0 || !isfinite(rho1.re) || !isfinite(rho1.im)) {
     S.brk = 1;
@@ -112,10 +115,10 @@ __device__ __forceinline__ void bl_mr(BlSt& S, const double* tot, double piv) {
   for (int i = 0; i < LL; ++i) S.gam[i + 1] = g[i];
   S.omega = g[LL - 1];
   S.trunc = (m < LL) ? 1 : 0;
-  S.pend = !S.brk;           // k_bl_update forms the sums of the cycle's end
+  S.due = S.brk ? kBlNone : kBlCycle;   // k_bl_update forms the sums of the cycle's end
 }
 __device__ __forceinline__ void bl_cycle(BlSt& S, const double* tot) {
-  S.pend = 0;
+  S.due = kBlAlpha;
   const z_t rho1 = {tot[0], tot[1]};
   const double rr = tot[2];
   S.iter += 1;
@@ -143,11 +146,11 @@ struct BlResid {
   __device__ void operator()(BlSt& S, const double* o) const { bl_resid(S, o); }
 };
 struct BlAlpha {
-  __device__ bool on(const BlSt& S) const { return !bl_off(S); }
+  __device__ bool on(const BlSt& S) const { return !bl_off(S) && S.due == kBlAlpha; }
   __device__ void operator()(BlSt& S, const double* o) const { bl_alpha(S, o); }
 };
 struct BlBeta {
-  __device__ bool on(const BlSt& S) const { return !bl_off(S); }
+  __device__ bool on(const BlSt& S) const { return !bl_off(S) && S.due == kBlBeta; }
   __device__ void operator()(BlSt& S, const double* o) const { bl_beta(S, o); }
 };
 template <int LL>
@@ -157,7 +160,7 @@ struct BlMr {
   __device__ void operator()(BlSt& S, const double* o) const { bl_mr<LL>(S, o, piv); }
 };
 struct BlCycle {
-  __device__ bool on(const BlSt& S) const { return S.pend; }
+  __device__ bool on(const BlSt& S) const { return S.due == kBlCycle; }
   __device__ void operator()(BlSt& S, const double* o) const { bl_cycle(S, o); }
 };
 
@@ -210,8 +213,8 @@ template <typename T, int F, int J>
 __global__ void __launch_bounds__(kBlock) k_bl_u(Seg L, TzOp Z, Part P, Part Pc, const BlSt* in, BlSt* out, BlV<T> V,
                                                  int j) {
   const Tile t = vec_tile(L);
-  const BlSt& S = j == 0 ? advance<3>(Pc, in, out, t, first_block(L, t), BlCycle{})
-                         : advance<2>(P, in, out, t, first_block(L, t), BlBeta{});
+  const BlSt& S = j == 0 ? advance<3, (F < kFormTensor)>(Pc, in, out, t, first_block(L, t), BlCycle{})
+                         : advance<2, (F < kFormTensor)>(P, in, out, t, first_block(L, t), BlBeta{});
   if (bl_off(S)) return;
   const TzSeg B = form_seg<F>(Z, t);
   const z_t b = S.beta;
@@ -257,7 +260,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_bl_prod(Seg L, SellOp<T> A, const BlSt* st, 
 template <typename T, int F, int J>
 __global__ void __launch_bounds__(kBlock) k_bl_r(Seg L, TzOp Z, Part P, const BlSt* in, BlSt* out, BlV<T> V, int j) {
   const Tile t = vec_tile(L);
-  const BlSt& S = advance<2>(P, in, out, t, first_block(L, t), BlAlpha{});
+  const BlSt& S = advance<2, (F < kFormTensor)>(P, in, out, t, first_block(L, t), BlAlpha{});
   if (bl_off(S)) return;
   const TzSeg B = form_seg<F>(Z, t);
   const z_t a = S.alpha;
@@ -323,7 +326,7 @@ __global__ void __launch_bounds__(kBlock) k_bl_mr(Part P, const BlSt* in, BlSt* 
   Tile t;
   t.tile = t.seg = blockIdx.x;
   t.row = 0;
-  advance<gram_nq<LL>()>(P, in, out, t, true, BlMr<LL>{piv});
+  advance<gram_nq<LL>(), false>(P, in, out, t, true, BlMr<LL>{piv});
 }
 
 // x += sum gamma_j r_{j-1}; r_0 -= sum gamma_j r_j; u_0 -= sum gamma_j u_j;
@@ -401,12 +404,12 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
   V.e = A.tz.on ? vec("e") : x;
   V.in = A.tz.on ? vec("in") : nullptr;
   if (rc) return rc;
-  // state slots: start of a cycle, after beta, after alpha
-  DevBuf* stb = ctx->buf(p + "st", sizeof(BlSt) * 3 * S.nseg, &rc);
+  // state slots: start of a cycle, after beta, after alpha; one nobody reads
+  DevBuf* stb = ctx->buf(p + "st", sizeof(BlSt) * 4 * S.nseg, &rc);
   if (rc) return rc;
   DevBuf* fnb = ctx->buf(p + "fn2", sizeof(double) * S.nseg, &rc);
   if (rc) return rc;
-  BlSt *st = stb->as<BlSt>(), *st_b = st + S.nseg, *st_a = st_b + S.nseg;   // st: what a cycle starts from
+  BlSt *st = stb->as<BlSt>(), *st_b = st + S.nseg, *st_a = st_b + S.nseg, *st_u = st_a + S.nseg;   // st: what a cycle starts from
   hipStream_t s = ctx->stream;
   const Seg& L = S.dev;
   const Seg& P = prod_seg(A, L);   // the products' layout
@@ -416,7 +419,7 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
   out->fnorm.resize(S.nseg);
   for (int i = 0; i < S.nseg; ++i) out->fnorm[i] = std::sqrt(fn2[i]);
   HZ_HIP(hipMemcpyAsync(fnb->p, fn2.data(), sizeof(double) * S.nseg, hipMemcpyHostToDevice, s));
-  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(BlSt) * 3 * S.nseg, s));
+  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(BlSt) * 4 * S.nseg, s));
   k_bl_set_thr<<<ceil_div(S.nseg, kBlock), kBlock, 0, s>>>(S.nseg, st, fnb->as<double>(), ctl.tol);
   HZ_HIP(hipGetLastError());
 
@@ -449,12 +452,13 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
   };
   auto enqueue_cycle = [&]() -> int {
     for (int j = 0; j < l; ++j) {
-      const BlSt* from = j == 0 ? st : st_a;
-      HZ_BY_STEP(j, HZ_BY_SCALING(A, k_bl_u<T, F, J><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pb.part, pc.part, from, st_b, V, j)));
+      const BlSt* in = j == 0 ? st : st_a;
+      const PartBuf& pu = j == 0 ? pc : pb;   // whose sums k_bl_u's step takes
+      HZ_BY_STEP(j, HZ_BY_SCALING(A, k_bl_u<T, F, J><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pb.part, pc.part, pu.from(in, st_b), pu.to(st_b, st_u), V, j)));
       const cx<T>* uj = A.tz.on ? V.in : V.u[j];
       HZ_BY_FORM(A, k_bl_prod<T, F, true><<<P.nblk, kBlock, 0, s>>>(P, A, st_b, uj, V.u[j + 1], V.rt, pa.raw));
       HZ_TRY(pa.step<2>(s, st_b, st_a, BlAlpha{}));
-      HZ_BY_STEP(j, HZ_BY_SCALING(A, k_bl_r<T, F, J><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st_b, st_a, V, j)));
+      HZ_BY_STEP(j, HZ_BY_SCALING(A, k_bl_r<T, F, J><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, pa.from(st_b, st_a), pa.to(st_a, st_u), V, j)));
       const cx<T>* rj = A.tz.on ? V.in : V.r[j];
       if (j + 1 < l) {
         HZ_BY_FORM(A, k_bl_prod<T, F, true><<<P.nblk, kBlock, 0, s>>>(P, A, st_a, rj, V.r[j + 1], V.rt, pb.raw));

@@ -314,7 +314,8 @@ int replay(hz_ctx ctx, const std::string& tag, const ReplayKey& key, Body body, 
 constexpr int64_t kMaxConsumed = int64_t(1024) * 1024;
 struct PartBuf {
   double* raw = nullptr;             // where the producing kernel stores
-  Part part;                         // what the consuming kernels add (p NULL: nothing, step has run)
+  Part part;                         // what the consuming kernels add (nothing, if step makes the step)
+  bool stepped = false;
   Seg lay;
   // consumers: blocks of the kernels that would add the partials (0: one block
   // per segment does, by advance)
@@ -322,7 +323,13 @@ struct PartBuf {
   // The scalar step from state in to out, if the consumers do not make it
   // themselves; always, at a restart or for the host.
   template <int NQ, class St, class Step>
-  int step(hipStream_t s, const St* in, St* out, Step f) const { return part.p ? HZ_OK : step_now<NQ>(s, in, out, f); }
+  int step(hipStream_t s, const St* in, St* out, Step f) const { return stepped ? step_now<NQ>(s, in, out, f) : HZ_OK; }
+  // The slots of a consuming kernel whose step goes from in to out: it starts from
+  // out if the step has been made, and then leaves its copy in a slot nobody reads.
+  template <class St>
+  const St* from(const St* in, const St* out) const { return stepped ? out : in; }
+  template <class St>
+  St* to(St* out, St* unread) const { return stepped ? unread : out; }
   template <int NQ, class St, class Step>
   int step_now(hipStream_t s, const St* in, St* out, Step f, St* copy = nullptr, St* next = nullptr) const {
     k_step<NQ, St, Step><<<lay.nseg, kFinBlock, 0, s>>>(lay, raw, in, out, copy, next, f);

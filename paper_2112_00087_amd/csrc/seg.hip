@@ -96,15 +96,15 @@ int StatePoll::wait(int k) {
 
 int PartBuf::init(hz_ctx ctx, const SegHost& S, const Seg& L, int nq, int consumers, const std::string& name) {
   int rc = 0;
-  const bool many = int64_t(L.nblk) * consumers > kMaxConsumed * S.nseg;
+  stepped = int64_t(L.nblk) * consumers > kMaxConsumed * S.nseg;
   DevBuf* b = ctx->buf(name, sizeof(double) * nq * size_t(L.nblk), &rc);
   if (rc) return rc;
   raw = b->as<double>();
   lay = L;
   part.nseg = S.nseg;
-  part.p = many ? nullptr : raw;
-  part.seg_blk = L.seg_blk;
-  part.nblk = L.nblk;
+  part.p = raw;
+  part.seg_blk = stepped ? S.zeros : L.seg_blk;
+  part.nblk = stepped ? 0 : L.nblk;
   return HZ_OK;
 }
 
@@ -154,6 +154,11 @@ int seg_upload(hz_ctx ctx, SegHost* S, const std::string& tag) {
   if (per > 1) HZ_TRY(layout(per, ".vecr", &S->vec_runs));
   else S->vec_runs = S->vec;
   S->vec_runs.xcd_runs = 0;
+  DevBuf* zb = ctx->buf(tag + ".zeros", sizeof(int) * (S->nseg + 1), &rc);
+  if (rc) return rc;
+  const std::vector<int> zeros(S->nseg + 1, 0);
+  HZ_HIP(hipMemcpy(zb->p, zeros.data(), sizeof(int) * (S->nseg + 1), hipMemcpyHostToDevice));
+  S->zeros = zb->as<int>();
   S->dev.nseg = S->nseg;
   S->dev.nblk = S->nblk;
   S->dev.nrows = S->nrows;

@@ -29,12 +29,13 @@
 
 namespace {
 
+enum { kTqNone = 0, kTqAlpha, kTqEven, kTqOdd };
 struct TqSt {
   z_t alpha, rho, beta, eta;
   double theta, tau, thr, thr2, rr;
   double chk;           // quasi-residual bound at the last stall checkpoint
   int m, iter, done, brk, nan, restart;
-  int pend, pad;        // pend: the sums of the alpha step are formed
+  int due, pad;         // due: the step that the sums formed next (or last) are for
   int mchk, stall_win;  // half-step of that checkpoint; its spacing (0: off)
   int stalled, pad2;    // the bound stalled: the solve ends unconfirmed
 };
@@ -104,7 +105,7 @@ __device__ __forceinline__ void tq_resid(TqSt& S, const double* o) {
   S.done = (rr <= S.thr2) || S.nan;
   S.brk = 0;
   S.restart = S.done ? 0 : 2;   // 2: the first product, v = uhat = B u, is due
-  S.pend = !S.done;
+  S.due = S.done ? kTqNone : kTqAlpha;
   S.tau = sqrt(rr);
   S.theta = 0.0;
   S.eta = z_t{0.0, 0.0};
@@ -115,7 +116,7 @@ __device__ __forceinline__ void tq_resid(TqSt& S, const double* o) {
 }
 // alpha = rho / r*^H v
 __device__ __forceinline__ void tq_alpha(TqSt& S, const double* o) {
-  S.pend = 0;
+  S.due = kTqEven;
   S.restart = 0;
   const z_t sg = {o[0], o[1]};
   if (norm2(sg) == 0.0 || !isfinite(o[0]) || !isfinite(o[1])) S.brk = 1;
@@ -130,23 +131,26 @@ __device__ __forceinline__ void tq_odd(TqSt& S, const double* o) {
     S.beta = cdiv(rho1, S.rho);
     S.rho = rho1;
   }
-  S.pend = !tq_off(S);   // k_tq_odd3 forms the sums of the alpha step
+  S.due = tq_off(S) ? kTqNone : kTqAlpha;   // k_tq_odd3 forms the sums of the alpha step
 }
-__device__ __forceinline__ void tq_even(TqSt& S, const double* o) { tq_qmr(S, o[0]); }
+__device__ __forceinline__ void tq_even(TqSt& S, const double* o) {
+  S.due = kTqOdd;
+  tq_qmr(S, o[0]);
+}
 struct TqResid {
   __device__ bool on(const TqSt& S) const { return S.restart == 1; }
   __device__ void operator()(TqSt& S, const double* o) const { tq_resid(S, o); }
 };
 struct TqAlpha {
-  __device__ bool on(const TqSt& S) const { return S.pend; }
+  __device__ bool on(const TqSt& S) const { return S.due == kTqAlpha; }
   __device__ void operator()(TqSt& S, const double* o) const { tq_alpha(S, o); }
 };
 struct TqEven {
-  __device__ bool on(const TqSt& S) const { return !tq_off(S); }
+  __device__ bool on(const TqSt& S) const { return !tq_off(S) && S.due == kTqEven; }
   __device__ void operator()(TqSt& S, const double* o) const { tq_even(S, o); }
 };
 struct TqOdd {
-  __device__ bool on(const TqSt& S) const { return !tq_off(S); }
+  __device__ bool on(const TqSt& S) const { return !tq_off(S) && S.due == kTqOdd; }
   __device__ void operator()(TqSt& S, const double* o) const { tq_odd(S, o); }
 };
 
@@ -198,7 +202,7 @@ __global__ void HZ_PRODUCT_BOUNDS k_tq_resid_prod(Seg L, SellOp<T> A, const TqSt
 template <typename T, int F>
 __global__ void __launch_bounds__(kBlock) k_tq_even1(Seg L, TzOp Z, Part P, const TqSt* in, TqSt* out, TqV<T> V, double* part) {
   const SumTile t = vec_tile_sums(L);
-  const TqSt& S = advance<2>(P, in, out, t, first_block(L, t), TqAlpha{});
+  const TqSt& S = advance<2, (F < kFormTensor)>(P, in, out, t, first_block(L, t), TqAlpha{});
   if (tq_off(S)) return;
   const TzSeg B = form_seg<F>(Z, t);
   const z_t a = S.alpha;
@@ -218,14 +222,16 @@ __global__ void __launch_bounds__(kBlock) k_tq_even1(Seg L, TzOp Z, Part P, cons
 }
 
 // theta, tau, eta; x += eta d; then (unless stopping) uhat = B u' (stored forms).
+// prev: the state before the step, whoever made it.
 // x is updated ahead of the product: with eta and the stop flag held across it
 // the kernel took 98 VGPRs instead of 92 and lost a wave per SIMD (38.5 -> 42.3
 // us at 289,937 rows in split form).
 template <typename T, int F>
-__global__ void HZ_PRODUCT_BOUNDS k_tq_even2(Seg L, SellOp<T> A, Part P, const TqSt* in, TqSt* out, TqV<T> V) {
+__global__ void HZ_PRODUCT_BOUNDS k_tq_even2(Seg L, SellOp<T> A, Part P, const TqSt* prev, const TqSt* in, TqSt* out,
+                                             TqV<T> V) {
   const Tile t = tile_of(L);
-  const bool was_done = in[t.seg].done;
-  const TqSt& S = advance<1>(P, in, out, t, first_block(L, t), TqEven{});
+  const bool was_done = prev[t.seg].done;
+  const TqSt& S = advance<1, (F < kFormTensor)>(P, in, out, t, first_block(L, t), TqEven{});
   if (S.brk || S.nan || was_done) return;
   V.x[t.row] = zt<T>(zd(V.x[t.row]) + S.eta * zd(V.d[t.row]));
   if (S.done) return;
@@ -260,11 +266,11 @@ __global__ void __launch_bounds__(kBlock) k_tq_odd1(Seg L, const TqSt* st, TqV<T
 // and d again (12 -> 9 vector passes; at 161x97x81 nodes 45.8 -> 38.1 us,
 // and one launch less where launches count).
 template <typename T, int F>
-__global__ void HZ_PRODUCT_BOUNDS k_tq_even2_odd1(Seg L, SellOp<T> A, Part P, const TqSt* in, TqSt* out, TqV<T> V,
-                                                  double* part) {
+__global__ void HZ_PRODUCT_BOUNDS k_tq_even2_odd1(Seg L, SellOp<T> A, Part P, const TqSt* prev, const TqSt* in,
+                                                  TqSt* out, TqV<T> V, double* part) {
   const SumTile t = prod_tile_sums<F>(L);
-  const bool was_done = in[t.seg].done;
-  const TqSt& S = advance<1>(P, in, out, t, first_block(L, t), TqEven{});
+  const bool was_done = prev[t.seg].done;
+  const TqSt& S = advance<1, (F < kFormTensor)>(P, in, out, t, first_block(L, t), TqEven{});
   if (S.brk || S.nan || was_done) return;
   const z_t eta = S.eta, a = S.alpha;
   const z_t g = (S.theta * S.theta) * cdiv(eta, a);
@@ -289,10 +295,11 @@ __global__ void HZ_PRODUCT_BOUNDS k_tq_even2_odd1(Seg L, SellOp<T> A, Part P, co
 
 // theta, tau, eta, beta; x += eta d; then (unless stopping) u = w + beta u'
 template <typename T, int F>
-__global__ void __launch_bounds__(kBlock) k_tq_odd2(Seg L, TzOp Z, Part P, const TqSt* in, TqSt* out, TqV<T> V) {
+__global__ void __launch_bounds__(kBlock) k_tq_odd2(Seg L, TzOp Z, Part P, const TqSt* prev, const TqSt* in, TqSt* out,
+                                                    TqV<T> V) {
   const Tile t = vec_tile(L);
-  const bool was_done = in[t.seg].done;
-  const TqSt& S = advance<3>(P, in, out, t, first_block(L, t), TqOdd{});
+  const bool was_done = prev[t.seg].done;
+  const TqSt& S = advance<3, (F < kFormTensor)>(P, in, out, t, first_block(L, t), TqOdd{});
   if (S.nan || (S.brk && !S.done) || was_done) return;
   const TzSeg B = form_seg<F>(Z, t);
   if (S.done) {
@@ -368,12 +375,12 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     if (rc) return rc;
     *vecs[i] = b->as<cx<T>>();
   }
-  // state slots: start of a pair, after alpha, after the even half-step
-  DevBuf* stb = ctx->buf(p + "st", sizeof(TqSt) * 3 * S.nseg, &rc);
+  // state slots: start of a pair, after alpha, after the even half-step; one nobody reads
+  DevBuf* stb = ctx->buf(p + "st", sizeof(TqSt) * 4 * S.nseg, &rc);
   if (rc) return rc;
   DevBuf* fnb = ctx->buf(p + "fn2", sizeof(double) * S.nseg, &rc);
   if (rc) return rc;
-  TqSt *st = stb->as<TqSt>(), *st_a = st + S.nseg, *st_e = st_a + S.nseg;   // st: what a pair starts from
+  TqSt *st = stb->as<TqSt>(), *st_a = st + S.nseg, *st_e = st_a + S.nseg, *st_u = st_e + S.nseg;   // st: what a pair starts from
   hipStream_t s = ctx->stream;
   const Seg& L = S.dev;
   const Seg& P = prod_seg(A, L);   // the products' layout
@@ -383,7 +390,7 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
   out->fnorm.resize(S.nseg);
   for (int i = 0; i < S.nseg; ++i) out->fnorm[i] = std::sqrt(fn2[i]);
   HZ_HIP(hipMemcpyAsync(fnb->p, fn2.data(), sizeof(double) * S.nseg, hipMemcpyHostToDevice, s));
-  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(TqSt) * 3 * S.nseg, s));
+  HZ_HIP(hipMemsetAsync(stb->p, 0, sizeof(TqSt) * 4 * S.nseg, s));
   k_tq_set_thr<<<ceil_div(S.nseg, kBlock), kBlock, 0, s>>>(S.nseg, st, fnb->as<double>(), ctl.tol,
                                                             ctl.stall_halfsteps);
   HZ_HIP(hipGetLastError());
@@ -416,18 +423,18 @@ int tfqmr_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* f, 
     return poll.wait(poll.posted - 1);
   };
   auto enqueue_pair = [&]() -> int {
-    HZ_BY_SCALING(A, k_tq_even1<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, st, st_a, V, pe.raw));
+    HZ_BY_SCALING(A, k_tq_even1<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, pa.part, pa.from(st, st_a), pa.to(st_a, st_u), V, pe.raw));
     HZ_TRY(pe.step<1>(s, st_a, st_e, TqEven{}));
     if (A.tz.on == 1) {
-      k_tq_even2_odd1<T, kFormTensor><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, st_e, V, po.raw);
+      k_tq_even2_odd1<T, kFormTensor><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, pe.from(st_a, st_e), pe.to(st_e, st_u), V, po.raw);
     } else if (A.tz.on) {
-      k_tq_even2_odd1<T, kFormTensorExt><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, st_e, V, po.raw);
+      k_tq_even2_odd1<T, kFormTensorExt><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, pe.from(st_a, st_e), pe.to(st_e, st_u), V, po.raw);
     } else {
-      HZ_BY_STORED(A, k_tq_even2<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, st_e, V));
+      HZ_BY_STORED(A, k_tq_even2<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, pe.part, st_a, pe.from(st_a, st_e), pe.to(st_e, st_u), V));
       k_tq_odd1<T><<<W.nblk, kBlock, 0, s>>>(W, st_e, V, po.raw);
     }
     HZ_TRY(po.step<3>(s, st_e, st, TqOdd{}));
-    HZ_BY_SCALING(A, k_tq_odd2<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, st_e, st, V));
+    HZ_BY_SCALING(A, k_tq_odd2<T, F><<<W.nblk, kBlock, 0, s>>>(W, A.tz, po.part, st_e, po.from(st_e, st), po.to(st, st_u), V));
     HZ_BY_FORM(A, k_tq_odd3<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pa.raw));
     HZ_TRY(pa.step<2>(s, st, st_a, TqAlpha{}));
     HZ_HIP(hipGetLastError());

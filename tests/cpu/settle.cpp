@@ -11,12 +11,14 @@ using St = BlSt;
 constexpr int kSums = 3;
 static void start(St& S) { S.rho0 = S.omega = z_t{1.0, 0.5}; }
 using Pending = BlCycle;
+constexpr int kDue = kBlCycle;
 static void breaks(St& S, double* sums) { S.trunc = 1; sums[0] = sums[2] = 2.0; }   // a truncated Gram matrix
 #else
 using St = TqSt;
 constexpr int kSums = 2;
 static void start(St& S) { S.rho = z_t{1.0, 0.5}; }
 using Pending = TqAlpha;
+constexpr int kDue = kTqAlpha;
 static void breaks(St& S, double* sums) { sums[0] = sums[1] = 0.0; }                // r*^H v = 0
 #endif
 
@@ -34,7 +36,7 @@ int main() {
             for (double& v : part[s]) v = 1.5;
             start(st[s]);
             st[s].alpha = z_t{0.5, 0.25};
-            st[s].pend = pend;
+            st[s].due = pend ? kDue : 0;
             st[s].restart = 1 - brk;   // left by an earlier restart
             if (brk && pend) breaks(st[s], part[s]);
             if (brk && !pend) st[s].brk = 1;
@@ -48,9 +50,9 @@ int main() {
                              [&] { k_step<kSums, St>(L, &part[0][0], st, st, nullptr, nullptr, Settle<Pending>{{}, all}); });
           for (int s = 0; s < 2; ++s) {
             out[down][s] = st[s];
-            if (st[s].restart != (all || brk) || st[s].brk != brk || st[s].pend) {
-              std::printf("all %d pending %d breaks %d, threads %s: segment %d restart %d brk %d pend %d\n", all, pend, brk,
-                          down ? "downwards" : "upwards", s, st[s].restart, st[s].brk, st[s].pend);
+            if (st[s].restart != (all || brk) || st[s].brk != brk || st[s].due == kDue) {
+              std::printf("all %d pending %d breaks %d, threads %s: segment %d restart %d brk %d due %d\n", all, pend, brk,
+                          down ? "downwards" : "upwards", s, st[s].restart, st[s].brk, st[s].due);
               ++bad;
             }
           }
