@@ -386,8 +386,9 @@ int hz_dd_alpha(double k, double H, double h, int32_t sides, hz_c128* alpha);
  * adjoint and hz_apply use the tensor form (HZ_SPMV_TENSOR): no stored
  * entries, the product is formed from the 1-D matrices of the axes, and a
  * vector is read and written once (with an absorption field also 8 bytes per
- * element).  HZ_SPMV_SOLVER keeps naming the stored form that stands in where
- * the tensor form does not apply.  Environment variables HZ_TENSOR=0,
+ * element).  HZ_SPMV_SOLVER names the stored form that the solvers take where
+ * the tensor form does not apply, also on a context whose solvers use the
+ * tensor form: ask for HZ_SPMV_TENSOR to time that one.  Environment variables HZ_TENSOR=0,
  * HZ_STENCIL=0 and HZ_SPLIT=0 (read when the context is created) disable the
  * tensor, the tensor and stencil, and all three forms. */
 enum { HZ_SPMV_SOLVER = 0, HZ_SPMV_COMPLEX = 1, HZ_SPMV_SPLIT = 2, HZ_SPMV_STENCIL = 3, HZ_SPMV_TENSOR = 4 };
@@ -398,10 +399,10 @@ enum { HZ_SPMV_SOLVER = 0, HZ_SPMV_COMPLEX = 1, HZ_SPMV_SPLIT = 2, HZ_SPMV_STENC
  * on that stream, and returns the average duration of one product in
  * milliseconds.  precision HZ_FP64 times the complex128 product of the FP64
  * solvers; HZ_MIXED the complex64 product of the mixed-precision inner
- * solves.  format: HZ_SPMV_SOLVER (the stored form the solvers use),
+ * solves.  format: HZ_SPMV_SOLVER (the solvers' stored form, see above),
  * HZ_SPMV_COMPLEX, HZ_SPMV_SPLIT, HZ_SPMV_STENCIL or HZ_SPMV_TENSOR
- * (HZ_ERR_STATE if that form is not formed).  x and y are internal buffers.  Host result; synchronises the
- * stream. */
+ * (HZ_ERR_STATE if that form is not formed).  x and y are internal buffers.
+ * Host result; synchronises the stream. */
 int hz_time_spmv(hz_ctx ctx, int32_t reps, int32_t precision, int32_t format, double* avg_ms);
 
 /* Measurement of the frequency sweep's multi-vector product (the sparse

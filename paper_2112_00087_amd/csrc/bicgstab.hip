@@ -3,10 +3,11 @@
 //
 // One iteration of van der Vorst's method is five kernels, two of them
 // products.  The scalar steps (alpha, omega, rho and beta) run at the start
-// of the kernel that needs them (advance), on a state that moves through
-// three slots.  The early-exit test on ||s|| rides on the omega step.  The
-// scalars never leave the device; the host reads the per-segment state every
-// few iterations, one chunk behind.
+// of the kernel that needs them (advance), on large systems in three kernels of
+// their own (k_step), on a state that moves through three slots.  The
+// early-exit test on ||s|| rides on the omega step.  The scalars never leave
+// the device; the host reads the per-segment state after each chunk of
+// iterations, once the next chunk is queued (Pace).
 // Every kernel first reads its segment's flags and returns if that segment
 // has converged, so extra queued iterations cost only empty launches.
 #include <chrono>
@@ -296,11 +297,11 @@ int bicgstab_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>* 
     return poll.posted_one();
   };
   auto enqueue_resid = [&]() -> int {
-    // the slot an iteration starts from takes up the pending sums
+    // the slot an iteration starts from takes up the sums of its rho step
     if (resid_calls > 0) HZ_TRY(pn.step_now<3>(s, st, st, BiRho{}));
     HZ_BY_FORM(A, k_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, V, pr.raw));
     HZ_HIP(hipGetLastError());
-    // (nothing is pending: st_a is what the next iteration's first step would make of st)
+    // (no rho step is due: st_a is what the next iteration's first step would make of st)
     HZ_TRY(pr.step_now<1>(s, st, st, BiResid{}, poll.slot<BiSt>(), st_a));
     ++resid_calls;
     return poll.posted_one();

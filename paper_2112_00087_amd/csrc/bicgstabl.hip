@@ -16,10 +16,11 @@
 // leading well-conditioned directions and the segment restarts from its
 // true residual after the cycle.
 //
-// Per cycle: 4 l + 3 launches, 2 l products.  The scalar steps run at the
-// start of the kernel that needs them (advance), on a state that moves
-// through three slots.  Krylov scalars stay on the device; the host polls the
-// per-segment state every few cycles, one chunk behind.
+// Per cycle: 4 l + 3 launches, 2 l products, and a launch for the report once a
+// chunk.  The scalar steps run at the start of the kernel that needs them
+// (advance) or, on large systems, 2 l in kernels of their own (k_step), on a state
+// that moves through three slots.  Krylov scalars stay on the device; the host
+// reads the per-segment state after each chunk of cycles (Pace).
 //
 // In the tensor form the products take D^-1-scaled inputs: the kernels that
 // make u_j and r_j also write the scaled copy that their product reads, and x
@@ -444,7 +445,7 @@ int bicgstabl_run(hz_ctx ctx, const SegHost& S, const SellOp<T>& A, const cx<T>*
     if (A.tz.on && resid_calls > 0) k_bl_fold<T><<<W.nblk, kBlock, 0, s>>>(W, A.tz, st, V, 0);
     HZ_BY_FORM(A, k_bl_resid<T, F><<<P.nblk, kBlock, 0, s>>>(P, A, st, V, pr.raw));
     HZ_HIP(hipGetLastError());
-    // (nothing is pending: st_b is what the next cycle's first step would make of st)
+    // (no step is due: st_b is what the next cycle's first step would make of st)
     HZ_TRY(pr.step_now<1>(s, st, st, BlResid{}, poll.slot<BlSt>(), st_b));
     ++resid_calls;
     HZ_TRY(poll.posted_one());

@@ -72,7 +72,7 @@ struct TzSeg {                    // one box: a segment's rows
 };
 struct TzOp {
   int on = 0;                     // 1: plain, 2: with an absorption field
-  int scale = 0;                  // x is scaled by 1 / diag(A) as it is loaded
+  int scale = 0;                  // the operator is A D^-1: vector kernels scale the product's inputs (tz_pre)
   int nseg = 0;
   TzSeg s0 = {};                  // the only segment (nseg 1)
   const TzSeg* segs = nullptr;    // [nseg] on the device
@@ -373,9 +373,9 @@ struct Part {
 // A step f of a state St: f.on(state) says whether it is due, f(state, sums) makes it.
 //
 // All threads of the block call it; the state is in LDS afterwards.
-// EARLY: leave at once where the step has been made.  The stored forms, which run
-// so beyond 260,000 rows, gain 1 to 2% by it; the tensor form, which hardly ever
-// does, would lose 1% on small systems by the test.
+// EARLY: leave at once where the step has been made.  The stored forms beyond
+// 260,000 rows, where it is (kMaxConsumed), gain 1 to 2% by it; in the tensor form
+// it gains nothing at 1.26 million and the test costs small systems 1%.
 template <int NQ, bool EARLY, class St, class Step>
 __device__ __forceinline__ const St& advance(const Part& P, const St* in, St* out, const Tile& t, bool first, Step f) {
   constexpr int kPasses = kFinBlock / kBlock, kWaves = kFinBlock / kWave;
@@ -538,7 +538,7 @@ __global__ void __launch_bounds__(kFinBlock) k_step(Seg L, const double* part, c
   if (copy && threadIdx.x < kWords) reinterpret_cast<int*>(copy + s)[threadIdx.x] = sw[threadIdx.x];
   if (next && threadIdx.x < kWords) reinterpret_cast<int*>(next + s)[threadIdx.x] = sw[threadIdx.x];
 }
-// Takes up a segment's pending sums and sets which segments restart: all of
+// Makes a segment's due step and sets which segments restart: all of
 // them, or those that broke down.  One step on the state in LDS: the words of
 // the stored state are written by different threads, so none may be read or
 // written again behind it.

@@ -2528,7 +2528,8 @@ __global__ void __launch_bounds__(kBlock) k_sl_dots(int64_t total, int s, const 
 // All NQ sums of column c over the G_ blocks' partials, by one block in one
 // pass (the order of block_sum_strided for each), valid in every thread.  One
 // sum after the other cost a reload latency and two barriers each: 44 us for
-// the 28 sums and the solve of k_sl_mr<4>, 15 us now.
+// the 28 sums and the solve of k_sl_mr<4>, 12.6 to 16.9 us now (traced at
+// 37x25x19 with 13 columns).
 template <int NQ>
 __device__ __forceinline__ void sl_totals(int G_, int s, const double* __restrict__ part, int c, double (&o)[NQ]) {
   __shared__ double lds[NQ][kBlock / kWave];

@@ -17,16 +17,18 @@
 // complex128 Kx x is formed from differences (its rows sum to zero but for the
 // walls), so it rounds relative to the result; FP64 sums of complex64 vectors
 // need no such care.  The product is bound by the block's read and write
-// (67 us of copy at 80x48x40 and 64 columns, where it takes 92; the stencil
-// form took 163 us, streaming 27 pairs a row through the broadcast unit); the
+// (67 us of copy at 80x48x40 and 64 columns, where it takes 92 repeated alone and
+// 109 between a solve's vector passes, which leave less of x in the caches; the
+// stencil form took 163 us, streaming 27 pairs a row through the broadcast unit); the
 // patch is 2 x 2 because its 4 rows in 16 loads (4 from L1 / L2 per row,
 // against 9 in the stencil form) still leave two waves per SIMD with the next
 // plane's loads in flight.  With an absorption field 118 : 200 us there; fewer
 // columns then leave one wave per SIMD: at two, 54 registers went to scratch memory
 // (32 columns at 80x48x40 124 -> 76 us, 16 at 20x12x10 12.1 -> 8.0 us).
 // On small blocks the march is a chain of load latencies: 13 : 126 us at
-// 80x48x40 and 4 columns, 10.8 : 13.4 us at 37x25x19 and 13.  (One plane a
-// wave with all its loads at once took 11.2 us there, and 6.9 : 7.3 us at 4.)
+// 80x48x40 and 4 columns, 10.8 : 13.4 us at 37x25x19 and 13, laid out as 16
+// (a later run on another card: 9.3).  One plane a wave with all its loads at
+// once took 11.2 : 9.3 us there, and 6.9 : 7.3 us at 4.
 // Arithmetic is FP64 for both vector types.
 #pragma once
 

@@ -11,8 +11,9 @@
 //          v = beta uhat + beta^2 v + B u;  uhat = B u;  alpha = rho' / r*^H v
 // Kernels: 3 vector and 2 product (with fused dot) per pair; in the tensor form
 // the odd update rides on the even product, 2 vector and 2 product kernels.
-// The scalar steps run at the start of the kernel that needs them (advance),
-// on a state that moves through three slots.  In the tensor form u, u', d and
+// The scalar steps run at the start of the kernel that needs them (advance) or,
+// on large systems, in two or three kernels of their own (k_step), on a state
+// that moves through three slots.  In the tensor form u, u', d and
 // x are kept scaled by D^-1 (x is the solution itself), so only w and v are
 // scaled where they enter u and u' and the product's inputs need no pass of
 // their own.  u' lives in its own buffer for the odd half-step (it is never

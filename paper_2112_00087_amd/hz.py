@@ -304,9 +304,10 @@ class Helmholtz:
         return dict(perm=perm, slots=sl.value, bandwidth=bw.value, n_imag=ni.value)
 
     def time_spmv(self, reps=100, precision="fp64", form="solver"):
-        """Average duration (ms) of one sparse product of the given storage form
-        ("solver", "complex", "split" or "stencil"), HIP events on the context
-        stream."""
+        """Average duration (ms) of one sparse product of the given form
+        ("complex", "split", "stencil", "tensor", or "solver": the solvers'
+        stored form, also where they run the tensor form), HIP events on the
+        context stream."""
         ms = C.c_double()
         check(lib().hz_time_spmv(self.ctx, int(reps), PRECISIONS[precision], SPMV_FORMS[form], C.byref(ms)),
               False)
